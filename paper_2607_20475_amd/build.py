@@ -18,7 +18,7 @@ OBJ_DIR = os.path.join(HERE, "_build")
 LIB_PATH = os.path.join(HERE, "libss.so")
 # measurement aid of bench.py (a plain streaming read), kept out of libss.so
 BENCH_LIB_PATH = os.path.join(HERE, "libss_bench.so")
-HEADERS = [os.path.join(CSRC, h) for h in ("ss_impl.hpp", "ss_device.hpp", "ss_launch.hpp")] + [
+HEADERS = [os.path.join(CSRC, h) for h in ("ss_impl.hpp", "ss_row.hpp", "ss_device.hpp", "ss_launch.hpp")] + [
     os.path.join(ROOT, "include", "ss.h")
 ]
 

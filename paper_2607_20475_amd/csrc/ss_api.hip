@@ -1,6 +1,6 @@
 // ss_api.hip -- host side of libss.so: workspace layout, argument validation,
 // launch sequence and the C ABI declared in ss.h.
-#include "ss_impl.hpp"
+#include "ss_row.hpp"
 #include "ss_launch.hpp"
 
 namespace ss {
@@ -23,12 +23,7 @@ static bool make_layout(int op, int B, int V, int L, int k_max, int dtype, Layou
   const int rows = op == OP_VERIFY ? B * (L + 1) : B;
   const int U = (V + kUE - 1) / kUE;
   const int cap = unit_cap(k_max, U, dtype);
-  // pool entries: candidates; after selection T in the front half and, for
-  // the sampling ops, its fixed-point weights in the back half
-  int pcap = 2 * k_max + 128;
-  if (pcap < 1024) pcap = 1024;
-  if (pcap < next_pow2(k_max)) pcap = next_pow2(k_max);
-  pcap = (pcap + 255) & ~255;
+  const int pcap = stage_cap(k_max);
   size_t o = 0;
   lay->off_rec = o;
   o = align256(o + (size_t)rows * U * 16);
@@ -61,7 +56,7 @@ static bool make_layout(int op, int B, int V, int L, int k_max, int dtype, Layou
   lay->cap = cap;
   lay->pcap = pcap;
   lay->rows = rows;
-  lay->smem = kSmemFixed + 8 * (pcap + kBlock);  // pool plus one dump slot per thread
+  lay->smem = merge_smem(k_max);
   return true;
 }
 
@@ -108,24 +103,24 @@ static int esize(int dtype) { return dtype == SS_BF16 ? 2 : 4; }
 // Gumbel-max draw has its own, so plain sampling carries neither extension.
 static int merge_op(const KArgs& k) { return (k.op == OP_SAMPLE && (k.full || k.gum)) ? (int)OP_SAMPLE_X : k.op; }
 
-static void launch_merge_any(const KArgs& k, int dtype, dim3 grid, dim3 block, int smem, hipStream_t st) {
+static void launch_merge_any(const KArgs& k, int dtype, int rows, int smem, hipStream_t st) {
   if (dtype == SS_BF16) {
     switch (merge_op(k)) {
-      case OP_TOPK: launch_merge<SS_BF16, OP_TOPK>(k, grid, block, smem, st); break;
-      case OP_SAMPLE: launch_merge<SS_BF16, OP_SAMPLE>(k, grid, block, smem, st); break;
-      case OP_VERIFY: launch_merge<SS_BF16, OP_VERIFY>(k, grid, block, smem, st); break;
-      case OP_LOGPROBS: launch_merge<SS_BF16, OP_LOGPROBS>(k, grid, block, smem, st); break;
-      case OP_SAMPLE_X: launch_merge<SS_BF16, OP_SAMPLE_X>(k, grid, block, smem, st); break;
-      default: launch_merge<SS_BF16, OP_PROCESS>(k, grid, block, smem, st); break;
+      case OP_TOPK: launch_merge<SS_BF16, OP_TOPK>(k, rows, smem, st); break;
+      case OP_SAMPLE: launch_merge<SS_BF16, OP_SAMPLE>(k, rows, smem, st); break;
+      case OP_VERIFY: launch_merge<SS_BF16, OP_VERIFY>(k, rows, smem, st); break;
+      case OP_LOGPROBS: launch_merge<SS_BF16, OP_LOGPROBS>(k, rows, smem, st); break;
+      case OP_SAMPLE_X: launch_merge<SS_BF16, OP_SAMPLE_X>(k, rows, smem, st); break;
+      default: launch_merge<SS_BF16, OP_PROCESS>(k, rows, smem, st); break;
     }
   } else {
     switch (merge_op(k)) {
-      case OP_TOPK: launch_merge<SS_F32, OP_TOPK>(k, grid, block, smem, st); break;
-      case OP_SAMPLE: launch_merge<SS_F32, OP_SAMPLE>(k, grid, block, smem, st); break;
-      case OP_VERIFY: launch_merge<SS_F32, OP_VERIFY>(k, grid, block, smem, st); break;
-      case OP_LOGPROBS: launch_merge<SS_F32, OP_LOGPROBS>(k, grid, block, smem, st); break;
-      case OP_SAMPLE_X: launch_merge<SS_F32, OP_SAMPLE_X>(k, grid, block, smem, st); break;
-      default: launch_merge<SS_F32, OP_PROCESS>(k, grid, block, smem, st); break;
+      case OP_TOPK: launch_merge<SS_F32, OP_TOPK>(k, rows, smem, st); break;
+      case OP_SAMPLE: launch_merge<SS_F32, OP_SAMPLE>(k, rows, smem, st); break;
+      case OP_VERIFY: launch_merge<SS_F32, OP_VERIFY>(k, rows, smem, st); break;
+      case OP_LOGPROBS: launch_merge<SS_F32, OP_LOGPROBS>(k, rows, smem, st); break;
+      case OP_SAMPLE_X: launch_merge<SS_F32, OP_SAMPLE_X>(k, rows, smem, st); break;
+      default: launch_merge<SS_F32, OP_PROCESS>(k, rows, smem, st); break;
     }
   }
 }
@@ -171,25 +166,26 @@ static ss_status launch(KArgs& k, int dtype, const Layout& lay, void* ws, hipStr
   k.ptab = reinterpret_cast<uint32_t*>(w + lay.off_ptab);
   k.usum = (k.op == OP_LOGPROBS || k.full) ? reinterpret_cast<double*>(w + lay.off_usum) : nullptr;
   // patch-table workgroups (a multiple of 8, so the stream's XCD remap holds)
-  k.patch_wgs = k.op == OP_TOPK ? 0 : (lay.rows + 7) & ~7;
+  k.patch_wgs = (k.feat & (SS_REP | SS_FREQ | SS_PRES | SS_BIAS)) ? (lay.rows + 7) & ~7 : 0;
   const int di = dtype == SS_BF16 ? 1 : 0;
   const int mop = merge_op(k);
   if (!smem_configured[di][mop]) {
     // the largest dynamic LDS any call can ask for
-    const int maxb = kSmemFixed + 8 * (((2 * SS_MAX_K + 128 + 255) & ~255) + kBlock);
+    const int maxb = merge_smem(SS_MAX_K);
     if (merge_smem_any(dtype, mop, maxb) != hipSuccess) return SS_ERR_HIP;
     smem_configured[di][mop] = true;
   }
   const int nunits = lay.rows * lay.U;
   const dim3 grid((unsigned)(k.patch_wgs + (nunits + kSWaves - 1) / kSWaves)), sblock(kSBlock),
-      rgrid((unsigned)lay.rows), block(kBlock);
-  const int psmem = k.patch_wgs ? (int)sizeof(PSmem) : 0;
+      block(kBlock);
+  const int psmem = k.patch_wgs ? (int)sizeof(PSmem) : kSWaves * (int)sizeof(WStage);
+  static_assert(sizeof(PSmem) >= kSWaves * sizeof(WStage), "the emission strips share the patch tables' space");
   const bool lp = k.op == OP_LOGPROBS || k.full;  // units add their normaliser shares
   if (dtype == SS_BF16)
     lp ? launch_stream<SS_BF16, true>(k, grid, sblock, psmem, st) : launch_stream<SS_BF16, false>(k, grid, sblock, psmem, st);
   else
     lp ? launch_stream<SS_F32, true>(k, grid, sblock, psmem, st) : launch_stream<SS_F32, false>(k, grid, sblock, psmem, st);
-  launch_merge_any(k, dtype, rgrid, block, lay.smem, st);
+  launch_merge_any(k, dtype, lay.rows, lay.smem, st);
   if (k.op == OP_VERIFY) launch_assemble(k, dim3((unsigned)((k.B + kBlock - 1) / kBlock)), block, st);
   if (materialize) {
     const int T = (k.V + 4095) / 4096;

@@ -103,6 +103,12 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_s_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
+// Orders this wavefront's own LDS writes before its later LDS reads.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
 __device__ __forceinline__ int lane() { return (int)__lane_id(); }
 __device__ __forceinline__ int wave() { return (int)(threadIdx.x >> 6); }
 
@@ -179,68 +185,14 @@ __device__ __forceinline__ T wave_incl_scan(T v) {
   return v;
 }
 
-// Workgroup reductions through a small LDS scratch of kWaves entries.
-// Every call ends with a barrier so the scratch can be reused at once.
-template <typename T>
-__device__ inline T block_max(T v, T* scratch) {
-  v = wave_max(v);
-  if (lane() == 0) scratch[wave()] = v;
-  lds_barrier();
-  T r = scratch[0];
-#pragma unroll
-  for (int w = 1; w < kWaves; ++w) r = scratch[w] > r ? scratch[w] : r;
-  lds_barrier();
-  return r;
-}
-template <typename T>
-__device__ inline T block_min(T v, T* scratch) {
-  v = wave_min(v);
-  if (lane() == 0) scratch[wave()] = v;
-  lds_barrier();
-  T r = scratch[0];
-#pragma unroll
-  for (int w = 1; w < kWaves; ++w) r = scratch[w] < r ? scratch[w] : r;
-  lds_barrier();
-  return r;
-}
-// Deterministic sum: fixed shuffle tree, then waves in order.
-template <typename T>
-__device__ inline T block_sum(T v, T* scratch) {
-  v = wave_sum(v);
-  if (lane() == 0) scratch[wave()] = v;
-  lds_barrier();
-  T r = scratch[0];
-#pragma unroll
-  for (int w = 1; w < kWaves; ++w) r += scratch[w];
-  lds_barrier();
-  return r;
-}
-// Exclusive scan over threads in thread order; returns this thread's offset,
-// writes the workgroup total.
-template <typename T>
-__device__ inline T block_excl_scan(T v, T* scratch, T& total) {
-  const T inc = wave_incl_scan(v);
-  if (lane() == 63) scratch[wave()] = inc;
-  lds_barrier();
-  T off = T(0), tot = T(0);
-#pragma unroll
-  for (int w = 0; w < kWaves; ++w) {
-    const T s = scratch[w];
-    if (w < wave()) off += s;
-    tot += s;
-  }
-  lds_barrier();
-  total = tot;
-  return off + inc - v;
-}
-
 // ---------------------------------------------------------------------------
 // LDS bitonic sort, descending, of n (power of two) 64-bit keys.
 // ---------------------------------------------------------------------------
+template <int BS>
 __device__ inline void lds_sort_desc(uint64_t* a, int n) {
   for (int k = 2; k <= n; k <<= 1) {
     for (int j = k >> 1; j > 0; j >>= 1) {
-      for (int p = threadIdx.x; p < (n >> 1); p += kBlock) {
+      for (int p = threadIdx.x; p < (n >> 1); p += BS) {
         const int i = ((p & ~(j - 1)) << 1) | (p & (j - 1));
         const int m = i + j;
         const uint64_t x = a[i], y = a[m];
@@ -288,7 +240,7 @@ __device__ __forceinline__ uint32_t wave_excl_small(uint32_t c, uint32_t& total)
   return off;
 }
 
-__host__ __device__ inline int next_pow2(int v) {
+__host__ __device__ constexpr int next_pow2(int v) {
   int p = 1;
   while (p < v) p <<= 1;
   return p;

@@ -10,7 +10,7 @@ struct KArgs;
 template <int DT, bool LP>
 void launch_stream(const KArgs& k, dim3 grid, dim3 block, int smem, hipStream_t st);
 template <int DT, int OP>
-void launch_merge(const KArgs& k, dim3 grid, dim3 block, int smem, hipStream_t st);
+void launch_merge(const KArgs& k, int rows, int smem, hipStream_t st);
 template <int DT, int OP>
 hipError_t merge_smem_limit(int bytes);
 template <int DT>
@@ -19,7 +19,7 @@ void launch_assemble(const KArgs& k, dim3 grid, dim3 block, hipStream_t st);
 void launch_zero(uint32_t* p, size_t n, dim3 grid, dim3 block, hipStream_t st);
 
 #define SS_EXTERN_MERGE(DT, OP)                                                            \
-  extern template void launch_merge<DT, OP>(const KArgs&, dim3, dim3, int, hipStream_t); \
+  extern template void launch_merge<DT, OP>(const KArgs&, int, int, hipStream_t); \
   extern template hipError_t merge_smem_limit<DT, OP>(int);
 SS_EXTERN_MERGE(0, 0)
 SS_EXTERN_MERGE(0, 1)

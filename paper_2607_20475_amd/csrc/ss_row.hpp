@@ -1,0 +1,1298 @@
+// ss_row.hpp -- the merge kernel: one workgroup finishes one row.
+//
+//   1. One round trip loads everything: the request's parameters, the unit
+//      records, the first candidates of every unit (a fixed share of threads
+//      per unit, issued before the counts are known) and the row's patch table.
+//   2. Every emitted element whose composite (key, lower index first) reaches
+//      tc, the largest unit threshold, and every patched final value at or above
+//      it takes part; raw copies of patched ids drop out by a bitmap.  No unit
+//      having overflowed, these are all of the row's elements at or above tc: if
+//      at least k of them are, they hold its exact top-k.  Otherwise (skewed or
+//      tied rows, patched top tokens) an exact slow path re-reads the units that
+//      could hide a top-k element.
+//   3. Greedy rows take the maximum.  Other rows are sorted in one pass: a
+//      histogram over kNB equal key ranges between tc and the row maximum, a
+//      scan, a scatter into bin order, and each element's rank inside its bin by
+//      comparing it with the bin's few others.  Bins past the k-th element are
+//      left out.  Crowded bins (ties) are sorted by a bitonic network instead.
+//      (Radix selection, two radix searches for the cuts and a bitonic sort for
+//      lists took 26.8 us at B=64 V=2^17 bf16 with a 64-entry list, 87 us for
+//      top-k at B=256 V=2^18 fp32 k<=4096; this takes 9.8 and 23.5 us.)
+//   4. On the sorted list the Alg. 11 epilogue is one prefix sum of 2^-50
+//      fixed-point weights: top-p, min-p and the draw are each the first rank
+//      whose running mass crosses a target, found by the one thread that holds it.
+//
+// What bounds it is latency: a row is one workgroup's chain of one global round
+// trip and nine barriers (LDS only, so loads stay in flight across them).
+#pragma once
+#include "ss_impl.hpp"
+
+namespace ss {
+
+constexpr int kNBLog = 11;
+constexpr int kNB = 1 << kNBLog;  // key bins of the one-pass sort
+constexpr int kCrowd = 256;       // bins up to this occupancy are ranked by comparison
+constexpr uint32_t kNone = 0xFFFFFFFFu;
+
+// Threads of a merge workgroup.
+template <int DT, int OP>
+constexpr int merge_threads() {
+  return OP == OP_TOPK ? 1024 : kBlock;
+}
+constexpr int kMaxWaves = 16;
+
+struct MSmem {
+  uint64_t x64[3][kMaxWaves];  // scratch of the workgroup reductions
+  double rd[kMaxWaves];
+  uint32_t x32[4][kMaxWaves];
+  uint64_t bc64[4];
+  uint32_t bc[12];
+  uint32_t rmask[kMaxU / 32];  // units re-read by the slow path
+  alignas(16) uint32_t pbits[kPB / 32];  // bit pbit(id) set for every patched id
+  int32_t hk[kH];                        // patched id (or -1)
+  uint32_t hf[kH];                       // final key
+  alignas(16) uint32_t bins[kNB];        // counts, then starts, then ends; the slow path's digit counts
+};
+constexpr int kSmemFixed = (int)((sizeof(MSmem) + 15) & ~(size_t)15);
+// The sorted list's staging area: room for the k_cap leading elements and the
+// rest of the bin that holds the last of them; after it the sorted list.  The
+// two together hold the next power of two of the staging area (bitonic sort).
+__host__ __device__ constexpr int stage_cap(int k_cap) { return (k_cap + 512 + 255) & ~255; }
+__host__ __device__ constexpr int sorted_cap(int k_cap) {
+  const int s = stage_cap(k_cap), p = next_pow2(s) - s;
+  return (p > k_cap ? p : k_cap) + 8;  // rank loops read up to three entries past a bin
+}
+constexpr int merge_smem(int k_cap) { return kSmemFixed + 8 * (stage_cap(k_cap) + sorted_cap(k_cap)); }
+static_assert(merge_smem(SS_MAX_K) <= 160 * 1024, "merge LDS beyond a CU's 160 KiB");
+// The verification epilogue keeps a sparse draft list (one 64-bit entry per
+// listed id) over the patch bitmap and table, which are dead by then.
+static_assert(offsetof(MSmem, hk) == offsetof(MSmem, pbits) + sizeof(uint32_t) * (kPB / 32) &&
+                  offsetof(MSmem, hf) == offsetof(MSmem, hk) + sizeof(int32_t) * kH &&
+                  offsetof(MSmem, pbits) % 8 == 0 &&
+                  sizeof(uint32_t) * (kPB / 32 + 2 * kH) >= sizeof(uint64_t) * SS_MAX_K,
+              "sparse draft list view");
+__device__ __forceinline__ uint64_t* qlist_view(MSmem& S) { return reinterpret_cast<uint64_t*>(S.pbits); }
+
+// Workgroup reductions (scratch reusable on return).
+template <int BS, typename T, typename Op>
+__device__ __forceinline__ T wg_reduce(T v, T* scratch, Op op) {
+  v = wave_reduce(v, op);
+  if (lane() == 0) scratch[wave()] = v;
+  lds_barrier();
+  T r = scratch[0];
+#pragma unroll
+  for (int w = 1; w < BS / 64; ++w) r = op(r, scratch[w]);
+  lds_barrier();
+  return r;
+}
+template <int BS, typename T>
+__device__ __forceinline__ T wg_sum(T v, T* scratch) {
+  return wg_reduce<BS>(v, scratch, [](T x, T y) { return x + y; });
+}
+template <int BS, typename T>
+__device__ __forceinline__ T wg_max(T v, T* scratch) {
+  return wg_reduce<BS>(v, scratch, [](T x, T y) { return x > y ? x : y; });
+}
+
+// Patched-id bitmap position: the id itself when V <= kPB (the bitmap is then
+// exact), else an 18-bit hash (a set bit then needs a table lookup).
+__device__ __forceinline__ uint32_t pbit(int id, bool exact) {
+  return exact ? (uint32_t)id : (((uint32_t)id * 0x9E3779B1u) >> (32 - kPBLog));
+}
+// false only when id is certainly not patched (one LDS read)
+__device__ __forceinline__ bool maybe_patched(const MSmem& S, int id, bool exact) {
+  const uint32_t h = pbit(id, exact);
+  return (S.pbits[h >> 5] >> (h & 31)) & 1u;
+}
+__device__ __forceinline__ int hfind(const MSmem& S, int id) {
+  uint32_t s = hslot(id);
+  for (int p = 0; p < kProbe; ++p) {
+    const int k = S.hk[s];
+    if (k == id) return (int)s;
+    if (k < 0) return -1;
+    s = (s + 1) & (kH - 1);
+  }
+  return -1;
+}
+__device__ __forceinline__ bool lds_patched(const MSmem& S, int id, bool exact) {
+  return maybe_patched(S, id, exact) && (exact || hfind(S, id) >= 0);
+}
+
+
+// ---------------------------------------------------------------------------
+// Patch table of a row in global memory, used when the row's history and
+// bias lists hold more distinct ids than the LDS table: open addressing over
+// kGH slots.  The row's merge clears the tags before it inserts (a tag of
+// generation `gen` marks a slot of this call), so nothing depends on what the
+// workspace held before the call.
+// ---------------------------------------------------------------------------
+struct PatchG {
+  uint64_t* tag;
+  uint32_t* cnt;
+  uint32_t* fin;
+  uint32_t gen;
+};
+__device__ __forceinline__ uint32_t ghslot(int id) { return ((uint32_t)id * 2654435761u) >> 18; }  // 14 bits
+static_assert(kGH == 16384, "ghslot assumes 16384 slots");
+
+__device__ __forceinline__ int gfind(const PatchG& g, int id) {
+  const uint64_t want = ((uint64_t)g.gen << 32) | (uint32_t)(id + 1);
+  uint32_t s = ghslot(id);
+  for (int p = 0; p < kGProbe; ++p) {
+    const uint64_t t = __hip_atomic_load(&g.tag[s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (t == want) return (int)s;
+    if ((uint32_t)(t >> 32) != g.gen) return -1;
+    s = (s + 1) & (kGH - 1);
+  }
+  return -1;
+}
+// claims a slot for id (the claiming thread zeroes its count); -1 when full
+__device__ __forceinline__ int gclaim(const PatchG& g, int id) {
+  const uint64_t want = ((uint64_t)g.gen << 32) | (uint32_t)(id + 1);
+  uint32_t s = ghslot(id);
+  for (int p = 0; p < kGProbe; ++p) {
+    uint64_t t = __hip_atomic_load(&g.tag[s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (;;) {
+      if (t == want) return (int)s;
+      if ((uint32_t)(t >> 32) == g.gen) break;  // another id of this call
+      const uint64_t old = atomicCAS((unsigned long long*)&g.tag[s], (unsigned long long)t, (unsigned long long)want);
+      if (old == t) {
+        g.cnt[s] = 0u;
+        return (int)s;
+      }
+      t = old;
+    }
+    s = (s + 1) & (kGH - 1);
+  }
+  return -1;
+}
+
+// patch modes: 0 none, 1 LDS table, 2 global table, 3 linear lookups
+template <int DT>
+__device__ __forceinline__ bool is_patched(const Ctx& c, const MSmem& S, int pmode, const PatchG& g, int id) {
+  if (pmode == 0) return false;
+  if (pmode == 1) return lds_patched(S, id, c.pexact);
+  if (pmode == 2) return gfind(g, id) >= 0;
+  int cn;
+  bool hb;
+  float bs;
+  return lin_info(c, id, &cn, &hb, &bs);
+}
+
+// Builds the row's patch table in global memory when its lists hold more
+// distinct ids than the LDS table (status 2); returns the patch mode: 2, or 3
+// (linear lookups) when that table overflows too.
+template <int DT, int BS>
+__device__ __forceinline__ int global_table(const KArgs& a, const Ctx& c, MSmem& S, int row, PatchG& pg) {
+  const int tid = threadIdx.x;
+  const int Wm = (a.V + 31) >> 5;
+  pg.tag = a.gtag + (size_t)row * kGH;
+  pg.cnt = a.gcnt + (size_t)row * kGH;
+  pg.fin = a.gfin + (size_t)row * kGH;
+  // cleared first (its contents before the call are unspecified)
+  for (int sl = tid; sl < kGH / 2; sl += BS) reinterpret_cast<uint4*>(pg.tag)[sl] = make_uint4(0u, 0u, 0u, 0u);
+  pg.gen = 1u;
+  if (tid == 0) S.bc[9] = 0u;
+  __threadfence();
+  __syncthreads();
+  const int ne = c.nhist + c.nextra + c.nbias;
+  bool full = false;
+  for (int e = tid; e < ne; e += BS) {
+    const int id = lin_entry(c, e);
+    if (id >= 0 && id < a.V && gclaim(pg, id) < 0) full = true;
+  }
+  if (full) S.bc[9] = 1u;
+  __threadfence();
+  __syncthreads();
+  if (S.bc[9] != 0u) return 3;
+  for (int e = tid; e < ne; e += BS) {
+    const int id = lin_entry(c, e);
+    if (id < 0 || id >= a.V) continue;
+    const int sl = gfind(pg, id);
+    if (e < c.nhist + c.nextra) atomicAdd(&pg.cnt[sl], 1u);
+    else atomicOr(&pg.cnt[sl], 0x80000000u);
+  }
+  __threadfence();
+  __syncthreads();
+  for (int sl = tid; sl < kGH; sl += BS) {
+    const uint64_t t = pg.tag[sl];
+    if ((uint32_t)(t >> 32) != pg.gen) continue;
+    const int id = (int)((uint32_t)t - 1u);
+    const uint32_t hcv = pg.cnt[sl];
+    const bool hb = (hcv >> 31) != 0u;
+    float bsum = 0.0f;
+    if (hb) {
+      for (int e = 0; e < c.nbias; ++e)
+        if (c.bias_ids[e] == id) bsum = bsum + c.bias_vals[e];
+    }
+    const bool allowed = !c.mask || ((((id >> 5) < Wm ? c.mask[id >> 5] : 0u) >> (id & 31)) & 1u);
+    pg.fin[sl] = allowed ? fold_nan(penalised_key(load_elem_bits<DT>(c.xrow, id), c.mode, c.rep, c.freq,
+                                                  c.pres, (int)(hcv & 0x7FFFFFFFu), hb, bsum))
+                         : 0u;
+  }
+  __threadfence();
+  __syncthreads();
+  return 2;
+}
+
+// ---------------------------------------------------------------------------
+// Exact slow path: writes to pool elements that include the row's `want`
+// largest composites (raw copies of patched ids left out, patched finals
+// among them) and returns their number.  v0 = the want-th largest element
+// among the emitted ones bounds the k-th of the row from below, so only units
+// whose threshold lies above v0 (or that overflowed) can hide a top-k element:
+// they are re-read whole, and everything at or above v0 is collected (if that
+// is more than the pool holds, after a second selection).  want == 1 needs the
+// maximum only.  One visiting loop serves every pass: its operation is `op`.
+// ---------------------------------------------------------------------------
+template <int DT, int BS>
+__device__ __forceinline__ int slow_select(const KArgs& a, const Ctx& c, MSmem& S, uint64_t* pool, int pmode,
+                                           const PatchG& pg, uint32_t want) {
+  enum { V_COUNT, V_KEY, V_IDX, V_COLLECT, V_MAX };
+  constexpr int VW = DTT<DT>::VW, EPW = DT == SS_BF16 ? 1 : 2;  // words of a candidate
+  const int tid = threadIdx.x;
+  const int U = a.U;
+  const int W = (a.V + 31) >> 5;
+  int op = want == 1u ? V_MAX : V_COUNT;
+  bool second = false;            // the marked units are re-read
+  uint64_t thr = 0ull;            // composites at or above it are the wanted ones (so far)
+  uint32_t need = want, prefix = 0u, ip = 0u;
+  int sh = 24, ib = 10;
+  for (;;) {
+    for (int i = tid; i < 1024; i += BS) S.bins[i] = 0u;
+    if (tid == 0) S.bc[8] = 0u;
+    lds_barrier();
+    uint32_t acc = 0u;
+    uint64_t best = 0ull;
+    auto apply = [&](uint32_t k, uint32_t i) {
+      if (k < kKeyFloor || is_patched<DT>(c, S, pmode, pg, (int)i)) return;
+      const uint64_t cm = comp_of(k, i);
+      if (cm < thr) return;
+      if (op == V_COUNT) {
+        ++acc;
+      } else if (op == V_MAX) {
+        best = max(best, cm);
+      } else if (op == V_KEY) {
+        if (sh == 24 || (k >> (sh + 8)) == prefix) atomicAdd(&S.bins[(k >> sh) & 255u], 1u);
+      } else if (op == V_IDX) {
+        if (k == prefix && (ib == 10 || (i >> 10) == ip)) atomicAdd(&S.bins[(i >> ib) & 1023u], 1u);
+      } else {
+        const uint32_t p = atomicAdd(&S.bc[8], 1u);
+        if (p < (uint32_t)a.pcap) pool[p] = cm;
+      }
+    };
+    // 1. candidates of the units that are not marked
+    {
+      const int tpu = a.tpu;
+      const int u = (tid * a.tpu_inv) >> 20, sub = tid - u * tpu;
+      const bool act = u < U && !((S.rmask[u >> 5] >> (u & 31)) & 1u);
+      const size_t g = (size_t)c.row * U + (u < U ? u : 0);
+      const uint32_t cn = act ? a.rec[g].y : 0u;
+      const uint32_t* src = reinterpret_cast<const uint32_t*>(a.cand + g * a.cap);
+      for (uint32_t i = (uint32_t)sub; i < cn; i += (uint32_t)tpu) {
+        const uint32_t w = src[i * EPW];
+        if constexpr (DT == SS_BF16) apply(w & 0xFFFF0000u, (uint32_t)(u * kUE) + (w & 0xFFFFu));
+        else apply(w, (uint32_t)(u * kUE) + src[i * EPW + 1]);
+      }
+    }
+    // 2. every element of the marked units (grammar mask applied, NaN
+    // invalid): eight of them at a time, a share of the threads each
+    if (second) {
+      constexpr int SH = BS / 8;  // threads per unit
+      int nth = tid / SH;         // this share's unit: the nth marked one
+      int seen = 0;
+      for (int w = 0; w < (U + 31) >> 5; ++w) {
+        uint32_t mk = S.rmask[w];
+        while (mk) {
+          const int u = w * 32 + __builtin_ctz(mk);
+          mk &= mk - 1u;
+          if (seen++ != nth) continue;
+          nth += 8;
+          const int lo = u * kUE;
+#pragma unroll 1
+          for (int l0 = (tid & (SH - 1)) * VW; l0 < kUE; l0 += SH * VW) {
+            uint32_t w4[4] = {0u, 0u, 0u, 0u};
+            if (a.vec_ok && lo + kUE <= a.V) {
+              const uint4 r = *reinterpret_cast<const uint4*>(c.xrow + (size_t)(lo + l0) * DTT<DT>::ES);
+              w4[0] = r.x;
+              w4[1] = r.y;
+              w4[2] = r.z;
+              w4[3] = r.w;
+            } else {
+#pragma unroll
+              for (int e = 0; e < VW; ++e) {
+                if (lo + l0 + e < a.V) {
+                  const uint32_t bits = load_elem_bits<DT>(c.xrow, lo + l0 + e);
+                  if constexpr (DT == SS_F32) w4[e] = bits;
+                  else w4[e >> 1] |= (bits >> 16) << (16 * (e & 1));
+                }
+              }
+            }
+            uint32_t mw = 0xFFFFFFFFu;
+            if (c.mask) {
+              const int wi = (lo + l0) >> 5;
+              mw = wi < W ? (c.mask[wi] >> ((lo + l0) & 31)) : 0u;
+            }
+#pragma unroll 1
+            for (int e = 0; e < VW; ++e) {
+              const int i = lo + l0 + e;
+              if (i >= a.V) break;
+              uint32_t bits;
+              if constexpr (DT == SS_F32) {
+                bits = w4[0];
+                w4[0] = w4[1];
+                w4[1] = w4[2];
+                w4[2] = w4[3];
+              } else {
+                bits = w4[0] << 16;
+                w4[0] = (w4[0] >> 16) | (w4[1] << 16);
+                w4[1] = (w4[1] >> 16) | (w4[2] << 16);
+                w4[2] = (w4[2] >> 16) | (w4[3] << 16);
+                w4[3] >>= 16;
+              }
+              uint32_t k = fold_nan(key_raw(bits));
+              if (!((mw >> e) & 1u)) k = 0u;
+              apply(k, (uint32_t)i);
+            }
+          }
+        }
+      }
+    }
+    // 3. patched final values
+    auto final_value = [&](uint32_t k, uint32_t id) {
+      const uint64_t cm = comp_of(k, id);
+      if (k < kKeyFloor || cm < thr) return;
+      if (op == V_COUNT) {
+        ++acc;
+      } else if (op == V_MAX) {
+        best = max(best, cm);
+      } else if (op == V_KEY) {
+        if (sh == 24 || (k >> (sh + 8)) == prefix) atomicAdd(&S.bins[(k >> sh) & 255u], 1u);
+      } else if (op == V_IDX) {
+        if (k == prefix && (ib == 10 || (id >> 10) == ip)) atomicAdd(&S.bins[(id >> ib) & 1023u], 1u);
+      } else {
+        const uint32_t p = atomicAdd(&S.bc[8], 1u);
+        if (p < (uint32_t)a.pcap) pool[p] = cm;
+      }
+    };
+    const int nf = pmode == 1 ? kH : (pmode == 2 ? kGH : (pmode == 3 ? c.nhist + c.nextra + c.nbias : 0));
+#pragma unroll 1
+    for (int sl = tid; sl < nf; sl += BS) {
+      int id = -1;
+      uint32_t k = 0u;
+      if (pmode == 1) {
+        id = S.hk[sl];
+        k = S.hf[sl];
+      } else if (pmode == 2) {
+        const uint64_t t = pg.tag[sl];
+        if ((uint32_t)(t >> 32) == pg.gen) {
+          id = (int)((uint32_t)t - 1u);
+          k = pg.fin[sl];
+        }
+      } else {
+        id = lin_entry(c, sl);
+        for (int e2 = 0; e2 < sl && id >= 0; ++e2)
+          if (lin_entry(c, e2) == id) id = -1;  // listed before
+        if (id >= 0 && id < a.V) k = lin_final<DT>(a, c, id);
+        else id = -1;
+      }
+      if (id >= 0) final_value(k, (uint32_t)id);
+    }
+    lds_barrier();
+
+    // what the pass found
+    bool have_thr = false;
+    if (op == V_MAX) {
+      best = wg_max<BS>(best, S.x64[0]);
+      if (second) {
+        if (tid == 0) pool[0] = best;
+        lds_barrier();
+        return best != 0ull ? 1 : 0;
+      }
+      thr = best;
+      have_thr = true;
+    } else if (op == V_COUNT) {
+      acc = wg_sum<BS>(acc, S.x32[0]);
+      if (acc < want) {  // too few emitted: everything valid takes part
+        thr = comp_of(kKeyFloor, kNone);
+        have_thr = true;
+      } else {
+        op = V_KEY;
+      }
+    } else if (op == V_COLLECT) {
+      const uint32_t n = S.bc[8];
+      if (n <= (uint32_t)a.pcap) {
+        lds_barrier();
+        return (int)n;
+      }
+      need = min(want, n);
+      sh = 24;
+      prefix = 0u;
+      op = V_KEY;
+    } else {
+      // the digit holding the need-th element: keys descending, indices ascending
+      const bool key = op == V_KEY;
+      const int nb = key ? 256 : 1024;
+      constexpr int PER = 1024 / BS;
+      uint32_t h[PER], s = 0u;
+#pragma unroll
+      for (int q = 0; q < PER; ++q) {
+        const int r = tid * PER + q;
+        h[q] = r < nb ? S.bins[key ? nb - 1 - r : r] : 0u;
+        s += h[q];
+      }
+      const uint32_t inc = wave_incl_scan(s);
+      if (lane() == 63) S.x32[0][wave()] = inc;
+      lds_barrier();
+      uint32_t run = inc - s;
+      for (int w = 0; w < wave(); ++w) run += S.x32[0][w];
+#pragma unroll
+      for (int q = 0; q < PER; ++q) {
+        const int r = tid * PER + q;
+        if (run < need && run + h[q] >= need) {
+          S.bc[4] = (uint32_t)(key ? nb - 1 - r : r);
+          S.bc[5] = run;
+          S.bc[6] = h[q];
+        }
+        run += h[q];
+      }
+      lds_barrier();
+      const uint32_t d = S.bc[4], before = S.bc[5], hd = S.bc[6];
+      need -= before;
+      if (key) {
+        prefix = (prefix << 8) | d;
+        if (hd == need) {  // every key with this prefix is wanted
+          thr = comp_of(prefix << sh, kNone);
+          have_thr = true;
+        } else if (sh == 0) {
+          op = V_IDX;
+          ib = 10;
+        } else {
+          sh -= 8;
+        }
+      } else if (ib == 10 && hd != need) {
+        ip = d;
+        ib = 0;
+      } else {
+        const uint32_t last = ib == 10 ? (d << 10) | 1023u : (ip << 10) | d;
+        thr = comp_of(prefix, last);
+        have_thr = true;
+      }
+    }
+    if (have_thr) {
+      if (!second) {
+        // units whose threshold (ties cut by index) lies above the bound
+        for (int u = tid; u < U; u += BS) {
+          const uint4 r4 = a.rec[(size_t)c.row * U + u];
+          if (r4.x != kNoEmit && comp_of(r4.x, r4.w) > thr) atomicOr(&S.rmask[u >> 5], 1u << (u & 31));
+        }
+        second = true;
+      }
+      if (op != V_MAX) op = V_COLLECT;
+    }
+    lds_barrier();
+  }
+}
+
+// This thread's share of the full-row normaliser sum_j exp((y_j - M) / tau)
+// over the row's valid processed logits: the units' sums (taken by the
+// streaming kernel relative to each unit's raw maximum) rescaled to M, each
+// patched id's raw term (recomputed bit for bit) replaced by its final
+// value's; rows whose lists exceed the LDS table recompute every element.
+// The caller sums the shares over the workgroup.
+template <int DT, int BS>
+__device__ __forceinline__ double row_norm_part(const KArgs& a, const Ctx& c, const MSmem& S, int row, int pmode,
+                                                const PatchG& pg, double M, float tauf) {
+  const int U = a.U, tid = threadIdx.x;
+  const float itau = 1.0f / tauf;
+  const double tau = (double)tauf;
+  const int Wm = (a.V + 31) >> 5;
+  auto allowed = [&](int id) { return !c.mask || ((((id >> 5) < Wm ? c.mask[id >> 5] : 0u) >> (id & 31)) & 1u); };
+  double z = 0.0;
+  if (pmode <= 1) {
+    for (int u = tid; u < U; u += BS) {
+      const uint32_t wmu = a.rec[(size_t)row * U + u].z;
+      if (wmu >= kKeyFloor) z += exp(((double)float_of_key(wmu) - M) / tau) * a.usum[(size_t)row * U + u];
+    }
+    for (int sl = tid; pmode == 1 && sl < kH; sl += BS) {
+      const int id = S.hk[sl];
+      if (id < 0) continue;
+      uint32_t kr = fold_nan(key_raw(load_elem_bits<DT>(c.xrow, id)));  // as the unit sum counted it
+      if (!allowed(id)) kr = 0u;
+      if (kr >= kKeyFloor) {
+        const float mu = float_of_key(a.rec[(size_t)row * U + id / kUE].z);
+        z -= exp(((double)mu - M) / tau) * (double)lp_term(float_of_key(kr), mu, itau);
+      }
+      if (S.hf[sl] >= kKeyFloor) z += exp(((double)float_of_key(S.hf[sl]) - M) / tau);
+    }
+  } else {  // lists beyond the LDS table: every element's processed value
+    for (int i = tid; i < a.V; i += BS) {
+      uint32_t k = fold_nan(key_raw(load_elem_bits<DT>(c.xrow, i)));
+      if (!allowed(i)) k = 0u;
+      if (is_patched<DT>(c, S, pmode, pg, i)) k = pmode == 2 ? pg.fin[gfind(pg, i)] : lin_final<DT>(a, c, i);
+      if (k >= kKeyFloor) z += exp(((double)float_of_key(k) - M) / tau);
+    }
+  }
+  return z;
+}
+
+
+// Merge of one row by the whole workgroup.
+template <int DT, int OP>
+__device__ __forceinline__ void merge_row(const KArgs& a, int row, MSmem& S, uint64_t* stage) {
+  constexpr int BS = merge_threads<DT, OP>();
+  constexpr int NW = BS / 64;
+  constexpr int EPQ = DT == SS_BF16 ? 4 : 2;   // candidates per 16-byte load
+  constexpr int NQM = DT == SS_BF16 ? 3 : 6;   // candidate loads a thread holds at most
+  constexpr int EM = SS_MAX_K / BS;            // list entries per thread at most
+  const int tid = threadIdx.x;
+  const int ln = lane(), wv = wave();
+  const int U = a.U;
+  int b = row, ell = 0;
+  if constexpr (OP == OP_VERIFY) {
+    b = row / (a.L + 1);
+    ell = row - b * (a.L + 1);
+  }
+
+  // 1. every load of the row, none depending on another
+  const int tpu = a.tpu;
+  int u = (tid * a.tpu_inv) >> 20;
+  const int sub = tid - u * tpu;
+  const bool act = u < U;
+  if (!act) u = 0;
+  const size_t gu = (size_t)row * U + u;
+  const uint4* region = a.cand + gu * (size_t)a.cap;
+  const uint4 r4 = a.rec[gu];
+  uint4 cq[NQM];
+  auto load_batch = [&](int batch) {
+#pragma unroll
+    for (int j = 0; j < NQM; ++j)
+      if (j < a.nq) cq[j] = region[min((batch * a.nq + j) * tpu + sub, a.cap - 1)];
+  };
+  load_batch(0);
+  const bool tables = OP != OP_TOPK && a.patch_wgs > 0;
+  constexpr int KT = (kH / 4 + BS - 1) / BS;  // 16-byte words per thread and table half
+  uint4 tid4[KT], tfin4[KT];
+  int pst = 0;
+  if (tables) {
+    const uint4* tsrc = reinterpret_cast<const uint4*>(a.ptab + (size_t)row * 2 * kH);
+#pragma unroll
+    for (int m = 0; m < KT; ++m) {
+      const int w = min(tid + m * BS, kH / 4 - 1);
+      tid4[m] = tsrc[w];
+      tfin4[m] = tsrc[kH / 4 + w];
+    }
+    pst = a.pstat[row];
+  }
+  uint32_t mode = SS_TOPK;
+  float temp = 1.0f, topp_v = 1.0f, minp_v = 0.0f;
+  int kreq_v = 0, dtok = -1;
+  uint64_t seed = 0ull;
+  int64_t pos = ell;
+  if constexpr (OP == OP_TOPK) {
+    kreq_v = a.top_k ? a.top_k[b] : a.k_cap;
+  } else {
+    mode = a.mode[b] & a.feat;
+    if (a.feat & SS_TEMP) temp = a.temperature[b];
+    if (a.feat & SS_TOPK) kreq_v = a.top_k[b];
+    if (a.feat & SS_TOPP) topp_v = a.top_p[b];
+    if (a.feat & SS_MINP) minp_v = a.min_p[b];
+    if (a.seed) seed = a.seed[b];
+    if (a.position) pos += a.position[b];
+    if constexpr (OP == OP_VERIFY) {
+      if (ell < a.L) dtok = a.draft_tokens[(size_t)b * a.L + ell];
+    }
+  }
+  // the tables in LDS are cleared while the loads are in flight
+  for (int i = tid; i < kNB / 4; i += BS) reinterpret_cast<uint4*>(S.bins)[i] = make_uint4(0u, 0u, 0u, 0u);
+  const bool pexact = a.V <= kPB;
+  if (tables) {
+    const int pwords = pexact ? (a.V + 31) >> 5 : kPB / 32;
+    for (int s = tid; s < (pwords + 3) >> 2; s += BS) reinterpret_cast<uint4*>(S.pbits)[s] = make_uint4(0u, 0u, 0u, 0u);
+  }
+  if (tid < kMaxU / 32) S.rmask[tid] = 0u;
+  if (tid == 0) {
+    S.bc[0] = 0u;     // entries of the bins that hold the list
+    S.bc[1] = 0u;     // largest of those bins
+    S.bc[2] = kNone;  // top-p: last rank kept
+    S.bc[3] = kNone;  // min-p: first rank dropped
+    S.bc[7] = kNone;  // top-p against the whole row: last rank kept
+    S.bc64[3] = 0ull;
+  }
+  lds_barrier();
+
+  // 2. largest threshold, row maximum, longest candidate list; the patch table
+  const uint32_t cnt = (act && r4.y != kOvf) ? r4.y : 0u;
+  if (act && r4.y == kOvf) atomicOr(&S.rmask[u >> 5], 1u << (u & 31));
+  uint32_t hfmax = 0u;
+  if (pst == 1) {
+#pragma unroll
+    for (int m = 0; m < KT; ++m) {
+      if (tid + m * BS >= kH / 4) {
+        tid4[m] = make_uint4(kNone, kNone, kNone, kNone);
+        continue;
+      }
+      reinterpret_cast<uint4*>(S.hk)[tid + m * BS] = tid4[m];
+      reinterpret_cast<uint4*>(S.hf)[tid + m * BS] = tfin4[m];
+      const int ids[4] = {(int)tid4[m].x, (int)tid4[m].y, (int)tid4[m].z, (int)tid4[m].w};
+      const uint32_t fk[4] = {tfin4[m].x, tfin4[m].y, tfin4[m].z, tfin4[m].w};
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        if (ids[q] < 0) continue;
+        const uint32_t hb = pbit(ids[q], pexact);
+        atomicOr(&S.pbits[hb >> 5], 1u << (hb & 31));
+        hfmax = max(hfmax, fk[q]);
+      }
+    }
+  }
+  uint64_t tc = (act && r4.x != kNoEmit) ? comp_of(r4.x, r4.w) : 0ull;
+  uint32_t hi = act ? r4.z : 0u;
+  uint32_t cmax = act ? r4.y : 0u;  // kOvf when a unit overflowed
+  tc = wave_max(tc);
+  hi = wave_max_u32(hi);
+  hfmax = wave_max_u32(hfmax);
+  cmax = wave_max_u32(cmax);
+  if (ln == 0) {
+    S.x64[0][wv] = tc;
+    S.x32[0][wv] = hi;
+    S.x32[1][wv] = hfmax;
+    S.x32[2][wv] = cmax;
+  }
+  lds_barrier();
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    tc = max(tc, S.x64[0][w]);
+    hi = max(hi, S.x32[0][w]);
+    hfmax = max(hfmax, S.x32[1][w]);
+    cmax = max(cmax, S.x32[2][w]);
+  }
+  const uint32_t tck = comp_key(tc), tcut = comp_idx(tc);
+
+  // the request
+  bool greedy = false, kcap = false, full_row = false;
+  int want;
+  if constexpr (OP == OP_TOPK) {
+    want = kreq_v < 0 ? 0 : min(kreq_v, a.k_cap);
+  } else if constexpr (OP == OP_LOGPROBS) {
+    want = (mode & SS_LOGPROBS) ? a.k_cap : 0;
+  } else {
+    const float tm = (mode & SS_TEMP) ? temp : 1.0f;
+    greedy = (mode & SS_GREEDY) || ((mode & SS_TEMP) && tm <= 0.0f);
+    const bool cutk = (mode & SS_TOPK) && kreq_v >= 1;
+    const int kreq = cutk ? kreq_v : INT_MAX;
+    kcap = !greedy && kreq > a.k_cap;
+    full_row = a.full && !greedy && !cutk;
+    want = greedy ? 1 : min(kreq, a.k_cap);
+  }
+  int flags = kcap ? SS_FLAG_KCAP : 0;
+  const bool empty = hi < kKeyFloor;
+  bool slow = cmax == kOvf || pst == 2;
+
+  // 3. the elements that take part
+  const int covered = a.nq * tpu * EPQ;  // candidates per unit in one batch
+  const int nbatch = (!empty && want > 0 && !slow) ? max(1, (int)((cmax + (uint32_t)covered - 1u) / (uint32_t)covered)) : 0;
+  auto elem = [&](int j, int e, uint32_t& key, uint32_t& idx) {
+    const uint32_t w = e == 0 ? cq[j].x : (e == 1 ? cq[j].y : (e == 2 ? cq[j].z : cq[j].w));
+    if constexpr (DT == SS_BF16) {
+      key = w & 0xFFFF0000u;
+      idx = (uint32_t)(u * kUE) + (w & 0xFFFFu);
+    } else {
+      key = e == 0 ? cq[j].x : cq[j].z;
+      idx = (uint32_t)(u * kUE) + (e == 0 ? cq[j].y : cq[j].w);
+    }
+  };
+  auto select = [&](int batch) -> uint32_t {
+    uint32_t sel = 0u;
+#pragma unroll
+    for (int j = 0; j < NQM; ++j) {
+      if (j < a.nq) {
+        const uint32_t n0 = (uint32_t)(((batch * a.nq + j) * tpu + sub) * EPQ);
+#pragma unroll
+        for (int e = 0; e < EPQ; ++e) {
+          uint32_t key, idx;
+          elem(j, e, key, idx);
+          const bool at = key > tck || (key == tck && idx <= tcut);  // composite >= tc
+          if (n0 + (uint32_t)e < cnt && at) sel |= 1u << (j * EPQ + e);
+        }
+      }
+    }
+    if (pst == 1 && sel != 0u) {  // raw copies of patched ids
+#pragma unroll
+      for (int j = 0; j < NQM; ++j) {
+        if (j < a.nq) {
+#pragma unroll
+          for (int e = 0; e < EPQ; ++e) {
+            if ((sel >> (j * EPQ + e)) & 1u) {
+              uint32_t key, idx;
+              elem(j, e, key, idx);
+              if (lds_patched(S, (int)idx, pexact)) sel &= ~(1u << (j * EPQ + e));
+            }
+          }
+        }
+      }
+    }
+    return sel;
+  };
+  uint32_t sel = 0u;
+  uint32_t fsel = 0u;  // patched finals at or above tc
+  if (nbatch > 0 && pst == 1) {
+#pragma unroll
+    for (int m = 0; m < KT; ++m) {
+      const int ids[4] = {(int)tid4[m].x, (int)tid4[m].y, (int)tid4[m].z, (int)tid4[m].w};
+      const uint32_t fk[4] = {tfin4[m].x, tfin4[m].y, tfin4[m].z, tfin4[m].w};
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (ids[q] >= 0 && fk[q] >= kKeyFloor && comp_of(fk[q], (uint32_t)ids[q]) >= tc) fsel |= 1u << (4 * m + q);
+    }
+  }
+  // calls f(key, index) for each of this thread's elements
+  auto each = [&](bool again, auto&& f) {
+    for (int batch = 0; batch < nbatch; ++batch) {
+      if (batch > 0 || (again && nbatch > 1)) load_batch(batch);
+      if (!(again && nbatch == 1)) sel = select(batch);
+      if (sel != 0u) {
+#pragma unroll
+        for (int j = 0; j < NQM; ++j) {
+#pragma unroll
+          for (int e = 0; e < EPQ; ++e) {
+            if ((sel >> (j * EPQ + e)) & 1u) {
+              uint32_t key, idx;
+              elem(j, e, key, idx);
+              f(key, idx);
+            }
+          }
+        }
+      }
+    }
+    if (fsel != 0u) {
+#pragma unroll
+      for (int m = 0; m < KT; ++m) {
+        const uint32_t ids[4] = {tid4[m].x, tid4[m].y, tid4[m].z, tid4[m].w};
+        const uint32_t fk[4] = {tfin4[m].x, tfin4[m].y, tfin4[m].z, tfin4[m].w};
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if ((fsel >> (4 * m + q)) & 1u) f(fk[q], ids[q]);
+      }
+    }
+  };
+
+  uint64_t* sorted = stage + a.pcap;
+  const uint64_t* T = sorted;  // the row's list in canonical order
+  int nT = 0;
+  bool crowded = false;  // the list (or a superset) is in stage, unsorted
+  uint32_t nB = 0u;      // entries of stage
+  if (nbatch > 0) {
+    if (want == 1) {
+      uint64_t mc = 0ull;
+      each(false, [&](uint32_t key, uint32_t idx) { mc = max(mc, comp_of(key, idx)); });
+      mc = wave_max(mc);
+      if (ln == 0) S.x64[1][wv] = mc;
+      lds_barrier();
+#pragma unroll
+      for (int w = 0; w < NW; ++w) mc = max(mc, S.x64[1][w]);
+      slow = mc == 0ull;
+      nT = slow ? 0 : 1;
+      if (tid == 0) sorted[0] = mc;
+      lds_barrier();
+    } else {
+      // bins of 2^sh keys below the largest possible key, in descending order
+      const uint32_t kmax = max(hi, hfmax);
+      const int sh = max(0, 32 - __clz(kmax - tck) - kNBLog);
+      auto bin_of = [&](uint32_t key) { return (kmax - key) >> sh; };
+      each(false, [&](uint32_t key, uint32_t) { atomicAdd(&S.bins[bin_of(key)], 1u); });
+      lds_barrier();
+      constexpr int BPT = kNB / BS;  // bins per thread
+      uint32_t h[BPT], s = 0u;
+#pragma unroll
+      for (int q = 0; q < BPT; ++q) {
+        h[q] = S.bins[tid * BPT + q];
+        s += h[q];
+      }
+      const uint32_t inc = wave_incl_scan(s);
+      if (ln == 63) S.x32[3][wv] = inc;
+      lds_barrier();
+      uint32_t run = inc - s, total = 0u;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        const uint32_t x = S.x32[3][w];
+        if (w < wv) run += x;
+        total += x;
+      }
+      if (total < (uint32_t)want) {
+        // at the lowest threshold there is the list is the whole row (few
+        // tokens allowed by a grammar); otherwise elements may be missing
+        if (tc == comp_of(kKeyFloor, kNone)) want = (int)total;
+        else slow = true;
+      }
+      uint32_t occ = 0u;
+#pragma unroll
+      for (int q = 0; q < BPT; ++q) {
+        S.bins[tid * BPT + q] = run;
+        if (run < (uint32_t)want) {
+          occ = max(occ, h[q]);
+          if (run + h[q] >= (uint32_t)want) S.bc[0] = run + h[q];
+        }
+        run += h[q];
+      }
+      occ = wave_max_u32(occ);
+      if (ln == 0 && occ != 0u) atomicMax(&S.bc[1], occ);
+      lds_barrier();
+      nB = S.bc[0];
+      if (!slow && nB > (uint32_t)a.pcap) slow = true;  // ties beyond the staging area
+      if (!slow) {
+        crowded = S.bc[1] > (uint32_t)kCrowd;
+        // scatter into bin order: each bin's start becomes its end
+        each(true, [&](uint32_t key, uint32_t idx) {
+          const uint32_t bn = bin_of(key);
+          if (S.bins[bn] < nB) {
+            const uint32_t p = atomicAdd(&S.bins[bn], 1u);
+            if (p < nB) stage[p] = comp_of(key, idx);
+          }
+        });
+        lds_barrier();
+        nT = want;
+        if (!crowded) {
+          for (uint32_t p = (uint32_t)tid; p < nB; p += (uint32_t)BS) {
+            const uint64_t e = stage[p];
+            const uint32_t bn = bin_of(comp_key(e));
+            const uint32_t bs = bn != 0u ? S.bins[bn - 1u] : 0u, be = S.bins[bn];
+            uint32_t r = bs;
+            for (uint32_t j = bs; j < be; j += 4u) {
+              const uint64_t s0 = stage[j], s1 = stage[j + 1u], s2 = stage[j + 2u], s3 = stage[j + 3u];
+              r += (s0 > e ? 1u : 0u) + ((j + 1u < be && s1 > e) ? 1u : 0u) + ((j + 2u < be && s2 > e) ? 1u : 0u) +
+                   ((j + 3u < be && s3 > e) ? 1u : 0u);
+            }
+            if (r < (uint32_t)want) sorted[r] = e;
+          }
+          lds_barrier();
+        }
+      }
+    }
+  }
+
+  // 4. the exact slow path, and lists beyond the patch table
+  int pmode = pst == 1 ? 1 : 0;
+  PatchG pg = {};
+  Ctx c = {};
+  auto norm_ctx = [&] {  // what row_norm_part reads beside the patch table
+    c.xrow = reinterpret_cast<const unsigned char*>(a.x) + (size_t)row * (size_t)a.ld * DTT<DT>::ES;
+    c.mask = (mode & SS_GRAMMAR) ? a.bitmask + (size_t)row * (size_t)a.mask_ld : nullptr;
+  };
+  if (!empty && want > 0 && slow) {
+    flags |= SS_FLAG_FALLBACK;
+    c = make_ctx<DT>(a, row);
+    if (pst == 2) pmode = global_table<DT, BS>(a, c, S, row, pg);
+    nB = (uint32_t)slow_select<DT, BS>(a, c, S, stage, pmode, pg, (uint32_t)want);
+    nT = min(want, (int)nB);
+    crowded = true;
+  }
+  if (crowded) {
+    T = stage;
+    if (nB > 1u) {
+      const int N = next_pow2((int)nB);
+      for (int i = tid + (int)nB; i < N; i += BS) stage[i] = 0ull;
+      lds_barrier();
+      lds_sort_desc<BS>(stage, N);
+    }
+  }
+  const bool none = empty || nT == 0;
+  if (none) flags = empty ? SS_FLAG_EMPTY : flags | SS_FLAG_EMPTY;
+  const uint64_t Mcomp = none ? 0ull : T[0];
+  const int argmax = none ? -1 : (int)comp_idx(Mcomp);
+
+  // 5. outputs
+  if constexpr (OP == OP_TOPK) {
+    for (int r = tid; r < a.k_cap; r += BS) {
+      const size_t o = (size_t)b * a.k_cap + r;
+      const uint64_t cm = r < nT ? T[r] : 0ull;
+      a.out_val[o] = r < nT ? float_of_key(comp_key(cm)) : -__builtin_inff();
+      a.out_idx[o] = r < nT ? (int32_t)comp_idx(cm) : -1;
+    }
+    if (a.flags && tid == 0) a.flags[b] = flags & SS_FLAG_FALLBACK;
+    return;
+  } else if constexpr (OP == OP_LOGPROBS) {
+    const float tauf = lp_tau(a, mode, b);
+    const double tau = (double)tauf;
+    const double M = none ? 0.0 : (double)float_of_key(comp_key(Mcomp));
+    double lz = 0.0;
+    if (!none) {
+      if (!slow) norm_ctx();
+      lz = log(wg_sum<BS>(row_norm_part<DT, BS>(a, c, S, row, pmode, pg, M, tauf), S.rd));
+    }
+    for (int r = tid; r < a.k_cap; r += BS) {
+      const size_t o = (size_t)b * a.k_cap + r;
+      const uint64_t cm = r < nT ? T[r] : 0ull;
+      a.out_idx[o] = r < nT ? (int32_t)comp_idx(cm) : -1;
+      a.out_val[o] = r < nT ? (float)(((double)float_of_key(comp_key(cm)) - M) / tau - lz) : -__builtin_inff();
+    }
+    if (a.flags && tid == 0) a.flags[b] = (mode & SS_LOGPROBS) ? flags & (SS_FLAG_FALLBACK | SS_FLAG_EMPTY) : 0;
+    return;
+  } else {
+    if constexpr (OP == OP_PROCESS) {  // patched ids for the materialising pass
+      if (empty || pmode <= 1) {
+        if (tid == 0) a.npatched[row] = (pst == 1 && !empty) ? kTable : 0u;
+      } else if (pmode == 3) {
+        if (tid == 0) a.npatched[row] = kLinear;
+      } else {
+        if (tid == 0) S.bc[8] = 0u;
+        lds_barrier();
+        for (int s = tid; s < kGH; s += BS) {
+          const uint64_t t = pg.tag[s];
+          if ((uint32_t)(t >> 32) == pg.gen)
+            a.patched[(size_t)row * kGH + atomicAdd(&S.bc[8], 1u)] = make_uint2((uint32_t)t - 1u, pg.fin[s]);
+        }
+        lds_barrier();
+        if (tid == 0) a.npatched[row] = S.bc[8];
+      }
+    }
+    const bool has_draft = OP == OP_VERIFY && ell < a.L && dtok >= 0 && dtok < a.V;
+    if (none || greedy) {
+      if constexpr (OP == OP_PROCESS) {
+        if (tid == 0) {
+          RowSummary s;
+          s.thr = Mcomp;
+          s.Z = 1.0;
+          s.M = none ? 0.0f : float_of_key(comp_key(Mcomp));
+          s.tau = 1.0f;
+          s.argmax = argmax;
+          s.kind = none ? KIND_EMPTY : KIND_GREEDY;
+          a.summ[row] = s;
+          if (a.flags) a.flags[b] = flags;
+        }
+      } else if constexpr (sampling_op(OP)) {
+        if (tid == 0) {
+          a.out_token[b] = argmax;
+          if (a.out_logprob) a.out_logprob[b] = 0.0f;
+          if (a.flags) a.flags[b] = flags;
+        }
+        if (a.out_idx) {
+          for (int r = tid; r < a.k_out; r += BS) {
+            a.out_idx[(size_t)b * a.k_out + r] = r == 0 ? argmax : -1;
+            a.out_prob[(size_t)b * a.k_out + r] = (r == 0 && !none) ? 1.0f : 0.0f;
+          }
+        }
+      } else {
+        if (tid == 0) {
+          RowResult rr;
+          rr.accept = has_draft && !none && dtok == argmax;
+          rr.emit = argmax;
+          rr.flags = flags;
+          rr.pad = 0;
+          a.res[row] = rr;
+        }
+      }
+      return;
+    }
+
+    // ---- truncation and selection (Alg. 11 order) on T[0, nT): entry r =
+    // 64 (E wave + j) + lane is held by one thread, E entries per thread
+    const double M = (double)float_of_key(comp_key(Mcomp));
+    const float tauf = (mode & SS_TEMP) ? temp : 1.0f;
+    const double tau = (double)tauf;
+    const double itau = 1.0 / tau;
+    const float minp_f = (mode & SS_MINP) ? minp_v : 0.0f;
+    const float topp_f = (mode & SS_TOPP) ? topp_v : 1.0f;
+    const bool minp = minp_f > 0.0f;
+    const bool topp = topp_f < 1.0f;
+    const double lt = minp ? log((double)minp_f) : 0.0;
+    const int E = (nT + BS - 1) / BS;
+    const int r0 = 64 * E * wv + ln;
+    auto yval = [&](uint64_t cm) { return (double)float_of_key(comp_key(cm)); };
+    auto weight = [&](uint64_t cm) { return weight_fast(yval(cm), M, itau); };
+    auto dropped = [&](uint64_t cm) {  // by min-p; never the first
+      const double y = yval(cm);
+      const double l = (y == M) ? 0.0 : (y - M) / tau;
+      return cm != Mcomp && !(l >= lt);
+    };
+    // exclusive prefix sums of wt over the list; returns the total
+    uint64_t wt[EM], ex[EM];
+    auto scan_list = [&](uint64_t* scratch) -> uint64_t {
+      uint64_t run = 0ull;
+#pragma unroll
+      for (int j = 0; j < EM; ++j) {
+        if (j < E) {
+          const uint64_t inc = wave_incl_scan(wt[j]);
+          ex[j] = run + inc - wt[j];
+          run += readlane_T(inc, 63);
+        }
+      }
+      if (ln == 0) scratch[wv] = run;
+      lds_barrier();
+      uint64_t before = 0ull, total = 0ull;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        const uint64_t x = scratch[w];
+        if (w < wv) before += x;
+        total += x;
+      }
+#pragma unroll
+      for (int j = 0; j < EM; ++j)
+        if (j < E) ex[j] += before;
+      return total;
+    };
+#pragma unroll
+    for (int j = 0; j < EM; ++j) {
+      if (j < E) {
+        const int r = r0 + 64 * j;
+        wt[j] = r < nT ? (uint64_t)__double2ll_rn(weight(T[r]) * kFix) : 0ull;
+      }
+    }
+    const uint64_t Zk = scan_list(S.x64[1]);
+    // Full-row truncation takes its boundary against the whole row's mass;
+    // its result stands when fewer than k_max tokens are kept, else the bounded
+    // one (mass of the list) is taken with KCAP.
+    double zrow = 0.0;
+    if (OP == OP_SAMPLE_X && full_row) {
+      if (!slow) norm_ctx();
+      zrow = kFix * wg_sum<BS>(row_norm_part<DT, BS>(a, c, S, row, pmode, pg, M, lp_tau(a, mode, b)), S.rd);
+    }
+    const double Xp = (double)topp_f * (double)Zk, Xr = (double)topp_f * zrow;
+#pragma unroll
+    for (int j = 0; j < EM; ++j) {
+      if (j < E) {
+        const int r = r0 + 64 * j;
+        if (r < nT) {
+          const double in = (double)(ex[j] + wt[j]), be = (double)ex[j];
+          // the first entry whose inclusive mass reaches the boundary is kept, the next are not
+          if (topp && in >= Xp && (r == 0 || be < Xp)) {
+            S.bc[2] = (uint32_t)r;
+            S.bc64[0] = ex[j] + wt[j];
+          }
+          if (OP == OP_SAMPLE_X && full_row && topp && in >= Xr && (r == 0 || be < Xr)) {
+            S.bc[7] = (uint32_t)r;
+            S.bc64[2] = ex[j] + wt[j];
+          }
+          if (minp && r > 0 && dropped(T[r]) && !dropped(T[r - 1])) {
+            S.bc[3] = (uint32_t)r;
+            S.bc64[1] = ex[j];
+          }
+        }
+      }
+    }
+    lds_barrier();
+    const uint32_t np = S.bc[2], nm = S.bc[3];
+    const uint64_t zp = S.bc64[0], zm = S.bc64[1];
+    uint32_t n_s = (uint32_t)nT;
+    uint64_t Zs = Zk;
+    auto cut_at = [&](uint32_t last, uint64_t z) {  // the shorter of the top-p and min-p prefixes
+      n_s = (uint32_t)nT;
+      Zs = Zk;
+      if (last != kNone) {
+        n_s = last + 1u;
+        Zs = z;
+      }
+      if (nm < n_s) {
+        n_s = nm;
+        Zs = zm;
+      }
+    };
+    cut_at(np, zp);
+    if (OP == OP_SAMPLE_X && full_row) {
+      cut_at(S.bc[7], S.bc64[2]);
+      if (n_s < (uint32_t)a.k_cap) {
+        flags &= ~SS_FLAG_KCAP;
+      } else {
+        flags |= SS_FLAG_KCAP;
+        cut_at(np, zp);
+      }
+    }
+    const double Zsd = (double)Zs / kFix;
+    const double u0 = OP == OP_PROCESS ? 0.0 : uniform01(seed, (uint32_t)b, pos, 0);
+    // calls f(composite) in the thread that holds the drawn entry: the first
+    // kept one whose inclusive mass exceeds u0 * total (else the last one)
+    auto draw = [&](double total, auto&& f) {
+      const double X = u0 * total;
+#pragma unroll
+      for (int j = 0; j < EM; ++j) {
+        if (j < E) {
+          const int r = r0 + 64 * j;
+          if (r < (int)n_s && ((double)(ex[j] + wt[j]) > X || r == (int)n_s - 1) && (r == 0 || (double)ex[j] <= X))
+            f(T[r]);
+        }
+      }
+    };
+    if constexpr (OP == OP_PROCESS) {
+      if (tid == 0) {
+        RowSummary s;
+        s.thr = T[n_s - 1u];
+        s.Z = Zsd;
+        s.M = (float)M;
+        s.tau = (float)tau;
+        s.argmax = argmax;
+        s.kind = KIND_DIST;
+        a.summ[row] = s;
+        if (a.flags) a.flags[b] = flags;
+      }
+    } else if constexpr (sampling_op(OP)) {
+      if (a.out_idx && (int)n_s > a.k_out) flags |= SS_FLAG_OUT_TRUNC;
+      auto emit = [&](uint64_t cm) {
+        a.out_token[b] = (int32_t)comp_idx(cm);
+        if (a.out_logprob) a.out_logprob[b] = (float)log(weight(cm) / Zsd);
+        if (a.flags) a.flags[b] = flags;
+      };
+      if (OP == OP_SAMPLE_X && a.gum) {
+        // Gumbel-max over the kept set (Appendix C.3): the largest
+        // (y - M)/tau - g[id] in double, the lower id on equal scores
+        const float* grow = a.gum + (size_t)b * (size_t)a.ld_g;
+        double bs = -__builtin_inf();
+        uint64_t bk = 0ull;  // (~id << 32) | key of this thread's best
+#pragma unroll
+        for (int j = 0; j < EM; ++j) {
+          if (j < E) {
+            const int r = r0 + 64 * j;
+            if (r < (int)n_s) {
+              const uint64_t cm = T[r];
+              const double y = yval(cm);
+              const double sc = (y == M ? 0.0 : (y - M) / tau) - (double)grow[comp_idx(cm)];
+              const uint64_t k2 = ((uint64_t)(~comp_idx(cm)) << 32) | comp_key(cm);
+              if (sc > bs || (sc == bs && k2 > bk)) {
+                bs = sc;
+                bk = k2;
+              }
+            }
+          }
+        }
+        const double top = wg_max<BS>(bs, S.rd);
+        const uint64_t win = wg_max<BS>(bs == top ? bk : (uint64_t)0, S.x64[2]);
+        if (tid == 0) emit(comp_of((uint32_t)win, ~(uint32_t)(win >> 32)));
+      } else {
+        draw((double)Zs, emit);
+      }
+      if (a.out_idx) {
+        for (int r = tid; r < a.k_out; r += BS) {
+          const bool in = r < (int)n_s;
+          const uint64_t cm = in ? T[r] : 0ull;
+          a.out_idx[(size_t)b * a.k_out + r] = in ? (int32_t)comp_idx(cm) : -1;
+          a.out_prob[(size_t)b * a.k_out + r] = in ? (float)(weight(cm) / Zsd) : 0.0f;
+        }
+      }
+    } else {
+      // verification: this row's decision; the assembly combines a request's rows
+      auto publish = [&](int accept, int token) {
+        RowResult rr;
+        rr.accept = accept;
+        rr.emit = token;
+        rr.flags = flags;
+        rr.pad = 0;
+        a.res[row] = rr;
+      };
+      if (!has_draft) {
+        draw((double)Zs, [&](uint64_t cm) { publish(0, (int)comp_idx(cm)); });
+        return;
+      }
+      // P(d): zero (bc64[3]) unless the draft token is kept
+#pragma unroll
+      for (int j = 0; j < EM; ++j) {
+        if (j < E) {
+          const int r = r0 + 64 * j;
+          if (r < (int)n_s && (int)comp_idx(T[r]) == dtok) S.bc64[3] = __builtin_bit_cast(uint64_t, weight(T[r]) / Zsd);
+        }
+      }
+      const float* qrow = a.draft_probs ? a.draft_probs + ((size_t)b * a.L + ell) * (size_t)a.ld_q : nullptr;
+      // sparse q: the entries naming an id summed, an unlisted id at 0
+      const bool sparse = a.kq > 0;
+      const size_t qo = ((size_t)b * a.L + ell) * (size_t)a.kq;
+      uint64_t* ql = qlist_view(S);
+      int NQ = 0;
+      double qd;
+      if (sparse) {
+        // the list into LDS as (id << 32 | q bits), ids outside [0, V)
+        // as 0xFFFFFFFF, padded to a power of two when it will be sorted
+        NQ = a.kq <= kQScan ? a.kq : next_pow2(a.kq);
+        double qs = 0.0;
+        for (int i = tid; i < NQ; i += BS) {
+          uint64_t e = ~0ull;
+          if (i < a.kq) {
+            const int id = a.dq_idx[qo + i];
+            const float v = a.dq_val[qo + i];
+            if (id == dtok) qs += (double)v;
+            if (id >= 0 && id < a.V) e = ((uint64_t)(uint32_t)id << 32) | __float_as_uint(v);
+          }
+          ql[i] = e;
+        }
+        qd = wg_sum<BS>(qs, S.rd);  // its barriers publish the list and P(d)
+      } else {
+        qd = (double)qrow[dtok];
+        lds_barrier();
+      }
+      const double Pd = __builtin_bit_cast(double, S.bc64[3]);
+      const double u1 = uniform01(seed, (uint32_t)b, pos, 1);
+      if (Pd > 0.0 && u1 * qd <= Pd) {
+        if (tid == 0) publish(1, -1);
+        return;
+      }
+      // a long list is sorted (ids descending, padding first) for binary
+      // search; a short one is scanned in list order, every lane reading
+      // the same entry
+      const bool qsorted = sparse && a.kq > kQScan;
+      if (qsorted) lds_sort_desc<BS>(ql, NQ);
+      auto q_of = [&](uint32_t id) -> double {
+        if (!sparse) return (double)qrow[id];
+        double s = 0.0;
+        if (!qsorted) {
+#pragma unroll 8
+          for (int j = 0; j < NQ; ++j) {
+            const uint64_t e = ql[j];
+            if ((uint32_t)(e >> 32) == id) s += (double)__uint_as_float((uint32_t)e);
+          }
+          return s;
+        }
+        int lo = 0, hi2 = NQ;  // first entry whose id is at most `id`
+        while (lo < hi2) {
+          const int mid = (lo + hi2) >> 1;
+          if ((uint32_t)(ql[mid] >> 32) > id) lo = mid + 1;
+          else hi2 = mid;
+        }
+        for (; lo < NQ && (uint32_t)(ql[lo] >> 32) == id; ++lo) s += (double)__uint_as_float((uint32_t)ql[lo]);
+        return s;
+      };
+      // residual max(0, P - q) over the kept set, canonical order; the kept
+      // weights again when it is empty
+      uint64_t rs[EM];
+#pragma unroll 1
+      for (int j = 0; j < E; ++j) {
+        const int r = r0 + 64 * j;
+        uint64_t v64 = 0ull;
+        if (r < (int)n_s) {
+          const uint64_t cm = T[r];
+          const double v = weight(cm) / Zsd - q_of(comp_idx(cm));
+          v64 = v > 0.0 ? (uint64_t)__double2ll_rn(v * kFix) : 0ull;
+        }
+#pragma unroll
+        for (int jj = 0; jj < EM; ++jj)
+          if (jj == j) rs[jj] = v64;
+      }
+      uint64_t any = 0ull;
+#pragma unroll
+      for (int j = 0; j < EM; ++j)
+        if (j < E) any |= rs[j];
+      any = wg_max<BS>(any, S.x64[2]);
+      double total = (double)Zs;
+      if (any != 0ull) {
+#pragma unroll
+        for (int j = 0; j < EM; ++j)
+          if (j < E) wt[j] = rs[j];
+        total = (double)scan_list(S.x64[0]);
+      }
+      draw(total, [&](uint64_t cm) { publish(0, (int)comp_idx(cm)); });
+    }
+  }
+}
+
+// Merge kernel: one workgroup per row (the launch boundary orders the
+// streaming kernel's records and candidates before it).
+template <int DT, int OP>
+__global__ __launch_bounds__((merge_threads<DT, OP>())) void ss_merge_kernel(KArgs a) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  MSmem& S = *reinterpret_cast<MSmem*>(smem_raw);
+  uint64_t* stage = reinterpret_cast<uint64_t*>(smem_raw + kSmemFixed);
+  // The streaming kernel placed row r's units on XCD floor(8 r / rows) when
+  // its grid splits evenly over the 8 XCDs; the same remap here runs the
+  // row's merge on that XCD as well.
+  int row = blockIdx.x;
+  const int nunits = a.rows * a.U;
+  if ((a.rows & 7) == 0 && (nunits & 31) == 0) row = (row & 7) * (a.rows >> 3) + (row >> 3);
+  merge_row<DT, OP>(a, row, S, stage);
+}
+
+}  // namespace ss

@@ -148,6 +148,55 @@ def test_topk_large_k_small_vocab(ssb):
     check_topk(ssb, inp, "topk-k4096-V20000")
 
 
+def _rows_for_sort(kind, rng, B, V):
+    x = rng.normal(0.0, 2.0, (B, V))
+    if kind == "grid":  # a few hundred equal values per level: crowded bins
+        x = np.round(x * 16) / 16
+    elif kind == "levels":  # three values: more ties than the staging area holds
+        x = rng.choice([0.0, 1.0, 2.0], (B, V), p=[0.9, 0.09, 0.01])
+    elif kind == "outlier":  # one value far above the rest: most keys share a few bins
+        x[np.arange(B), rng.integers(0, V, B)] = 1e30
+    elif kind == "inf":
+        x[np.arange(B), rng.integers(0, V, B)] = np.inf
+    elif kind == "one_unit":  # the row's largest values side by side: units overflow or hide them
+        lo = min(V // 2, V - 1)
+        x[:, lo:lo + 700] += 20.0
+    return x.astype(np.float32)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("kind,V,km", [
+    ("normal", 1, 4), ("normal", 63, 64), ("normal", 2049, 513), ("normal", 4097, 4096), ("normal", 33001, 4096),
+    ("normal", 131073, 1024), ("normal", 262143, 1024), ("grid", 100000, 1500), ("levels", 40000, 700),
+    ("outlier", 50001, 1024), ("inf", 50001, 65), ("one_unit", 60000, 900),
+])
+def test_merge_sort_paths(ssb, dtype, kind, V, km):
+    """The merge's one-pass sort at its edges: one batch of candidates per
+    unit and several, bins of one element and crowded ones, lists that end inside a
+    bin, ties beyond the staging area, key ranges set by one outlier."""
+    rng = np.random.default_rng(V + km)
+    B = 6
+    x = _rows_for_sort(kind, rng, B, V)
+    if dtype == "bf16":
+        x = W.bf16_bits_from_f32(x)
+    k = np.minimum(np.array([km, 1, 2, km - 1, km // 2 + 1, 0]), km).astype(np.int32)
+    dt = W.BF16 if dtype == "bf16" else W.F32
+    check_topk(ssb, W.custom_rows(x, dt, k_max=km, top_k=k), f"sort-{kind}-{V}-{dtype}")
+    # the same rows sampled: top-k, top-p, min-p and the draw on the sorted list, and the kept list itself
+    mode = np.full(B, W.MODE_TEMP | W.MODE_TOPK | W.MODE_TOPP | W.MODE_MINP, np.uint32)
+    top_p = np.array([0.95, 0.3, 0.0, 0.999, 1.0, 0.7], np.float32)
+    min_p = np.array([0.0, 0.1, 0.0, 0.0, 0.02, 2.0], np.float32)
+    inp = W.custom_rows(x, dt, k_max=km, mode=mode, top_k=np.maximum(k, 1), top_p=top_p, min_p=min_p,
+                        temperature=np.array([1.0, 0.5, 1.3, 2.0, 0.8, 1.0], np.float32))
+    for pos in range(2):
+        inp["position"] = np.full(B, pos, np.int64)
+        tok, lp, fl = run_sample(ssb, inp)
+        if kind == "inf":  # probabilities are undefined beside an infinite maximum: its token is drawn
+            assert np.array_equal(tok, oracle.sample(inp)["token"])
+        else:
+            check_sample(inp, tok, lp, fl, f"sort-sample-{kind}-{V}-{dtype}")
+
+
 # --------------------------------------------------------------------------
 # Fused sampling
 # --------------------------------------------------------------------------
