@@ -3,6 +3,8 @@
 #include "ss_row.hpp"
 #include "ss_launch.hpp"
 
+#include <type_traits>
+
 namespace ss {
 
 // ---------------------------------------------------------------------------
@@ -167,6 +169,24 @@ static ss_status launch(KArgs& k, int dtype, const Layout& lay, void* ws, hipStr
   k.usum = (k.op == OP_LOGPROBS || k.full) ? reinterpret_cast<double*>(w + lay.off_usum) : nullptr;
   // patch-table workgroups (a multiple of 8, so the stream's XCD remap holds)
   k.patch_wgs = (k.feat & (SS_REP | SS_FREQ | SS_PRES | SS_BIAS)) ? (lay.rows + 7) & ~7 : 0;
+  // parameter arrays that were not given: any readable memory of their length
+  // (the workspace holds 16 bytes per unit and row), ignored by feat and have
+  k.have = (k.top_k ? kHaveTopK : 0) | (k.seed ? kHaveSeed : 0) | (k.position ? kHavePos : 0);
+  auto some = [&](auto& p) {
+    if (!p) p = reinterpret_cast<std::remove_reference_t<decltype(p)>>(w);
+  };
+  some(k.mode);
+  some(k.temperature);
+  some(k.top_k);
+  some(k.top_p);
+  some(k.min_p);
+  some(k.rep);
+  some(k.freq);
+  some(k.pres);
+  some(k.hist_off);
+  some(k.bias_off);
+  some(k.seed);
+  some(k.position);
   const int di = dtype == SS_BF16 ? 1 : 0;
   const int mop = merge_op(k);
   if (!smem_configured[di][mop]) {

@@ -80,6 +80,7 @@ struct KArgs {
   int64_t ld;
   int op, B, rows, V, U, L, k_cap, cap, pcap, k_out, vec_ok;  // cap: candidate region of a unit in 16-byte words
   uint32_t feat;
+  int have;  // kHave* bits; a NULL parameter array points at the workspace instead, so it can be read (and ignored)
   const uint32_t* mode;
   const float* temperature;
   const int32_t* top_k;
@@ -134,6 +135,32 @@ struct KArgs {
   int nq;              // merge: 16-byte candidate loads a thread issues before anything is known
   double* usum;        // log-probabilities: per unit, sum of exp((x - unit max) / tau) over its valid logits
 };
+
+enum { kHaveTopK = 1, kHaveSeed = 2, kHavePos = 4 };
+
+// Brings the kernel arguments into the scalar cache in one round trip: each
+// 64-byte line costs about 540 cycles on first touch, and the compiler reads
+// them where they are used, one wait after another (2.0 us of a merge row's
+// first barrier, 0.9 us with the lines fetched together).  Returns zero, which
+// the caller adds to its block number so that nothing is read before; the asm
+// is not volatile, so later loads of uniform data stay scalar.
+__device__ __forceinline__ int warm_args() {
+  const auto* p = (const uint32_t __attribute__((address_space(4)))*)__builtin_amdgcn_kernarg_segment_ptr();
+  static_assert(sizeof(KArgs) > 7 * 64 && sizeof(KArgs) <= 8 * 64, "one word of each line");
+  int zero;
+  asm("s_mov_b32 %0, 0"
+      : "=s"(zero)
+      : "s"(p[0]), "s"(p[16]), "s"(p[32]), "s"(p[48]), "s"(p[64]), "s"(p[80]), "s"(p[96]), "s"(p[112]));
+  return zero;
+}
+// The kernel arguments through a pointer the compiler cannot connect with
+// earlier reads: arguments used late are read late (from the scalar cache)
+// instead of being held, and spilled, across the whole kernel.
+__device__ __forceinline__ const KArgs& late_args() {
+  uint64_t p = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
+  asm("" : "+s"(p));
+  return *(const KArgs*)(const KArgs __attribute__((address_space(4)))*)p;
+}
 
 // ---------------------------------------------------------------------------
 // Element layout: lane l, slot s (0..31) holds element (s / VW * 64 + l) * VW
@@ -246,8 +273,15 @@ __device__ __forceinline__ Ctx make_ctx(const KArgs& a, int row) {
     c.ell = 0;
   }
   const int b = c.req;
-  const uint32_t m = (a.op == OP_TOPK ? SS_TOPK : (a.mode ? a.mode[b] : 0u)) & a.feat;
+  const uint32_t m = (a.op == OP_TOPK ? SS_TOPK : a.mode[b]) & a.feat;
   c.mode = m;
+  // read together, used if their bits are set
+  const int h0 = a.hist_off[b], h1 = a.hist_off[b + 1], e0 = a.bias_off[b], e1 = a.bias_off[b + 1];
+  const float rep = a.rep[b], freq = a.freq[b], pres = a.pres[b], temp = a.temperature[b];
+  const float top_p = a.top_p[b], min_p = a.min_p[b];
+  const int topk = a.top_k[b];
+  const uint64_t seed = a.seed[b];
+  const int64_t position = a.position[b];
   const int64_t srow = a.op == OP_VERIFY ? source_row(a, row) : row;
   c.xrow = reinterpret_cast<const unsigned char*>(a.x) + (size_t)(srow < 0 ? 0 : srow) * (size_t)a.ld * DTT<DT>::ES;
   c.hist = nullptr;
@@ -255,8 +289,8 @@ __device__ __forceinline__ Ctx make_ctx(const KArgs& a, int row) {
   c.extra = nullptr;
   c.nextra = 0;
   if (m & (SS_REP | SS_FREQ | SS_PRES)) {
-    c.hist = a.hist_ids + a.hist_off[b];
-    c.nhist = a.hist_off[b + 1] - a.hist_off[b];
+    c.hist = a.hist_ids + h0;
+    c.nhist = h1 - h0;
     if (a.op == OP_VERIFY && a.draft_tokens) {
       c.extra = a.draft_tokens + (size_t)b * a.L;
       c.nextra = c.ell;
@@ -266,20 +300,20 @@ __device__ __forceinline__ Ctx make_ctx(const KArgs& a, int row) {
   c.bias_vals = nullptr;
   c.nbias = 0;
   if (m & SS_BIAS) {
-    c.bias_ids = a.bias_ids + a.bias_off[b];
-    c.bias_vals = a.bias_vals + a.bias_off[b];
-    c.nbias = a.bias_off[b + 1] - a.bias_off[b];
+    c.bias_ids = a.bias_ids + e0;
+    c.bias_vals = a.bias_vals + e0;
+    c.nbias = e1 - e0;
   }
   c.mask = (m & SS_GRAMMAR) ? a.bitmask + (size_t)row * (size_t)a.mask_ld : nullptr;
   if (srow < 0) c.mask = g_none_allowed;  // every token masked
-  c.rep = (m & SS_REP) ? a.rep[b] : 1.0f;
-  c.freq = (m & SS_FREQ) ? a.freq[b] : 0.0f;
-  c.pres = (m & SS_PRES) ? a.pres[b] : 0.0f;
-  c.tau = (m & SS_TEMP) ? a.temperature[b] : 1.0f;
-  c.top_p = (m & SS_TOPP) ? a.top_p[b] : 1.0f;
-  c.min_p = (m & SS_MINP) ? a.min_p[b] : 0.0f;
-  c.seed = a.seed ? a.seed[b] : 0ull;
-  c.pos = (a.position ? a.position[b] : 0) + c.ell;
+  c.rep = (m & SS_REP) ? rep : 1.0f;
+  c.freq = (m & SS_FREQ) ? freq : 0.0f;
+  c.pres = (m & SS_PRES) ? pres : 0.0f;
+  c.tau = (m & SS_TEMP) ? temp : 1.0f;
+  c.top_p = (m & SS_TOPP) ? top_p : 1.0f;
+  c.min_p = (m & SS_MINP) ? min_p : 0.0f;
+  c.seed = (a.have & kHaveSeed) ? seed : 0ull;
+  c.pos = ((a.have & kHavePos) ? position : 0) + c.ell;
   c.dtok = -1;
   if (a.op == OP_VERIFY && c.ell < a.L) c.dtok = a.draft_tokens[(size_t)b * a.L + c.ell];
   c.kcap = false;
@@ -287,17 +321,17 @@ __device__ __forceinline__ Ctx make_ctx(const KArgs& a, int row) {
   c.pexact = a.V <= kPB;
   if (a.op == OP_TOPK) {
     c.greedy = false;
-    int k = a.top_k ? a.top_k[b] : a.k_cap;
+    int k = (a.have & kHaveTopK) ? topk : a.k_cap;
     c.k_eff = k < 0 ? 0 : (k > a.k_cap ? a.k_cap : k);
   } else if (a.op == OP_LOGPROBS) {  // the leading k_cap tokens of rows with the bit
     c.greedy = false;
     c.k_eff = (m & SS_LOGPROBS) ? a.k_cap : 0;
   } else {
     c.greedy = (m & SS_GREEDY) || ((m & SS_TEMP) && c.tau <= 0.0f);
-    const int64_t kreq = ((m & SS_TOPK) && a.top_k[b] >= 1) ? (int64_t)a.top_k[b] : (int64_t)INT_MAX;
+    const int64_t kreq = ((m & SS_TOPK) && topk >= 1) ? (int64_t)topk : (int64_t)INT_MAX;
     c.k_eff = kreq < a.k_cap ? (int)kreq : a.k_cap;
     c.kcap = !c.greedy && kreq > a.k_cap;
-    c.full_row = a.full && !c.greedy && !((m & SS_TOPK) && a.top_k[b] >= 1);
+    c.full_row = a.full && !c.greedy && !((m & SS_TOPK) && topk >= 1);
     if (c.greedy) c.k_eff = 1;
   }
   return c;
@@ -504,12 +538,13 @@ struct WStage {
 // to the unit's region and returns their number.  Groups are compacted into
 // LDS (about one in forty is emitted), then 64 elements at a time are tested
 // and compacted by ballot: one store per element instead of a 16-byte record
-// per group.  bf16: (key16 << 16) | index within the unit; fp32: (key, index
-// within the unit).  Group g of a lane starts at element ((g / 2) 64 + lane)
+// per group.  An element is stored so that one unsigned comparison ranks it
+// (key, lower index first): bf16 as (key16 << 16) | (0xFFFF - index within the
+// unit), fp32 as its 64-bit composite.  Group g of a lane starts at element ((g / 2) 64 + lane)
 // VW + (g % 2) GE of the unit, i.e. is group ((g / 2) 64 + lane) 2 + g % 2.
 template <int DT, int NG>
 __device__ __forceinline__ uint32_t emit_elems(const uint2 (&gk)[NG], uint32_t gmask, uint32_t off, uint32_t total,
-                                               uint32_t t, uint4* region, WStage& W) {
+                                               uint32_t t, uint32_t lo, uint4* region, WStage& W) {
   constexpr int GE = DTT<DT>::GE;
   const int ln = lane();
   uint32_t out = 0u;
@@ -536,8 +571,8 @@ __device__ __forceinline__ uint32_t emit_elems(const uint2 (&gk)[NG], uint32_t g
       const uint64_t m = __ballot(hit);
       const uint32_t pos = out + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
       if (hit) {
-        if constexpr (DT == SS_BF16) reinterpret_cast<uint32_t*>(region)[pos] = (key << 16) | e;
-        else reinterpret_cast<uint2*>(region)[pos] = make_uint2(key, e);
+        if constexpr (DT == SS_BF16) reinterpret_cast<uint32_t*>(region)[pos] = (key << 16) | (0xFFFFu - e);
+        else reinterpret_cast<uint2*>(region)[pos] = make_uint2(~(lo + e), key);
       }
       out += (uint32_t)__popcll(m);
     }
@@ -560,7 +595,11 @@ __device__ __forceinline__ void scan_unit(const KArgs& a, int gu, WStage& W) {
   const int64_t srow = a.op == OP_VERIFY ? source_row(a, row) : row;
   const int n = srow < 0 ? 0 : min(kUE, a.V - lo);  // a row outside the tree reads nothing
   const int b = a.op == OP_VERIFY ? row / (a.L + 1) : row;
-  const uint32_t mode = (a.op == OP_TOPK ? SS_TOPK : (a.mode ? a.mode[b] : 0u)) & a.feat;
+  // the request's parameters: read together, before they are known to be needed
+  const uint32_t mode_v = a.mode[b];
+  const float temp = a.temperature[b];
+  const int topk = a.top_k[b];
+  const uint32_t mode = (a.op == OP_TOPK ? SS_TOPK : mode_v) & a.feat;
   const uint32_t* mask = (mode & SS_GRAMMAR) ? a.bitmask + (size_t)row * (size_t)a.mask_ld : nullptr;
   const unsigned char* xrow =
       reinterpret_cast<const unsigned char*>(a.x) + (size_t)(srow < 0 ? 0 : srow) * (size_t)a.ld * ES;
@@ -604,13 +643,13 @@ __device__ __forceinline__ void scan_unit(const KArgs& a, int gu, WStage& W) {
   // 2. row parameters (scalar), read while the chunks are in flight
   int k_eff;
   if (a.op == OP_TOPK) {
-    const int k = a.top_k ? a.top_k[b] : a.k_cap;
+    const int k = (a.have & kHaveTopK) ? topk : a.k_cap;
     k_eff = k < 0 ? 0 : min(k, a.k_cap);
   } else if (a.op == OP_LOGPROBS) {
     k_eff = (mode & SS_LOGPROBS) ? a.k_cap : 0;
   } else {
-    const bool greedy = (mode & SS_GREEDY) || ((mode & SS_TEMP) && a.temperature[b] <= 0.0f);
-    k_eff = greedy ? 1 : (((mode & SS_TOPK) && a.top_k[b] >= 1) ? min(a.top_k[b], a.k_cap) : a.k_cap);
+    const bool greedy = (mode & SS_GREEDY) || ((mode & SS_TEMP) && temp <= 0.0f);
+    k_eff = greedy ? 1 : (((mode & SS_TOPK) && topk >= 1) ? min(topk, a.k_cap) : a.k_cap);
   }
 
   // 3. keys, unit maximum, threshold, emission
@@ -704,7 +743,7 @@ __device__ __forceinline__ void scan_unit(const KArgs& a, int gu, WStage& W) {
       uint2 gk[8];
 #pragma unroll
       for (int g = 0; g < 8; ++g) gk[g] = make_uint2(kd[2 * g], kd[2 * g + 1]);
-      count = emit_elems<DT>(gk, gmask, off, total, t16, region, W);
+      count = emit_elems<DT>(gk, gmask, off, total, t16, (uint32_t)lo, region, W);
     }
     t = t16 >= 0x10000u ? kNoEmit : (t16 << 16);
     wm = wm16 << 16;
@@ -786,7 +825,7 @@ __device__ __forceinline__ void scan_unit(const KArgs& a, int gu, WStage& W) {
       uint2 gk[16];
 #pragma unroll
       for (int g = 0; g < 16; ++g) gk[g] = make_uint2(kk[2 * g], kk[2 * g + 1]);
-      count = emit_elems<DT>(gk, gmask, off, total, t, region, W);
+      count = emit_elems<DT>(gk, gmask, off, total, t, (uint32_t)lo, region, W);
     }
   }
   if (ln == 0) a.rec[gu] = make_uint4(t, count, wm, cut);
@@ -959,7 +998,7 @@ __device__ __forceinline__ void patch_row(const KArgs& a, int row, PSmem& P) {
 template <int DT, bool LP>
 __global__ __launch_bounds__(kSBlock) void ss_stream_kernel(KArgs a) {
   extern __shared__ __align__(16) unsigned char psmem[];
-  int bid = blockIdx.x;
+  int bid = blockIdx.x + warm_args();
   if (bid < a.patch_wgs) {  // patch-table workgroups (a multiple of 8) come first
     // on the XCD that streams the row (below), so the gathers of its listed
     // ids and its units' loads share that XCD's L2
@@ -993,7 +1032,7 @@ __global__ __launch_bounds__(kBlock) void ss_materialize_kernel(KArgs a) {
   const int lo = tile * TILE;
   const int hi = min(a.V, lo + TILE);
   const int b = row;
-  const uint32_t mode = (a.mode ? a.mode[b] : 0u) & a.feat;
+  const uint32_t mode = a.mode[b] & a.feat;
   const uint32_t* mask = (mode & SS_GRAMMAR) ? a.bitmask + (size_t)row * (size_t)a.mask_ld : nullptr;
   const unsigned char* xrow = reinterpret_cast<const unsigned char*>(a.x) + (size_t)row * (size_t)a.ld * DTT<DT>::ES;
   const RowSummary s = a.summ[row];

@@ -16,17 +16,17 @@ void launch_merge(const KArgs& k, int rows, int smem, hipStream_t st) {
   // the candidate loads a merge thread issues up front: its unit's share, and
   // enough of them for the elements a unit emits at the call's largest k (the
   // quota of groups, some holding more than one)
-  constexpr int BS = merge_threads<DT, OP>(), EPQ = DT == SS_BF16 ? 4 : 2, NQM = DT == SS_BF16 ? 3 : 6;
+  constexpr int BS = merge_threads<OP>(), EPQ = DT == SS_BF16 ? 4 : 2, NQM = DT == SS_BF16 ? 3 : 6;
   a.tpu = BS / a.U > 1 ? BS / a.U : 1;
   a.tpu_inv = ((1 << 20) + a.tpu - 1) / a.tpu;
   const int q = quota(a.k_cap, a.U), want = q + q / 8 + 4;
   const int nq = (want + a.tpu * EPQ - 1) / (a.tpu * EPQ);
   a.nq = nq < NQM ? nq : NQM;
-  hipLaunchKernelGGL((ss_merge_kernel<DT, OP>), dim3((unsigned)rows), dim3(BS), smem, st, a);
+  hipLaunchKernelGGL((ss_merge_kernel<DT, OP, BS>), dim3((unsigned)rows), dim3(BS), smem, st, a);
 }
 template <int DT, int OP>
 hipError_t merge_smem_limit(int bytes) {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(&ss_merge_kernel<DT, OP>),
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(&ss_merge_kernel<DT, OP, merge_threads<OP>()>),
                              hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
 }
 template void launch_merge<SS_MERGE_DT, SS_MERGE_OP>(const KArgs&, int, int, hipStream_t);

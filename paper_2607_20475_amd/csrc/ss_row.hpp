@@ -25,6 +25,8 @@
 // What bounds it is latency: a row is one workgroup's chain of one global round
 // trip and nine barriers (LDS only, so loads stay in flight across them).
 #pragma once
+#include <type_traits>
+
 #include "ss_impl.hpp"
 
 namespace ss {
@@ -34,8 +36,13 @@ constexpr int kNB = 1 << kNBLog;  // key bins of the one-pass sort
 constexpr int kCrowd = 256;       // bins up to this occupancy are ranked by comparison
 constexpr uint32_t kNone = 0xFFFFFFFFu;
 
-// Threads of a merge workgroup.
-template <int DT, int OP>
+// Threads of a merge workgroup.  A wavefront issues a dependent instruction
+// every four cycles and a SIMD keeps two wavefronts at that rate, so 512 threads
+// run the fixed part of a row (reductions, scans) as fast as one wavefront
+// would; 1024 made every row of up to 1024 entries slower (B=64 V=2^17 bf16
+// sampling: 12.4 -> 13.9 us, its 64-entry lists 8.9 -> 11.5 us).  Top-k alone
+// lists up to 4096 entries and has little else to do: 1024.
+template <int OP>
 constexpr int merge_threads() {
   return OP == OP_TOPK ? 1024 : kBlock;
 }
@@ -47,6 +54,8 @@ struct MSmem {
   uint32_t x32[4][kMaxWaves];
   uint64_t bc64[4];
   uint32_t bc[12];
+  uint64_t best;               // greedy rows: the maximum
+  uint4 wred[kMaxWaves];       // per wave: largest threshold key, its lowest cut, row maximum, longest list
   uint32_t rmask[kMaxU / 32];  // units re-read by the slow path
   alignas(16) uint32_t pbits[kPB / 32];  // bit pbit(id) set for every patched id
   int32_t hk[kH];                        // patched id (or -1)
@@ -72,6 +81,12 @@ static_assert(offsetof(MSmem, hk) == offsetof(MSmem, pbits) + sizeof(uint32_t) *
                   sizeof(uint32_t) * (kPB / 32 + 2 * kH) >= sizeof(uint64_t) * SS_MAX_K,
               "sparse draft list view");
 __device__ __forceinline__ uint64_t* qlist_view(MSmem& S) { return reinterpret_cast<uint64_t*>(S.pbits); }
+
+// A value read from LDS that every thread knows to be the same.
+__device__ __forceinline__ uint32_t uniform(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ uint64_t uniform(uint64_t v) {
+  return ((uint64_t)uniform((uint32_t)(v >> 32)) << 32) | uniform((uint32_t)v);
+}
 
 // Workgroup reductions (scratch reusable on return).
 template <int BS, typename T, typename Op>
@@ -106,6 +121,7 @@ __device__ __forceinline__ bool maybe_patched(const MSmem& S, int id, bool exact
 }
 __device__ __forceinline__ int hfind(const MSmem& S, int id) {
   uint32_t s = hslot(id);
+#pragma unroll 1
   for (int p = 0; p < kProbe; ++p) {
     const int k = S.hk[s];
     if (k == id) return (int)s;
@@ -291,8 +307,8 @@ __device__ __forceinline__ int slow_select(const KArgs& a, const Ctx& c, MSmem& 
       const uint32_t* src = reinterpret_cast<const uint32_t*>(a.cand + g * a.cap);
       for (uint32_t i = (uint32_t)sub; i < cn; i += (uint32_t)tpu) {
         const uint32_t w = src[i * EPW];
-        if constexpr (DT == SS_BF16) apply(w & 0xFFFF0000u, (uint32_t)(u * kUE) + (w & 0xFFFFu));
-        else apply(w, (uint32_t)(u * kUE) + src[i * EPW + 1]);
+        if constexpr (DT == SS_BF16) apply(w & 0xFFFF0000u, (uint32_t)(u * kUE) + 0xFFFFu - (w & 0xFFFFu));
+        else apply(src[i * EPW + 1], ~w);
       }
     }
     // 2. every element of the marked units (grammar mask applied, NaN
@@ -403,7 +419,7 @@ __device__ __forceinline__ int slow_select(const KArgs& a, const Ctx& c, MSmem& 
     // what the pass found
     bool have_thr = false;
     if (op == V_MAX) {
-      best = wg_max<BS>(best, S.x64[0]);
+      best = uniform(wg_max<BS>(best, S.x64[0]));
       if (second) {
         if (tid == 0) pool[0] = best;
         lds_barrier();
@@ -412,7 +428,7 @@ __device__ __forceinline__ int slow_select(const KArgs& a, const Ctx& c, MSmem& 
       thr = best;
       have_thr = true;
     } else if (op == V_COUNT) {
-      acc = wg_sum<BS>(acc, S.x32[0]);
+      acc = uniform(wg_sum<BS>(acc, S.x32[0]));
       if (acc < want) {  // too few emitted: everything valid takes part
         thr = comp_of(kKeyFloor, kNone);
         have_thr = true;
@@ -420,7 +436,7 @@ __device__ __forceinline__ int slow_select(const KArgs& a, const Ctx& c, MSmem& 
         op = V_KEY;
       }
     } else if (op == V_COLLECT) {
-      const uint32_t n = S.bc[8];
+      const uint32_t n = uniform(S.bc[8]);
       if (n <= (uint32_t)a.pcap) {
         lds_barrier();
         return (int)n;
@@ -457,7 +473,7 @@ __device__ __forceinline__ int slow_select(const KArgs& a, const Ctx& c, MSmem& 
         run += h[q];
       }
       lds_barrier();
-      const uint32_t d = S.bc[4], before = S.bc[5], hd = S.bc[6];
+      const uint32_t d = uniform(S.bc[4]), before = uniform(S.bc[5]), hd = uniform(S.bc[6]);
       need -= before;
       if (key) {
         prefix = (prefix << 8) | d;
@@ -537,16 +553,48 @@ __device__ __forceinline__ double row_norm_part(const KArgs& a, const Ctx& c, co
 }
 
 
+// Sums of the NW wave totals in scratch: of those before this wave, and of all
+// (one read and a few DPP steps per lane instead of a loop over the waves).
+template <int NW, typename T>
+__device__ __forceinline__ void wave_prefix(const T* scratch, int wv, T& before, T& total) {
+  const int w = lane() & (NW - 1);
+  T x = scratch[w];
+  T y = w < wv ? x : T(0);
+  auto step = [&](auto c) {
+    constexpr int C = decltype(c)::value;
+    x += dppT<T, C>(x, x);
+    y += dppT<T, C>(y, y);
+  };
+  step(std::integral_constant<int, 0xB1>{});   // quad_perm [1,0,3,2]
+  step(std::integral_constant<int, 0x4E>{});   // quad_perm [2,3,0,1]
+  step(std::integral_constant<int, 0x141>{});  // row_half_mirror
+  static_assert(NW == 8 || NW == 16, "wave totals fill half a row or a row");
+  if constexpr (NW == 16) step(std::integral_constant<int, 0x140>{});  // row_mirror
+  before = y;
+  total = x;
+}
+
+// Maximum over the NW lanes of every half row (row): lane l holds wave l mod
+// NW's value; uniform.
+template <int NW>
+__device__ __forceinline__ uint32_t waves_max(uint32_t x) {
+  x = max(x, dpp_mov<0xB1>(x));
+  x = max(x, dpp_mov<0x4E>(x));
+  x = max(x, dpp_mov<0x141>(x));
+  if constexpr (NW == 16) x = max(x, dpp_mov<0x140>(x));
+  return __builtin_amdgcn_readfirstlane(x);
+}
+
 // Merge of one row by the whole workgroup.
-template <int DT, int OP>
-__device__ __forceinline__ void merge_row(const KArgs& a, int row, MSmem& S, uint64_t* stage) {
-  constexpr int BS = merge_threads<DT, OP>();
+template <int DT, int OP, int BS>
+__device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S, uint64_t* stage) {
+  const KArgs& a = early;
   constexpr int NW = BS / 64;
   constexpr int EPQ = DT == SS_BF16 ? 4 : 2;   // candidates per 16-byte load
   constexpr int NQM = DT == SS_BF16 ? 3 : 6;   // candidate loads a thread holds at most
   constexpr int EM = SS_MAX_K / BS;            // list entries per thread at most
   const int tid = threadIdx.x;
-  const int ln = lane(), wv = wave();
+  const int ln = lane(), wv = __builtin_amdgcn_readfirstlane(wave());
   const int U = a.U;
   int b = row, ell = 0;
   if constexpr (OP == OP_VERIFY) {
@@ -590,15 +638,19 @@ __device__ __forceinline__ void merge_row(const KArgs& a, int row, MSmem& S, uin
   uint64_t seed = 0ull;
   int64_t pos = ell;
   if constexpr (OP == OP_TOPK) {
-    kreq_v = a.top_k ? a.top_k[b] : a.k_cap;
+    kreq_v = a.top_k[b];
+    if (!(a.have & kHaveTopK)) kreq_v = a.k_cap;
   } else {
-    mode = a.mode[b] & a.feat;
-    if (a.feat & SS_TEMP) temp = a.temperature[b];
-    if (a.feat & SS_TOPK) kreq_v = a.top_k[b];
-    if (a.feat & SS_TOPP) topp_v = a.top_p[b];
-    if (a.feat & SS_MINP) minp_v = a.min_p[b];
-    if (a.seed) seed = a.seed[b];
-    if (a.position) pos += a.position[b];
+    mode = a.mode[b];
+    temp = a.temperature[b];
+    kreq_v = a.top_k[b];
+    topp_v = a.top_p[b];
+    minp_v = a.min_p[b];
+    const uint64_t sd = a.seed[b];
+    const int64_t ps = a.position[b];
+    mode &= a.feat;
+    seed = (a.have & kHaveSeed) ? sd : 0ull;
+    pos += (a.have & kHavePos) ? ps : 0;
     if constexpr (OP == OP_VERIFY) {
       if (ell < a.L) dtok = a.draft_tokens[(size_t)b * a.L + ell];
     }
@@ -613,13 +665,41 @@ __device__ __forceinline__ void merge_row(const KArgs& a, int row, MSmem& S, uin
   if (tid < kMaxU / 32) S.rmask[tid] = 0u;
   if (tid == 0) {
     S.bc[0] = 0u;     // entries of the bins that hold the list
-    S.bc[1] = 0u;     // largest of those bins
+    S.bc[1] = 0u;     // set when one of them is crowded
     S.bc[2] = kNone;  // top-p: last rank kept
     S.bc[3] = kNone;  // min-p: first rank dropped
     S.bc[7] = kNone;  // top-p against the whole row: last rank kept
     S.bc64[3] = 0ull;
+    S.best = 0ull;
   }
   lds_barrier();
+
+  // the request, and what its epilogue needs (while the loads are in flight)
+  bool greedy = false, kcap = false, full_row = false;
+  int want;
+  double tau = 1.0, itau = 1.0, lt = 0.0, u0 = 0.0;
+  bool minp = false, topp = false;
+  if constexpr (OP == OP_TOPK) {
+    want = kreq_v < 0 ? 0 : min(kreq_v, a.k_cap);
+  } else if constexpr (OP == OP_LOGPROBS) {
+    want = (mode & SS_LOGPROBS) ? a.k_cap : 0;
+  } else {
+    const float tm = (mode & SS_TEMP) ? temp : 1.0f;
+    greedy = (mode & SS_GREEDY) || ((mode & SS_TEMP) && tm <= 0.0f);
+    const bool cutk = (mode & SS_TOPK) && kreq_v >= 1;
+    const int kreq = cutk ? kreq_v : INT_MAX;
+    kcap = !greedy && kreq > a.k_cap;
+    full_row = a.full && !greedy && !cutk;
+    want = greedy ? 1 : min(kreq, a.k_cap);
+    if (!greedy) {
+      tau = (double)tm;
+      itau = 1.0 / tau;
+      minp = (mode & SS_MINP) && minp_v > 0.0f;
+      topp = (mode & SS_TOPP) && topp_v < 1.0f;
+      if (minp) lt = log((double)minp_v);
+      if (OP != OP_PROCESS) u0 = uniform01(seed, (uint32_t)b, pos, 0);
+    }
+  }
 
   // 2. largest threshold, row maximum, longest candidate list; the patch table
   const uint32_t cnt = (act && r4.y != kOvf) ? r4.y : 0u;
@@ -645,45 +725,28 @@ __device__ __forceinline__ void merge_row(const KArgs& a, int row, MSmem& S, uin
       }
     }
   }
-  uint64_t tc = (act && r4.x != kNoEmit) ? comp_of(r4.x, r4.w) : 0ull;
-  uint32_t hi = act ? r4.z : 0u;
-  uint32_t cmax = act ? r4.y : 0u;  // kOvf when a unit overflowed
-  tc = wave_max(tc);
-  hi = wave_max_u32(hi);
-  hfmax = wave_max_u32(hfmax);
-  cmax = wave_max_u32(cmax);
-  if (ln == 0) {
-    S.x64[0][wv] = tc;
-    S.x32[0][wv] = hi;
-    S.x32[1][wv] = hfmax;
-    S.x32[2][wv] = cmax;
+  // (the largest threshold composite: its key first, then the lowest cut of
+  // that key; shared LDS words would serialise the units, one after another)
+  {
+    const uint32_t key = (act && r4.x != kNoEmit) ? r4.x : 0u;
+    const uint32_t kw = wave_max_u32(key);
+    const uint32_t cw = ~wave_max_u32(key == kw ? ~r4.w : 0u);
+    const uint32_t hw = wave_max_u32(act ? r4.z : 0u);
+    const uint32_t lw = wave_max_u32(act ? r4.y : 0u);  // kOvf when a unit overflowed
+    hfmax = wave_max_u32(hfmax);
+    if (ln == 0) {
+      S.wred[wv] = make_uint4(kw, cw, hw, lw);
+      S.x32[1][wv] = hfmax;
+    }
   }
   lds_barrier();
-#pragma unroll
-  for (int w = 0; w < NW; ++w) {
-    tc = max(tc, S.x64[0][w]);
-    hi = max(hi, S.x32[0][w]);
-    hfmax = max(hfmax, S.x32[1][w]);
-    cmax = max(cmax, S.x32[2][w]);
-  }
+  const uint4 wr = S.wred[ln & (NW - 1)];
+  hfmax = waves_max<NW>(S.x32[1][ln & (NW - 1)]);
+  const uint32_t hi = waves_max<NW>(wr.z), cmax = waves_max<NW>(wr.w);
+  const uint32_t tkw = waves_max<NW>(wr.x);
+  const uint64_t tc = tkw == 0u ? 0ull : comp_of(tkw, ~waves_max<NW>(wr.x == tkw ? ~wr.y : 0u));
   const uint32_t tck = comp_key(tc), tcut = comp_idx(tc);
 
-  // the request
-  bool greedy = false, kcap = false, full_row = false;
-  int want;
-  if constexpr (OP == OP_TOPK) {
-    want = kreq_v < 0 ? 0 : min(kreq_v, a.k_cap);
-  } else if constexpr (OP == OP_LOGPROBS) {
-    want = (mode & SS_LOGPROBS) ? a.k_cap : 0;
-  } else {
-    const float tm = (mode & SS_TEMP) ? temp : 1.0f;
-    greedy = (mode & SS_GREEDY) || ((mode & SS_TEMP) && tm <= 0.0f);
-    const bool cutk = (mode & SS_TOPK) && kreq_v >= 1;
-    const int kreq = cutk ? kreq_v : INT_MAX;
-    kcap = !greedy && kreq > a.k_cap;
-    full_row = a.full && !greedy && !cutk;
-    want = greedy ? 1 : min(kreq, a.k_cap);
-  }
   int flags = kcap ? SS_FLAG_KCAP : 0;
   const bool empty = hi < kKeyFloor;
   bool slow = cmax == kOvf || pst == 2;
@@ -691,43 +754,63 @@ __device__ __forceinline__ void merge_row(const KArgs& a, int row, MSmem& S, uin
   // 3. the elements that take part
   const int covered = a.nq * tpu * EPQ;  // candidates per unit in one batch
   const int nbatch = (!empty && want > 0 && !slow) ? max(1, (int)((cmax + (uint32_t)covered - 1u) / (uint32_t)covered)) : 0;
-  auto elem = [&](int j, int e, uint32_t& key, uint32_t& idx) {
-    const uint32_t w = e == 0 ? cq[j].x : (e == 1 ? cq[j].y : (e == 2 ? cq[j].z : cq[j].w));
+  constexpr int NE = NQM * EPQ;
+  // composite of candidate x = EPQ j + e
+  const uint32_t ubase = ~(uint32_t)(u * kUE) - 0xFFFFu;
+  auto elem = [&](int x) -> uint64_t {
+    const uint4 q = cq[x / EPQ];
+    const int e = x % EPQ;
     if constexpr (DT == SS_BF16) {
-      key = w & 0xFFFF0000u;
-      idx = (uint32_t)(u * kUE) + (w & 0xFFFFu);
+      const uint32_t w = e == 0 ? q.x : (e == 1 ? q.y : (e == 2 ? q.z : q.w));
+      return ((uint64_t)(w & 0xFFFF0000u) << 32) | (ubase + (w & 0xFFFFu));
     } else {
-      key = e == 0 ? cq[j].x : cq[j].z;
-      idx = (uint32_t)(u * kUE) + (e == 0 ? cq[j].y : cq[j].w);
+      return e == 0 ? ((uint64_t)q.y << 32) | q.x : ((uint64_t)q.w << 32) | q.z;
     }
   };
+  // bf16: tc as a stored word of this thread's unit
+  uint32_t wthr = tck;
+  if constexpr (DT == SS_BF16) {
+    const uint32_t lo = (uint32_t)(u * kUE);
+    if (tcut < lo) wthr = tck + 0x10000u;
+    else if (tcut - lo < (uint32_t)kUE) wthr = tck | (0xFFFFu - (tcut - lo));
+  }
+  // the candidates of a batch that are at or above tc and no raw copy of a
+  // patched id (every LDS read is issued before any is used)
   auto select = [&](int batch) -> uint32_t {
     uint32_t sel = 0u;
 #pragma unroll
     for (int j = 0; j < NQM; ++j) {
       if (j < a.nq) {
-        const uint32_t n0 = (uint32_t)(((batch * a.nq + j) * tpu + sub) * EPQ);
+        const int rem = (int)cnt - ((batch * a.nq + j) * tpu + sub) * EPQ;
 #pragma unroll
         for (int e = 0; e < EPQ; ++e) {
-          uint32_t key, idx;
-          elem(j, e, key, idx);
-          const bool at = key > tck || (key == tck && idx <= tcut);  // composite >= tc
-          if (n0 + (uint32_t)e < cnt && at) sel |= 1u << (j * EPQ + e);
+          bool at;
+          if constexpr (DT == SS_BF16) at = (e == 0 ? cq[j].x : (e == 1 ? cq[j].y : (e == 2 ? cq[j].z : cq[j].w))) >= wthr;
+          else at = elem(j * EPQ + e) >= tc;
+          sel |= (at && e < rem) ? 1u << (j * EPQ + e) : 0u;
         }
       }
     }
-    if (pst == 1 && sel != 0u) {  // raw copies of patched ids
+    if (pst == 1 && __ballot(sel != 0u) != 0ull) {
+      uint32_t pw[NE];
 #pragma unroll
-      for (int j = 0; j < NQM; ++j) {
-        if (j < a.nq) {
+      for (int x = 0; x < NE; ++x)
+        if (x / EPQ < a.nq) pw[x] = S.pbits[(pbit((int)comp_idx(elem(x)), pexact) >> 5) & (kPB / 32 - 1)];
+      uint32_t hit = 0u;
 #pragma unroll
-          for (int e = 0; e < EPQ; ++e) {
-            if ((sel >> (j * EPQ + e)) & 1u) {
-              uint32_t key, idx;
-              elem(j, e, key, idx);
-              if (lds_patched(S, (int)idx, pexact)) sel &= ~(1u << (j * EPQ + e));
-            }
-          }
+      for (int x = 0; x < NE; ++x)
+        if (x / EPQ < a.nq) hit |= ((pw[x] >> (pbit((int)comp_idx(elem(x)), pexact) & 31u)) & 1u) << x;
+      hit &= sel;
+      if (pexact) {
+        sel &= ~hit;
+      } else {  // hashed bitmap: confirmed in the table
+        while (hit != 0u) {
+          const uint32_t low = hit & (0u - hit);
+          int id = 0;
+#pragma unroll
+          for (int x = 0; x < NE; ++x) id = low == (1u << x) ? (int)comp_idx(elem(x)) : id;
+          if (hfind(S, id) >= 0) sel &= ~low;
+          hit ^= low;
         }
       }
     }
@@ -735,72 +818,105 @@ __device__ __forceinline__ void merge_row(const KArgs& a, int row, MSmem& S, uin
   };
   uint32_t sel = 0u;
   uint32_t fsel = 0u;  // patched finals at or above tc
+  uint64_t fc[4 * KT];
   if (nbatch > 0 && pst == 1) {
 #pragma unroll
     for (int m = 0; m < KT; ++m) {
-      const int ids[4] = {(int)tid4[m].x, (int)tid4[m].y, (int)tid4[m].z, (int)tid4[m].w};
+      const uint32_t ids[4] = {tid4[m].x, tid4[m].y, tid4[m].z, tid4[m].w};
       const uint32_t fk[4] = {tfin4[m].x, tfin4[m].y, tfin4[m].z, tfin4[m].w};
 #pragma unroll
-      for (int q = 0; q < 4; ++q)
-        if (ids[q] >= 0 && fk[q] >= kKeyFloor && comp_of(fk[q], (uint32_t)ids[q]) >= tc) fsel |= 1u << (4 * m + q);
+      for (int q = 0; q < 4; ++q) {
+        fc[4 * m + q] = comp_of(fk[q], ids[q]);
+        if ((int)ids[q] >= 0 && fk[q] >= kKeyFloor && fc[4 * m + q] >= tc) fsel |= 1u << (4 * m + q);
+      }
     }
   }
-  // calls f(key, index) for each of this thread's elements
-  auto each = [&](bool again, auto&& f) {
-    for (int batch = 0; batch < nbatch; ++batch) {
-      if (batch > 0 || (again && nbatch > 1)) load_batch(batch);
-      if (!(again && nbatch == 1)) sel = select(batch);
-      if (sel != 0u) {
-#pragma unroll
-        for (int j = 0; j < NQM; ++j) {
-#pragma unroll
-          for (int e = 0; e < EPQ; ++e) {
-            if ((sel >> (j * EPQ + e)) & 1u) {
-              uint32_t key, idx;
-              elem(j, e, key, idx);
-              f(key, idx);
-            }
-          }
-        }
-      }
-    }
-    if (fsel != 0u) {
-#pragma unroll
-      for (int m = 0; m < KT; ++m) {
-        const uint32_t ids[4] = {tid4[m].x, tid4[m].y, tid4[m].z, tid4[m].w};
-        const uint32_t fk[4] = {tfin4[m].x, tfin4[m].y, tfin4[m].z, tfin4[m].w};
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          if ((fsel >> (4 * m + q)) & 1u) f(fk[q], ids[q]);
-      }
-    }
-  };
-
   uint64_t* sorted = stage + a.pcap;
   const uint64_t* T = sorted;  // the row's list in canonical order
   int nT = 0;
   bool crowded = false;  // the list (or a superset) is in stage, unsorted
   uint32_t nB = 0u;      // entries of stage
-  if (nbatch > 0) {
-    if (want == 1) {
-      uint64_t mc = 0ull;
-      each(false, [&](uint32_t key, uint32_t idx) { mc = max(mc, comp_of(key, idx)); });
-      mc = wave_max(mc);
-      if (ln == 0) S.x64[1][wv] = mc;
-      lds_barrier();
+  // Bins in canonical order: 2^sh steps of an order value below the largest
+  // possible key.  bf16 keys lie on a grid of 2^16, so the order value of a grid
+  // element carries its index in the low half (a key that a hundred ids share
+  // spreads over bins of a few); an off-grid final value goes behind every index
+  // of the grid key above it.
+  const uint32_t kmax = DT == SS_BF16 ? (max(hi, hfmax) + 0xFFFFu) & 0xFFFF0000u : max(hi, hfmax);
+  const int ish = max(0, 16 - __clz(max(a.V - 1, 1)));
+  const int sh = max(0, 32 - __clz((kmax - tck) | (DT == SS_BF16 ? 0xFFFFu : 0u)) - kNBLog);
+  auto bin_of = [&](uint64_t cm) -> uint32_t {
+    const uint32_t key = comp_key(cm);
+    uint32_t o = kmax - key;
+    if constexpr (DT == SS_BF16) o |= (key & 0xFFFFu) ? 0xFFFFu : comp_idx(cm) >> ish;
+    return o >> sh;
+  };
+  // first pass: the maximum (want == 1) or the bins' counts; second pass:
+  // every element to its bin's next place (all places asked for before any is used)
+  uint32_t bp[NE + 4 * KT];
+  bool single = want == 1;
+  for (int pass = 0; pass < 2 && nbatch > 0 && !slow; ++pass) {
+    for (int batch = 0; batch < nbatch; ++batch) {
+      if (batch > 0 || (pass > 0 && nbatch > 1)) load_batch(batch);
+      if (pass == 0 || nbatch > 1) {
+        sel = select(batch);
+        if (!single) {
 #pragma unroll
-      for (int w = 0; w < NW; ++w) mc = max(mc, S.x64[1][w]);
+          for (int x = 0; x < NE; ++x)
+            if (x / EPQ < a.nq) bp[x] = bin_of(elem(x)) & (kNB - 1);
+        }
+      }
+      const uint32_t fs = batch == 0 ? fsel : 0u;
+      if (single) {
+        uint64_t mc = 0ull;
+#pragma unroll
+        for (int x = 0; x < NE; ++x)
+          if (x / EPQ < a.nq) mc = ((sel >> x) & 1u) ? max(mc, elem(x)) : mc;
+        if (fs != 0u) {
+#pragma unroll
+          for (int x = 0; x < 4 * KT; ++x) mc = ((fs >> x) & 1u) ? max(mc, fc[x]) : mc;
+        }
+        if (mc != 0ull) atomicMax((unsigned long long*)&S.best, (unsigned long long)mc);
+      } else if (pass == 0) {
+#pragma unroll
+        for (int x = 0; x < NE; ++x)
+          if ((sel >> x) & 1u) atomicAdd(&S.bins[bp[x]], 1u);
+        if (fs != 0u) {
+#pragma unroll
+          for (int x = 0; x < 4 * KT; ++x) {
+            bp[NE + x] = bin_of(fc[x]) & (kNB - 1);
+            if ((fs >> x) & 1u) atomicAdd(&S.bins[bp[NE + x]], 1u);
+          }
+        }
+      } else {
+#pragma unroll
+        for (int x = 0; x < NE; ++x)
+          if ((sel >> x) & 1u) bp[x] = atomicAdd(&S.bins[bp[x]], 1u);
+        if (fs != 0u) {
+#pragma unroll
+          for (int x = 0; x < 4 * KT; ++x)
+            if ((fs >> x) & 1u) bp[NE + x] = atomicAdd(&S.bins[bp[NE + x]], 1u);
+        }
+#pragma unroll
+        for (int x = 0; x < NE; ++x)
+          if (((sel >> x) & 1u) && bp[x] < nB) stage[bp[x]] = elem(x);
+        if (fs != 0u) {
+#pragma unroll
+          for (int x = 0; x < 4 * KT; ++x)
+            if (((fs >> x) & 1u) && bp[NE + x] < nB) stage[bp[NE + x]] = fc[x];
+        }
+      }
+    }
+    lds_barrier();
+    if (single) {
+      const uint64_t mc = uniform(S.best);
       slow = mc == 0ull;
       nT = slow ? 0 : 1;
       if (tid == 0) sorted[0] = mc;
       lds_barrier();
-    } else {
-      // bins of 2^sh keys below the largest possible key, in descending order
-      const uint32_t kmax = max(hi, hfmax);
-      const int sh = max(0, 32 - __clz(kmax - tck) - kNBLog);
-      auto bin_of = [&](uint32_t key) { return (kmax - key) >> sh; };
-      each(false, [&](uint32_t key, uint32_t) { atomicAdd(&S.bins[bin_of(key)], 1u); });
-      lds_barrier();
+      break;
+    }
+    if (pass == 0) {
+      // counts to starts; the bins that hold the list end at nB
       constexpr int BPT = kNB / BS;  // bins per thread
       uint32_t h[BPT], s = 0u;
 #pragma unroll
@@ -811,61 +927,45 @@ __device__ __forceinline__ void merge_row(const KArgs& a, int row, MSmem& S, uin
       const uint32_t inc = wave_incl_scan(s);
       if (ln == 63) S.x32[3][wv] = inc;
       lds_barrier();
-      uint32_t run = inc - s, total = 0u;
-#pragma unroll
-      for (int w = 0; w < NW; ++w) {
-        const uint32_t x = S.x32[3][w];
-        if (w < wv) run += x;
-        total += x;
-      }
+      uint32_t run, total;
+      wave_prefix<NW>(S.x32[3], wv, run, total);
+      run += inc - s;
+      total = uniform(total);
       if (total < (uint32_t)want) {
         // at the lowest threshold there is the list is the whole row (few
         // tokens allowed by a grammar); otherwise elements may be missing
         if (tc == comp_of(kKeyFloor, kNone)) want = (int)total;
         else slow = true;
       }
-      uint32_t occ = 0u;
 #pragma unroll
       for (int q = 0; q < BPT; ++q) {
         S.bins[tid * BPT + q] = run;
         if (run < (uint32_t)want) {
-          occ = max(occ, h[q]);
+          if (h[q] > (uint32_t)kCrowd) S.bc[1] = 1u;
           if (run + h[q] >= (uint32_t)want) S.bc[0] = run + h[q];
         }
         run += h[q];
       }
-      occ = wave_max_u32(occ);
-      if (ln == 0 && occ != 0u) atomicMax(&S.bc[1], occ);
       lds_barrier();
-      nB = S.bc[0];
-      if (!slow && nB > (uint32_t)a.pcap) slow = true;  // ties beyond the staging area
-      if (!slow) {
-        crowded = S.bc[1] > (uint32_t)kCrowd;
-        // scatter into bin order: each bin's start becomes its end
-        each(true, [&](uint32_t key, uint32_t idx) {
-          const uint32_t bn = bin_of(key);
-          if (S.bins[bn] < nB) {
-            const uint32_t p = atomicAdd(&S.bins[bn], 1u);
-            if (p < nB) stage[p] = comp_of(key, idx);
+      nB = uniform(S.bc[0]);
+      if (nB > (uint32_t)a.pcap) slow = true;  // ties beyond the staging area
+    } else {
+      crowded = uniform(S.bc[1]) != 0u;
+      nT = want;
+      if (!crowded) {
+        for (uint32_t p = (uint32_t)tid; p < nB; p += (uint32_t)BS) {
+          const uint64_t e = stage[p];
+          const uint32_t bn = bin_of(e);
+          const uint32_t bs = bn != 0u ? S.bins[bn - 1u] : 0u, be = S.bins[bn];
+          uint32_t r = bs;
+          for (uint32_t j = bs; j < be; j += 4u) {
+            const uint64_t s0 = stage[j], s1 = stage[j + 1u], s2 = stage[j + 2u], s3 = stage[j + 3u];
+            r += (s0 > e ? 1u : 0u) + ((j + 1u < be && s1 > e) ? 1u : 0u) + ((j + 2u < be && s2 > e) ? 1u : 0u) +
+                 ((j + 3u < be && s3 > e) ? 1u : 0u);
           }
-        });
-        lds_barrier();
-        nT = want;
-        if (!crowded) {
-          for (uint32_t p = (uint32_t)tid; p < nB; p += (uint32_t)BS) {
-            const uint64_t e = stage[p];
-            const uint32_t bn = bin_of(comp_key(e));
-            const uint32_t bs = bn != 0u ? S.bins[bn - 1u] : 0u, be = S.bins[bn];
-            uint32_t r = bs;
-            for (uint32_t j = bs; j < be; j += 4u) {
-              const uint64_t s0 = stage[j], s1 = stage[j + 1u], s2 = stage[j + 2u], s3 = stage[j + 3u];
-              r += (s0 > e ? 1u : 0u) + ((j + 1u < be && s1 > e) ? 1u : 0u) + ((j + 2u < be && s2 > e) ? 1u : 0u) +
-                   ((j + 3u < be && s3 > e) ? 1u : 0u);
-            }
-            if (r < (uint32_t)want) sorted[r] = e;
-          }
-          lds_barrier();
+          if (r < (uint32_t)want) sorted[r] = e;
         }
+        lds_barrier();
       }
     }
   }
@@ -879,6 +979,7 @@ __device__ __forceinline__ void merge_row(const KArgs& a, int row, MSmem& S, uin
     c.mask = (mode & SS_GRAMMAR) ? a.bitmask + (size_t)row * (size_t)a.mask_ld : nullptr;
   };
   if (!empty && want > 0 && slow) {
+    const KArgs& a = late_args();
     flags |= SS_FLAG_FALLBACK;
     c = make_ctx<DT>(a, row);
     if (pst == 2) pmode = global_table<DT, BS>(a, c, S, row, pg);
@@ -897,10 +998,12 @@ __device__ __forceinline__ void merge_row(const KArgs& a, int row, MSmem& S, uin
   }
   const bool none = empty || nT == 0;
   if (none) flags = empty ? SS_FLAG_EMPTY : flags | SS_FLAG_EMPTY;
-  const uint64_t Mcomp = none ? 0ull : T[0];
+  const uint64_t Mcomp = none ? 0ull : uniform(T[0]);
   const int argmax = none ? -1 : (int)comp_idx(Mcomp);
 
   // 5. outputs
+  {
+  const KArgs& a = late_args();
   if constexpr (OP == OP_TOPK) {
     for (int r = tid; r < a.k_cap; r += BS) {
       const size_t o = (size_t)b * a.k_cap + r;
@@ -987,25 +1090,18 @@ __device__ __forceinline__ void merge_row(const KArgs& a, int row, MSmem& S, uin
     // ---- truncation and selection (Alg. 11 order) on T[0, nT): entry r =
     // 64 (E wave + j) + lane is held by one thread, E entries per thread
     const double M = (double)float_of_key(comp_key(Mcomp));
-    const float tauf = (mode & SS_TEMP) ? temp : 1.0f;
-    const double tau = (double)tauf;
-    const double itau = 1.0 / tau;
-    const float minp_f = (mode & SS_MINP) ? minp_v : 0.0f;
-    const float topp_f = (mode & SS_TOPP) ? topp_v : 1.0f;
-    const bool minp = minp_f > 0.0f;
-    const bool topp = topp_f < 1.0f;
-    const double lt = minp ? log((double)minp_f) : 0.0;
     const int E = (nT + BS - 1) / BS;
     const int r0 = 64 * E * wv + ln;
     auto yval = [&](uint64_t cm) { return (double)float_of_key(comp_key(cm)); };
     auto weight = [&](uint64_t cm) { return weight_fast(yval(cm), M, itau); };
     auto dropped = [&](uint64_t cm) {  // by min-p; never the first
       const double y = yval(cm);
-      const double l = (y == M) ? 0.0 : (y - M) / tau;
+      double l = y == M ? 0.0 : (y - M) * itau;
+      if (fabs(l - lt) < 1e-9 * fabs(lt)) l = (y - M) / tau;  // the product may round to the other side
       return cm != Mcomp && !(l >= lt);
     };
     // exclusive prefix sums of wt over the list; returns the total
-    uint64_t wt[EM], ex[EM];
+    uint64_t el[EM], wt[EM], ex[EM];
     auto scan_list = [&](uint64_t* scratch) -> uint64_t {
       uint64_t run = 0ull;
 #pragma unroll
@@ -1018,13 +1114,8 @@ __device__ __forceinline__ void merge_row(const KArgs& a, int row, MSmem& S, uin
       }
       if (ln == 0) scratch[wv] = run;
       lds_barrier();
-      uint64_t before = 0ull, total = 0ull;
-#pragma unroll
-      for (int w = 0; w < NW; ++w) {
-        const uint64_t x = scratch[w];
-        if (w < wv) before += x;
-        total += x;
-      }
+      uint64_t before, total;
+      wave_prefix<NW>(scratch, wv, before, total);
 #pragma unroll
       for (int j = 0; j < EM; ++j)
         if (j < E) ex[j] += before;
@@ -1034,10 +1125,11 @@ __device__ __forceinline__ void merge_row(const KArgs& a, int row, MSmem& S, uin
     for (int j = 0; j < EM; ++j) {
       if (j < E) {
         const int r = r0 + 64 * j;
-        wt[j] = r < nT ? (uint64_t)__double2ll_rn(weight(T[r]) * kFix) : 0ull;
+        el[j] = r < nT ? T[r] : 0ull;
+        wt[j] = r < nT ? (uint64_t)__double2ll_rn(weight(el[j]) * kFix) : 0ull;
       }
     }
-    const uint64_t Zk = scan_list(S.x64[1]);
+    const uint64_t Zk = uniform(scan_list(S.x64[1]));
     // Full-row truncation takes its boundary against the whole row's mass;
     // its result stands when fewer than k_max tokens are kept, else the bounded
     // one (mass of the list) is taken with KCAP.
@@ -1046,7 +1138,7 @@ __device__ __forceinline__ void merge_row(const KArgs& a, int row, MSmem& S, uin
       if (!slow) norm_ctx();
       zrow = kFix * wg_sum<BS>(row_norm_part<DT, BS>(a, c, S, row, pmode, pg, M, lp_tau(a, mode, b)), S.rd);
     }
-    const double Xp = (double)topp_f * (double)Zk, Xr = (double)topp_f * zrow;
+    const double Xp = (double)topp_v * (double)Zk, Xr = (double)topp_v * zrow;
 #pragma unroll
     for (int j = 0; j < EM; ++j) {
       if (j < E) {
@@ -1062,7 +1154,11 @@ __device__ __forceinline__ void merge_row(const KArgs& a, int row, MSmem& S, uin
             S.bc[7] = (uint32_t)r;
             S.bc64[2] = ex[j] + wt[j];
           }
-          if (minp && r > 0 && dropped(T[r]) && !dropped(T[r - 1])) {
+        }
+        if (minp) {  // the kept ones are a prefix: the first dropped one follows a kept one
+          const bool dr = r < nT && dropped(el[j]);
+          const uint64_t dm = __ballot(dr);
+          if (dm != 0ull && ln == (int)__builtin_ctzll(dm) && (ln > 0 || !dropped(T[r - 1]))) {
             S.bc[3] = (uint32_t)r;
             S.bc64[1] = ex[j];
           }
@@ -1070,8 +1166,8 @@ __device__ __forceinline__ void merge_row(const KArgs& a, int row, MSmem& S, uin
       }
     }
     lds_barrier();
-    const uint32_t np = S.bc[2], nm = S.bc[3];
-    const uint64_t zp = S.bc64[0], zm = S.bc64[1];
+    const uint32_t np = uniform(S.bc[2]), nm = uniform(S.bc[3]);
+    const uint64_t zp = uniform(S.bc64[0]), zm = uniform(S.bc64[1]);
     uint32_t n_s = (uint32_t)nT;
     uint64_t Zs = Zk;
     auto cut_at = [&](uint32_t last, uint64_t z) {  // the shorter of the top-p and min-p prefixes
@@ -1088,7 +1184,7 @@ __device__ __forceinline__ void merge_row(const KArgs& a, int row, MSmem& S, uin
     };
     cut_at(np, zp);
     if (OP == OP_SAMPLE_X && full_row) {
-      cut_at(S.bc[7], S.bc64[2]);
+      cut_at(uniform(S.bc[7]), uniform(S.bc64[2]));
       if (n_s < (uint32_t)a.k_cap) {
         flags &= ~SS_FLAG_KCAP;
       } else {
@@ -1097,7 +1193,6 @@ __device__ __forceinline__ void merge_row(const KArgs& a, int row, MSmem& S, uin
       }
     }
     const double Zsd = (double)Zs / kFix;
-    const double u0 = OP == OP_PROCESS ? 0.0 : uniform01(seed, (uint32_t)b, pos, 0);
     // calls f(composite) in the thread that holds the drawn entry: the first
     // kept one whose inclusive mass exceeds u0 * total (else the last one)
     auto draw = [&](double total, auto&& f) {
@@ -1107,7 +1202,7 @@ __device__ __forceinline__ void merge_row(const KArgs& a, int row, MSmem& S, uin
         if (j < E) {
           const int r = r0 + 64 * j;
           if (r < (int)n_s && ((double)(ex[j] + wt[j]) > X || r == (int)n_s - 1) && (r == 0 || (double)ex[j] <= X))
-            f(T[r]);
+            f(el[j]);
         }
       }
     };
@@ -1141,7 +1236,7 @@ __device__ __forceinline__ void merge_row(const KArgs& a, int row, MSmem& S, uin
           if (j < E) {
             const int r = r0 + 64 * j;
             if (r < (int)n_s) {
-              const uint64_t cm = T[r];
+              const uint64_t cm = el[j];
               const double y = yval(cm);
               const double sc = (y == M ? 0.0 : (y - M) / tau) - (double)grow[comp_idx(cm)];
               const uint64_t k2 = ((uint64_t)(~comp_idx(cm)) << 32) | comp_key(cm);
@@ -1185,7 +1280,7 @@ __device__ __forceinline__ void merge_row(const KArgs& a, int row, MSmem& S, uin
       for (int j = 0; j < EM; ++j) {
         if (j < E) {
           const int r = r0 + 64 * j;
-          if (r < (int)n_s && (int)comp_idx(T[r]) == dtok) S.bc64[3] = __builtin_bit_cast(uint64_t, weight(T[r]) / Zsd);
+          if (r < (int)n_s && (int)comp_idx(el[j]) == dtok) S.bc64[3] = __builtin_bit_cast(uint64_t, weight(el[j]) / Zsd);
         }
       }
       const float* qrow = a.draft_probs ? a.draft_probs + ((size_t)b * a.L + ell) * (size_t)a.ld_q : nullptr;
@@ -1277,22 +1372,23 @@ __device__ __forceinline__ void merge_row(const KArgs& a, int row, MSmem& S, uin
       draw(total, [&](uint64_t cm) { publish(0, (int)comp_idx(cm)); });
     }
   }
+  }
 }
 
 // Merge kernel: one workgroup per row (the launch boundary orders the
 // streaming kernel's records and candidates before it).
-template <int DT, int OP>
-__global__ __launch_bounds__((merge_threads<DT, OP>())) void ss_merge_kernel(KArgs a) {
+template <int DT, int OP, int BS>
+__global__ __launch_bounds__(BS) void ss_merge_kernel(KArgs a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   MSmem& S = *reinterpret_cast<MSmem*>(smem_raw);
   uint64_t* stage = reinterpret_cast<uint64_t*>(smem_raw + kSmemFixed);
   // The streaming kernel placed row r's units on XCD floor(8 r / rows) when
   // its grid splits evenly over the 8 XCDs; the same remap here runs the
   // row's merge on that XCD as well.
-  int row = blockIdx.x;
+  int row = blockIdx.x + warm_args();
   const int nunits = a.rows * a.U;
   if ((a.rows & 7) == 0 && (nunits & 31) == 0) row = (row & 7) * (a.rows >> 3) + (row >> 3);
-  merge_row<DT, OP>(a, row, S, stage);
+  merge_row<DT, OP, BS>(a, row, S, stage);
 }
 
 }  // namespace ss
