@@ -99,8 +99,6 @@ static void fill_params(KArgs& k, const ss_params* p) {
   k.feat = feature_mask(p);
 }
 
-static int esize(int dtype) { return dtype == SS_BF16 ? 2 : 4; }
-
 // The merge instantiation of a call: sampling with full-row truncation or the
 // Gumbel-max draw has its own, so plain sampling carries neither extension.
 static int merge_op(const KArgs& k) { return (k.op == OP_SAMPLE && (k.full || k.gum)) ? (int)OP_SAMPLE_X : k.op; }
@@ -196,7 +194,8 @@ static ss_status launch(KArgs& k, int dtype, const Layout& lay, void* ws, hipStr
     smem_configured[di][mop] = true;
   }
   const int nunits = lay.rows * lay.U;
-  const dim3 grid((unsigned)(k.patch_wgs + (nunits + kSWaves - 1) / kSWaves)), sblock(kSBlock),
+  k.unit_wgs = (nunits + kSWaves - 1) / kSWaves;
+  const dim3 grid((unsigned)(k.patch_wgs + k.unit_wgs)), sblock(kSBlock),
       block(kBlock);
   const int psmem = k.patch_wgs ? (int)sizeof(PSmem) : kSWaves * (int)sizeof(WStage);
   static_assert(sizeof(PSmem) >= kSWaves * sizeof(WStage), "the emission strips share the patch tables' space");
@@ -265,7 +264,6 @@ ss_status ss_topk(const void* x, int dtype, int B, int V, int64_t ld, const int3
   a.L = 0;
   a.k_cap = k_max;
   a.k_out = 0;
-  a.vec_ok = aligned16(x) && ((ld * esize(dtype)) % 16 == 0);
   a.feat = SS_TOPK;
   a.top_k = k;
   a.out_val = out_val;
@@ -291,7 +289,6 @@ ss_status ss_logprobs(const void* logits, int dtype, int64_t ld, const ss_params
   a.V = V;
   a.L = 0;
   a.k_cap = n_lp;
-  a.vec_ok = aligned16(logits) && ((ld * esize(dtype)) % 16 == 0);
   fill_params(a, p);
   a.out_idx = out_idx;
   a.out_val = out_lp;
@@ -321,7 +318,6 @@ static ss_status sample_any(const void* logits, int dtype, int64_t ld, const ss_
   a.L = 0;
   a.k_cap = k_max;
   a.k_out = k_out;
-  a.vec_ok = aligned16(logits) && ((ld * esize(dtype)) % 16 == 0);
   fill_params(a, p);
   a.gum = noise;
   a.ld_g = noise ? ld_noise : 0;
@@ -382,7 +378,6 @@ static ss_status verify_any(const void* target_logits, int dtype, int64_t ld_row
   a.L = L;
   a.k_cap = k_max;
   a.k_out = 0;
-  a.vec_ok = aligned16(target_logits) && ((ld_row * esize(dtype)) % 16 == 0);
   fill_params(a, p);
   a.draft_probs = kq == 0 ? draft_probs : nullptr;
   a.ld_q = kq == 0 ? ld_q : 0;
@@ -442,7 +437,6 @@ ss_status ss_process_logits(const void* logits, int dtype, int64_t ld, const ss_
   a.L = 0;
   a.k_cap = k_max;
   a.k_out = 0;
-  a.vec_ok = aligned16(logits) && ((ld * esize(dtype)) % 16 == 0);
   fill_params(a, p);
   a.out_logits = out_logits;
   a.out_probs = out_probs;

@@ -78,7 +78,7 @@ struct RowResult {
 struct KArgs {
   const void* x;
   int64_t ld;
-  int op, B, rows, V, U, L, k_cap, cap, pcap, k_out, vec_ok;  // cap: candidate region of a unit in 16-byte words
+  int op, B, rows, V, U, L, k_cap, cap, pcap, k_out;  // cap: candidate region of a unit in 16-byte words
   uint32_t feat;
   int have;  // kHave* bits; a NULL parameter array points at the workspace instead, so it can be read (and ignored)
   const uint32_t* mode;
@@ -131,6 +131,7 @@ struct KArgs {
   int32_t* pstat;      // per row: 0 no lists, 1 patch table in ptab, 2 more ids than the table holds
   uint32_t* ptab;      // per row 2 kH words: slot ids (-1 empty), then final keys
   int patch_wgs;       // patch-table workgroups at the front of the streaming grid (0: the call has no lists)
+  int unit_wgs;        // workgroups of the streaming grid behind them
   int tpu, tpu_inv;    // merge: threads per unit of the candidate loads, and ceil(2^20 / tpu)
   int nq;              // merge: 16-byte candidate loads a thread issues before anything is known
   double* usum;        // log-probabilities: per unit, sum of exp((x - unit max) / tau) over its valid logits
@@ -208,6 +209,13 @@ __device__ __forceinline__ uint32_t fold_nan2(uint32_t d) {
   lo = lo > 0xFF80u ? 0u : lo;
   hi = hi > 0xFF80u ? 0u : hi;
   return lo | (hi << 16);
+}
+
+// 16 bytes at any alignment (one load: global accesses need none on this target)
+__device__ __forceinline__ uint4 load16(const unsigned char* p) {
+  uint4 v;
+  __builtin_memcpy(&v, p, 16);
+  return v;
 }
 
 // float32 bit pattern of element i of a row (scalar access, any alignment)
@@ -595,41 +603,47 @@ __device__ __forceinline__ void scan_unit(const KArgs& a, int gu, WStage& W) {
   const int64_t srow = a.op == OP_VERIFY ? source_row(a, row) : row;
   const int n = srow < 0 ? 0 : min(kUE, a.V - lo);  // a row outside the tree reads nothing
   const int b = a.op == OP_VERIFY ? row / (a.L + 1) : row;
-  // the request's parameters: read together, before they are known to be needed
+  const unsigned char* xrow =
+      reinterpret_cast<const unsigned char*>(a.x) + (size_t)(srow < 0 ? 0 : srow) * (size_t)a.ld * ES;
+
+  // 1. loads: the unit's chunks (16 bytes at any element alignment: rows of odd
+  // length need no path of their own), then the request's parameters, read
+  // together before they are known to be needed, then the grammar words
+  uint4 r[NLD];
+  if (n == kUE) {
+    const unsigned char* src = xrow + (size_t)lo * ES;
+#pragma unroll
+    for (int i = 0; i < NLD; ++i) r[i] = load16(src + (size_t)(i * 64 + ln) * 16);
+  } else {
+#pragma unroll
+    for (int i = 0; i < NLD; ++i) {
+      const int l0 = (i * 64 + ln) * VW;
+      r[i] = make_uint4(0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu);  // negative NaN: invalid
+      if (l0 + VW <= n) {
+        r[i] = load16(xrow + (size_t)(lo + l0) * ES);
+      } else if (l0 < n) {  // the row's last chunk
+        uint32_t w[4] = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};
+#pragma unroll
+        for (int e = 0; e < VW; ++e) {
+          if (l0 + e < n) {
+            if constexpr (DT == SS_F32) {
+              w[e] = reinterpret_cast<const uint32_t*>(xrow)[lo + l0 + e];
+            } else {
+              const uint32_t h = reinterpret_cast<const uint16_t*>(xrow)[lo + l0 + e];
+              const int q = e >> 1;
+              w[q] = (e & 1) ? ((w[q] & 0x0000FFFFu) | (h << 16)) : ((w[q] & 0xFFFF0000u) | h);
+            }
+          }
+        }
+        r[i] = make_uint4(w[0], w[1], w[2], w[3]);
+      }
+    }
+  }
   const uint32_t mode_v = a.mode[b];
   const float temp = a.temperature[b];
   const int topk = a.top_k[b];
   const uint32_t mode = (a.op == OP_TOPK ? SS_TOPK : mode_v) & a.feat;
   const uint32_t* mask = (mode & SS_GRAMMAR) ? a.bitmask + (size_t)row * (size_t)a.mask_ld : nullptr;
-  const unsigned char* xrow =
-      reinterpret_cast<const unsigned char*>(a.x) + (size_t)(srow < 0 ? 0 : srow) * (size_t)a.ld * ES;
-
-  // 1. loads: the unit's chunks, then the grammar words that cover them
-  uint4 r[NLD];
-  if (a.vec_ok && n == kUE) {
-    const uint4* src = reinterpret_cast<const uint4*>(xrow + (size_t)lo * ES);
-#pragma unroll
-    for (int i = 0; i < NLD; ++i) r[i] = src[i * 64 + ln];
-  } else {
-#pragma unroll
-    for (int i = 0; i < NLD; ++i) {
-      const int l0 = (i * 64 + ln) * VW;
-      uint32_t w[4] = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};  // negative NaN: invalid
-#pragma unroll
-      for (int e = 0; e < VW; ++e) {
-        if (l0 + e < n) {
-          if constexpr (DT == SS_F32) {
-            w[e] = reinterpret_cast<const uint32_t*>(xrow)[lo + l0 + e];
-          } else {
-            const uint32_t h = reinterpret_cast<const uint16_t*>(xrow)[lo + l0 + e];
-            const int q = e >> 1;
-            w[q] = (e & 1) ? ((w[q] & 0x0000FFFFu) | (h << 16)) : ((w[q] & 0xFFFF0000u) | h);
-          }
-        }
-      }
-      r[i] = make_uint4(w[0], w[1], w[2], w[3]);
-    }
-  }
   uint32_t mw[NLD];
   if (mask) {
     const int W = (a.V + 31) >> 5;
@@ -923,6 +937,7 @@ __device__ __forceinline__ void patch_row(const KArgs& a, int row, PSmem& P) {
   auto ins = [&](int id, uint32_t addc, bool bias, float bval) {
     if (id < 0 || id >= a.V) return;
     uint32_t sl = hslot(id);
+#pragma unroll 1
     for (int p = 0; p < kProbe; ++p) {
       const int old = atomicCAS(&P.hk[sl], -1, id);
       if (old == -1 || old == id) {
@@ -1008,7 +1023,7 @@ __global__ __launch_bounds__(kSBlock) void ss_stream_kernel(KArgs a) {
     return;
   }
   bid -= a.patch_wgs;
-  const int nb = gridDim.x - a.patch_wgs;
+  const int nb = a.unit_wgs;
   if (bid < (nb & ~7)) bid = (bid & 7) * (nb >> 3) + (bid >> 3);
   const int gu = __builtin_amdgcn_readfirstlane(bid * kSWaves + wave());
   if (gu < a.rows * a.U) scan_unit<DT, LP>(a, gu, reinterpret_cast<WStage*>(psmem)[wave()]);

@@ -328,8 +328,8 @@ __device__ __forceinline__ int slow_select(const KArgs& a, const Ctx& c, MSmem& 
 #pragma unroll 1
           for (int l0 = (tid & (SH - 1)) * VW; l0 < kUE; l0 += SH * VW) {
             uint32_t w4[4] = {0u, 0u, 0u, 0u};
-            if (a.vec_ok && lo + kUE <= a.V) {
-              const uint4 r = *reinterpret_cast<const uint4*>(c.xrow + (size_t)(lo + l0) * DTT<DT>::ES);
+            if (lo + l0 + VW <= a.V) {
+              const uint4 r = load16(c.xrow + (size_t)(lo + l0) * DTT<DT>::ES);
               w4[0] = r.x;
               w4[1] = r.y;
               w4[2] = r.z;
