@@ -519,10 +519,16 @@ __device__ __forceinline__ float lp_tau(const KArgs& a, uint32_t mode, int b) {
   if ((mode & SS_TEMP) && !(mode & SS_GREEDY) && a.temperature[b] > 0.0f) return a.temperature[b];
   return 1.0f;
 }
-// One term of a unit's normaliser sum, exp((v - mu) / tau) in float32 from
-// the float32 reciprocal itau; the merge recomputes it bit for bit for the
-// raw copies of patched ids.
-__device__ __forceinline__ float lp_term(float v, float mu, float itau) { return expf((v - mu) * itau); }
+// One term of a unit's normaliser sum, exp((v - mu) / tau) as 2^((v - mu) c)
+// in float32 with c = log2(e) / tau rounded once: one rounding of the constant,
+// one of the product and the hardware's 2^x (1 ulp), the same number of
+// roundings as expf of (v - mu) (1 / tau) at a fifth of its instructions.  The
+// merge recomputes a term bit for bit for the raw copies of patched ids.
+// Terms below 2^-126 of the unit's largest count as zero; so do NaNs.
+__device__ __forceinline__ float lp_scale(float tau) { return (float)(1.4426950408889634 / (double)tau); }
+__device__ __forceinline__ float lp_term(float v, float mu, float c) {
+  return fmaxf(__builtin_amdgcn_exp2f((v - mu) * c), 0.0f);
+}
 // Rows whose units add their share of the full-row normaliser: requests with
 // the log-probability bit, or, in full-row sampling, stochastic requests
 // without a top-k cut.
@@ -671,26 +677,28 @@ __device__ __forceinline__ void scan_unit(const KArgs& a, int gu, WStage& W) {
   const uint32_t cap = (uint32_t)a.cap;
   uint32_t t, wm, total, count, cut = 0xFFFFFFFFu;
   if constexpr (DT == SS_BF16) {
-    uint32_t kd[16];
+    uint32_t rd[16], kd[16];
 #pragma unroll
     for (int i = 0; i < NLD; ++i) {
-      kd[4 * i + 0] = key2_bf16(r[i].x);
-      kd[4 * i + 1] = key2_bf16(r[i].y);
-      kd[4 * i + 2] = key2_bf16(r[i].z);
-      kd[4 * i + 3] = key2_bf16(r[i].w);
+      rd[4 * i + 0] = r[i].x;
+      rd[4 * i + 1] = r[i].y;
+      rd[4 * i + 2] = r[i].z;
+      rd[4 * i + 3] = r[i].w;
     }
-    if (mask) {
+    if (mask) {  // masked elements become -inf
 #pragma unroll
       for (int i = 0; i < NLD; ++i) {
         const uint32_t bits = mw[i] >> (((i * 64 + ln) * 8) & 31);
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
-          const uint32_t b2 = bits >> (2 * w);
-          const uint32_t m = ((b2 & 1u) ? 0x0000FFFFu : 0u) | ((b2 & 2u) ? 0xFFFF0000u : 0u);
-          kd[4 * i + w] &= m;
+          const uint32_t m = ((uint32_t)((int32_t)(bits << (31 - 2 * w)) >> 31) & 0x0000FFFFu) |
+                             ((uint32_t)((int32_t)(bits << (30 - 2 * w)) >> 31) & 0xFFFF0000u);
+          rd[4 * i + w] = (rd[4 * i + w] & m) | (~m & 0xFF80FF80u);
         }
       }
     }
+#pragma unroll
+    for (int j = 0; j < 16; ++j) kd[j] = key2_bf16(rd[j]);
     uint32_t lm = kd[0];
 #pragma unroll
     for (int j = 1; j < 16; ++j) lm = pkmax16(lm, kd[j]);
@@ -707,15 +715,14 @@ __device__ __forceinline__ void scan_unit(const KArgs& a, int gu, WStage& W) {
       if (usum_row(a, mode, b)) {
         double sl = 0.0;
         if (wm16 >= 0x0081u) {
-          const float mu = float_of_key(wm16 << 16), itau = 1.0f / lp_tau(a, mode, b);
+          const float mu = float_of_key(wm16 << 16), c = lp_scale(lp_tau(a, mode, b));
+          double s1 = 0.0;  // two chains of additions
 #pragma unroll
-          for (int j = 0; j < 16; ++j) {
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-              const uint32_t k16 = (kd[j] >> (16 * h)) & 0xFFFFu;
-              if (k16 >= 0x0081u) sl += (double)lp_term(float_of_key(k16 << 16), mu, itau);
-            }
+          for (int j = 0; j < 16; ++j) {  // -inf terms are zero
+            sl += (double)lp_term(__uint_as_float(rd[j] << 16), mu, c);
+            s1 += (double)lp_term(__uint_as_float(rd[j] & 0xFFFF0000u), mu, c);
           }
+          sl += s1;
         }
         sl = wave_sum(sl);
         if (ln == 0) a.usum[gu] = sl;
@@ -794,10 +801,14 @@ __device__ __forceinline__ void scan_unit(const KArgs& a, int gu, WStage& W) {
       if (usum_row(a, mode, b)) {
         double sl = 0.0;
         if (wm >= kKeyFloor) {
-          const float mu = float_of_key(wm), itau = 1.0f / lp_tau(a, mode, b);
+          const float mu = float_of_key(wm), c = lp_scale(lp_tau(a, mode, b));
+          double s1 = 0.0;  // two chains of additions
 #pragma unroll
-          for (int j = 0; j < 32; ++j)
-            if (kk[j] >= kKeyFloor) sl += (double)lp_term(float_of_key(kk[j]), mu, itau);
+          for (int j = 0; j < 32; j += 2) {  // invalid keys are those of -inf and below
+            sl += (double)lp_term(kk[j] >= kKeyFloor ? float_of_key(kk[j]) : -__builtin_inff(), mu, c);
+            s1 += (double)lp_term(kk[j + 1] >= kKeyFloor ? float_of_key(kk[j + 1]) : -__builtin_inff(), mu, c);
+          }
+          sl += s1;
         }
         sl = wave_sum(sl);
         if (ln == 0) a.usum[gu] = sl;
@@ -978,6 +989,12 @@ __device__ __forceinline__ void patch_row(const KArgs& a, int row, PSmem& P) {
     mw[m] = c.mask ? ((ld >> 5) < Wm ? c.mask[ld >> 5] : 0u) : 0xFFFFFFFFu;
   }
   uint32_t* dst = a.ptab + (size_t)row * 2 * kH;
+  if (a.usum) {  // raw keys, for the row's normaliser (the global table's space: unused beside this table)
+    uint32_t* raw = a.gfin + (size_t)row * kGH;
+#pragma unroll
+    for (int m = 0; m < kSl; ++m)
+      raw[tid + m * kSBlock] = (id[m] >= 0 && ((mw[m] >> (id[m] & 31)) & 1u)) ? fold_nan(key_raw(bits[m])) : 0u;
+  }
 #pragma unroll
   for (int m = 0; m < kSl; ++m) {
     const int sl = tid + m * kSBlock;

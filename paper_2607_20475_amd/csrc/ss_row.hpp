@@ -511,47 +511,22 @@ __device__ __forceinline__ int slow_select(const KArgs& a, const Ctx& c, MSmem& 
 }
 
 // This thread's share of the full-row normaliser sum_j exp((y_j - M) / tau)
-// over the row's valid processed logits: the units' sums (taken by the
-// streaming kernel relative to each unit's raw maximum) rescaled to M, each
-// patched id's raw term (recomputed bit for bit) replaced by its final
-// value's; rows whose lists exceed the LDS table recompute every element.
-// The caller sums the shares over the workgroup.
+// over the row's valid processed logits, for rows whose lists exceed the LDS
+// table: every element's processed value.
 template <int DT, int BS>
-__device__ __forceinline__ double row_norm_part(const KArgs& a, const Ctx& c, const MSmem& S, int row, int pmode,
-                                                const PatchG& pg, double M, float tauf) {
-  const int U = a.U, tid = threadIdx.x;
-  const float itau = 1.0f / tauf;
-  const double tau = (double)tauf;
+__device__ __forceinline__ double row_norm_all(const KArgs& a, const Ctx& c, const MSmem& S, int pmode, const PatchG& pg,
+                                               double M, double tau) {
   const int Wm = (a.V + 31) >> 5;
-  auto allowed = [&](int id) { return !c.mask || ((((id >> 5) < Wm ? c.mask[id >> 5] : 0u) >> (id & 31)) & 1u); };
   double z = 0.0;
-  if (pmode <= 1) {
-    for (int u = tid; u < U; u += BS) {
-      const uint32_t wmu = a.rec[(size_t)row * U + u].z;
-      if (wmu >= kKeyFloor) z += exp(((double)float_of_key(wmu) - M) / tau) * a.usum[(size_t)row * U + u];
-    }
-    for (int sl = tid; pmode == 1 && sl < kH; sl += BS) {
-      const int id = S.hk[sl];
-      if (id < 0) continue;
-      uint32_t kr = fold_nan(key_raw(load_elem_bits<DT>(c.xrow, id)));  // as the unit sum counted it
-      if (!allowed(id)) kr = 0u;
-      if (kr >= kKeyFloor) {
-        const float mu = float_of_key(a.rec[(size_t)row * U + id / kUE].z);
-        z -= exp(((double)mu - M) / tau) * (double)lp_term(float_of_key(kr), mu, itau);
-      }
-      if (S.hf[sl] >= kKeyFloor) z += exp(((double)float_of_key(S.hf[sl]) - M) / tau);
-    }
-  } else {  // lists beyond the LDS table: every element's processed value
-    for (int i = tid; i < a.V; i += BS) {
-      uint32_t k = fold_nan(key_raw(load_elem_bits<DT>(c.xrow, i)));
-      if (!allowed(i)) k = 0u;
-      if (is_patched<DT>(c, S, pmode, pg, i)) k = pmode == 2 ? pg.fin[gfind(pg, i)] : lin_final<DT>(a, c, i);
-      if (k >= kKeyFloor) z += exp(((double)float_of_key(k) - M) / tau);
-    }
+#pragma unroll 1
+  for (int i = threadIdx.x; i < a.V; i += BS) {
+    uint32_t k = fold_nan(key_raw(load_elem_bits<DT>(c.xrow, i)));
+    if (c.mask && !((((i >> 5) < Wm ? c.mask[i >> 5] : 0u) >> (i & 31)) & 1u)) k = 0u;
+    if (is_patched<DT>(c, S, pmode, pg, i)) k = pmode == 2 ? pg.fin[gfind(pg, i)] : lin_final<DT>(a, c, i);
+    if (k >= kKeyFloor) z += exp(((double)float_of_key(k) - M) / tau);
   }
   return z;
 }
-
 
 // Sums of the NW wave totals in scratch: of those before this wave, and of all
 // (one read and a few DPP steps per lane instead of a loop over the waves).
@@ -631,6 +606,18 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
       tfin4[m] = tsrc[kH / 4 + w];
     }
     pst = a.pstat[row];
+  }
+  // the units' normaliser sums and the listed ids' raw keys (log-probabilities, full-row truncation)
+  constexpr bool NORM = OP == OP_LOGPROBS || OP == OP_SAMPLE_X;
+  double us = 0.0;
+  uint4 traw4[KT];
+  if constexpr (NORM) {
+    if (a.usum) us = a.usum[gu];
+    if (tables) {
+#pragma unroll
+      for (int m = 0; m < KT; ++m)
+        traw4[m] = reinterpret_cast<const uint4*>(a.gfin + (size_t)row * kGH)[min(tid + m * BS, kH / 4 - 1)];
+    }
   }
   uint32_t mode = SS_TOPK;
   float temp = 1.0f, topp_v = 1.0f, minp_v = 0.0f;
@@ -974,10 +961,6 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
   int pmode = pst == 1 ? 1 : 0;
   PatchG pg = {};
   Ctx c = {};
-  auto norm_ctx = [&] {  // what row_norm_part reads beside the patch table
-    c.xrow = reinterpret_cast<const unsigned char*>(a.x) + (size_t)row * (size_t)a.ld * DTT<DT>::ES;
-    c.mask = (mode & SS_GRAMMAR) ? a.bitmask + (size_t)row * (size_t)a.mask_ld : nullptr;
-  };
   if (!empty && want > 0 && slow) {
     const KArgs& a = late_args();
     flags |= SS_FLAG_FALLBACK;
@@ -1001,6 +984,46 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
   const uint64_t Mcomp = none ? 0ull : uniform(T[0]);
   const int argmax = none ? -1 : (int)comp_idx(Mcomp);
 
+  // The row's normaliser relative to M: the units' sums (taken relative to each
+  // unit's raw maximum) rescaled, each patched id's raw term replaced by its
+  // final value's.  The units' factors go through the bins' memory.
+  auto row_norm = [&](double M, float tauf) -> double {
+    const double tau2 = (double)tauf;
+    double z = 0.0;
+    if (pmode <= 1) {
+      const float c2 = lp_scale(tauf);
+      double* uf = reinterpret_cast<double*>(S.bins);
+      float* um = reinterpret_cast<float*>(S.bins + 2 * kMaxU);
+      static_assert(3 * kMaxU <= kNB, "unit factors and maxima over the bins");
+      if (act && sub == 0) {
+        const float mu = float_of_key(r4.z);
+        const double f = r4.z >= kKeyFloor ? exp(((double)mu - M) / tau2) : 0.0;
+        uf[u] = f;
+        um[u] = mu;
+        if (r4.z >= kKeyFloor) z = f * us;
+      }
+      lds_barrier();
+      if (pmode == 1) {
+#pragma unroll
+        for (int m = 0; m < KT; ++m) {
+          const int ids[4] = {(int)tid4[m].x, (int)tid4[m].y, (int)tid4[m].z, (int)tid4[m].w};
+          const uint32_t fk[4] = {tfin4[m].x, tfin4[m].y, tfin4[m].z, tfin4[m].w};
+          const uint32_t rk[4] = {traw4[m].x, traw4[m].y, traw4[m].z, traw4[m].w};
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            if (ids[q] < 0) continue;
+            if (rk[q] >= kKeyFloor)
+              z -= uf[ids[q] / kUE] * (double)lp_term(float_of_key(rk[q]), um[ids[q] / kUE], c2);
+            if (fk[q] >= kKeyFloor) z += exp(((double)float_of_key(fk[q]) - M) / tau2);
+          }
+        }
+      }
+    } else {
+      z = row_norm_all<DT, BS>(a, c, S, pmode, pg, M, tau2);
+    }
+    return wg_sum<BS>(z, S.rd);
+  };
+
   // 5. outputs
   {
   const KArgs& a = late_args();
@@ -1017,11 +1040,7 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
     const float tauf = lp_tau(a, mode, b);
     const double tau = (double)tauf;
     const double M = none ? 0.0 : (double)float_of_key(comp_key(Mcomp));
-    double lz = 0.0;
-    if (!none) {
-      if (!slow) norm_ctx();
-      lz = log(wg_sum<BS>(row_norm_part<DT, BS>(a, c, S, row, pmode, pg, M, tauf), S.rd));
-    }
+    const double lz = none ? 0.0 : log(row_norm(M, tauf));
     for (int r = tid; r < a.k_cap; r += BS) {
       const size_t o = (size_t)b * a.k_cap + r;
       const uint64_t cm = r < nT ? T[r] : 0ull;
@@ -1134,10 +1153,7 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
     // its result stands when fewer than k_max tokens are kept, else the bounded
     // one (mass of the list) is taken with KCAP.
     double zrow = 0.0;
-    if (OP == OP_SAMPLE_X && full_row) {
-      if (!slow) norm_ctx();
-      zrow = kFix * wg_sum<BS>(row_norm_part<DT, BS>(a, c, S, row, pmode, pg, M, lp_tau(a, mode, b)), S.rd);
-    }
+    if (OP == OP_SAMPLE_X && full_row) zrow = kFix * row_norm(M, (float)tau);
     const double Xp = (double)topp_v * (double)Zk, Xr = (double)topp_v * zrow;
 #pragma unroll
     for (int j = 0; j < EM; ++j) {
