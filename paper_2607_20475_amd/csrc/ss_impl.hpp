@@ -1046,76 +1046,120 @@ __global__ __launch_bounds__(kSBlock) void ss_stream_kernel(KArgs a) {
   if (gu < a.rows * a.U) scan_unit<DT, LP>(a, gu, reinterpret_cast<WStage*>(psmem)[wave()]);
 }
 
-// Verification assembly: per request, the accepted drafts, then the first
-
-
 // ---------------------------------------------------------------------------
 // Materialising pass of ss_process_logits: processed logits and final
 // probabilities for every element, from the per-row summary; patched ids take
-// their final values from the merge's list.
+// their final values from the row's patch table (or the merge's list).
+// Bound by memory (bf16: 2 bytes read and 8 written per element), so a thread
+// takes four consecutive elements: one load, one 16-byte store per output at any
+// row alignment.  The tile's patched ids are found by a bit each.  Element by
+// element it took 17.5 us at B=32 V=2^17 bf16.
 // ---------------------------------------------------------------------------
 template <int DT>
 __global__ __launch_bounds__(kBlock) void ss_materialize_kernel(KArgs a) {
-  constexpr int TILE = 4096;
+  constexpr int TILE = 4096, VE = 4, IT = TILE / (VE * kBlock);
   const int tid = threadIdx.x;
   const int T = (a.V + TILE - 1) / TILE;
-  const int row = blockIdx.x / T;
-  const int tile = blockIdx.x - row * T;
+  const int bid = blockIdx.x + warm_args();
+  const int row = bid / T;
+  const int tile = bid - row * T;
   const int lo = tile * TILE;
   const int hi = min(a.V, lo + TILE);
-  const int b = row;
-  const uint32_t mode = a.mode[b] & a.feat;
-  const uint32_t* mask = (mode & SS_GRAMMAR) ? a.bitmask + (size_t)row * (size_t)a.mask_ld : nullptr;
   const unsigned char* xrow = reinterpret_cast<const unsigned char*>(a.x) + (size_t)row * (size_t)a.ld * DTT<DT>::ES;
+  // raw bits of this thread's elements
+  uint32_t x[IT][VE];
+#pragma unroll
+  for (int t = 0; t < IT; ++t) {
+    const int i0 = lo + (t * kBlock + tid) * VE;
+    if (i0 + VE <= hi) {
+      if constexpr (DT == SS_F32) {
+        const uint4 v = load16(xrow + (size_t)i0 * 4);
+        x[t][0] = v.x, x[t][1] = v.y, x[t][2] = v.z, x[t][3] = v.w;
+      } else {
+        uint2 v;
+        __builtin_memcpy(&v, xrow + (size_t)i0 * 2, 8);
+        x[t][0] = v.x << 16, x[t][1] = v.x & 0xFFFF0000u, x[t][2] = v.y << 16, x[t][3] = v.y & 0xFFFF0000u;
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < VE; ++e) x[t][e] = i0 + e < hi ? load_elem_bits<DT>(xrow, i0 + e) : 0u;
+    }
+  }
+  const uint32_t mode = a.mode[row] & a.feat;
   const RowSummary s = a.summ[row];
+  const uint32_t np = a.npatched[row];
+  const uint32_t* mask = (mode & SS_GRAMMAR) ? a.bitmask + (size_t)row * (size_t)a.mask_ld : nullptr;
   const double sitau = 1.0 / (double)s.tau;
-  const size_t ob = (size_t)row * (size_t)a.V;
   const int Wm = (a.V + 31) >> 5;
-  auto emit = [&](uint32_t k, uint32_t i) {
-    if (a.out_logits) a.out_logits[ob + i] = k >= kKeyFloor ? float_of_key(k) : -__builtin_inff();
-    if (a.out_probs) {
+  // final keys of this tile's patched ids, and a bit for each
+  __shared__ uint32_t pv[TILE];
+  __shared__ uint32_t pbit[TILE / 32];
+  if (tid < TILE / 32) pbit[tid] = 0u;
+  __syncthreads();
+  auto put = [&](uint32_t id, uint32_t key) {
+    pv[id - lo] = key;
+    atomicOr(&pbit[(id - lo) >> 5], 1u << (id & 31));
+  };
+  if (np == kTable) {
+    const uint4* pt = reinterpret_cast<const uint4*>(a.ptab + (size_t)row * 2 * kH);
+    for (int w = tid; w < kH / 4; w += kBlock) {
+      const uint4 q = pt[w];
+      const int ids[4] = {(int)q.x, (int)q.y, (int)q.z, (int)q.w};  // -1: empty slot
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (ids[e] >= lo && ids[e] < hi) put((uint32_t)ids[e], reinterpret_cast<const uint32_t*>(pt)[kH + 4 * w + e]);
+    }
+  } else if (np != kLinear) {
+    const uint2* pl = a.patched + (size_t)row * kGH;
+    for (uint32_t j = tid; j < np; j += kBlock) {
+      const uint2 e = pl[j];
+      if ((int)e.x >= lo && (int)e.x < hi) put(e.x, e.y);
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < IT; ++t) {
+    const int l = (t * kBlock + tid) * VE;
+    const int i0 = lo + l;
+    if (i0 >= hi) break;
+    const uint32_t mw = mask ? mask[min(i0 >> 5, Wm - 1)] >> (i0 & 31) : 0xFu;
+    const uint32_t pb = pbit[l >> 5] >> (l & 31);
+    float yo[VE], po[VE];
+#pragma unroll
+    for (int e = 0; e < VE; ++e) {
+      const uint32_t i = (uint32_t)(i0 + e);
+      uint32_t k = fold_nan(key_raw(x[t][e]));
+      if (!((mw >> e) & 1u)) k = 0u;
+      if ((pb >> e) & 1u) k = pv[l + e];
+      if (np == kLinear && (int)i < hi) {  // very long lists: look every id up
+        const Ctx c = make_ctx<DT>(a, row);
+        int cn;
+        bool hb;
+        float bs;
+        if (lin_info(c, (int)i, &cn, &hb, &bs) && k != 0u) k = lin_final<DT>(a, c, (int)i);
+      }
+      yo[e] = k >= kKeyFloor ? float_of_key(k) : -__builtin_inff();
       float p = 0.0f;
       if (s.kind == KIND_GREEDY) {
         p = (int)i == s.argmax ? 1.0f : 0.0f;
       } else if (s.kind == KIND_DIST && k >= kKeyFloor && comp_of(k, i) >= s.thr) {
         p = (float)(weight_fast((double)float_of_key(k), (double)s.M, sitau) / s.Z);
       }
-      a.out_probs[ob + i] = p;
+      po[e] = p;
     }
-  };
-  // final keys of the patched ids of this tile, staged in LDS (kNone elsewhere)
-  constexpr uint32_t kNone = 0xFFFFFFFFu;
-  __shared__ uint32_t pv[TILE];
-  for (int l = tid; l < TILE; l += kBlock) pv[l] = kNone;
-  __syncthreads();
-  const uint32_t np = a.npatched ? a.npatched[row] : 0u;
-  const uint2* pl = a.patched + (size_t)row * kGH;
-  if (np == kTable) {
-    const uint32_t* pt = a.ptab + (size_t)row * 2 * kH;
-    for (int sl = tid; sl < kH; sl += kBlock) {
-      const int id = (int)pt[sl];  // -1: empty slot
-      if (id >= lo && id < hi) pv[id - lo] = pt[kH + sl];
+    const size_t o = (size_t)row * (size_t)a.V + i0;
+    if (i0 + VE <= hi) {
+      if (a.out_logits) __builtin_memcpy(a.out_logits + o, yo, 16);
+      if (a.out_probs) __builtin_memcpy(a.out_probs + o, po, 16);
+    } else {
+#pragma unroll
+      for (int e = 0; e < VE; ++e) {
+        if (i0 + e < hi) {
+          if (a.out_logits) a.out_logits[o + e] = yo[e];
+          if (a.out_probs) a.out_probs[o + e] = po[e];
+        }
+      }
     }
-  } else {
-    for (uint32_t j = tid; np != kLinear && j < np; j += kBlock) {
-      const uint2 e = pl[j];
-      if ((int)e.x >= lo && (int)e.x < hi) pv[e.x - lo] = e.y;
-    }
-  }
-  __syncthreads();
-  for (int i = lo + tid; i < hi; i += kBlock) {
-    uint32_t k = fold_nan(key_raw(load_elem_bits<DT>(xrow, i)));
-    if (mask && !((((i >> 5) < Wm ? mask[i >> 5] : 0u) >> (i & 31)) & 1u)) k = 0u;
-    const uint32_t pk = pv[i - lo];
-    if (pk != kNone) k = pk;
-    if (np == kLinear) {  // very long lists: look every id up
-      const Ctx c = make_ctx<DT>(a, row);
-      int cn;
-      bool hb;
-      float bs;
-      if (lin_info(c, i, &cn, &hb, &bs) && k != 0u) k = lin_final<DT>(a, c, i);
-    }
-    emit(k, (uint32_t)i);
   }
 }
 
