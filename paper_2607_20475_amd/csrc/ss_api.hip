@@ -205,7 +205,6 @@ static ss_status launch(KArgs& k, int dtype, const Layout& lay, void* ws, hipStr
   else
     lp ? launch_stream<SS_F32, true>(k, grid, sblock, psmem, st) : launch_stream<SS_F32, false>(k, grid, sblock, psmem, st);
   launch_merge_any(k, dtype, lay.rows, lay.smem, st);
-  if (k.op == OP_VERIFY) launch_assemble(k, dim3((unsigned)((k.B + kBlock - 1) / kBlock)), block, st);
   if (materialize) {
     const int T = (k.V + 4095) / 4096;
     const dim3 mgrid((unsigned)(lay.rows * T));

@@ -69,10 +69,9 @@ struct RowSummary {
   int32_t kind;
 };
 struct RowResult {
-  int32_t accept;
-  int32_t emit;
-  int32_t flags;
-  int32_t pad;
+  uint64_t word;     // (token << 32) | (flags << 1) | accept
+  uint32_t arrived;  // of a request's first row: merged rows of the request
+  uint32_t pad;
 };
 
 struct KArgs {
@@ -853,7 +852,10 @@ __device__ __forceinline__ void scan_unit(const KArgs& a, int gu, WStage& W) {
       count = emit_elems<DT>(gk, gmask, off, total, t, (uint32_t)lo, region, W);
     }
   }
-  if (ln == 0) a.rec[gu] = make_uint4(t, count, wm, cut);
+  if (ln == 0) {
+    a.rec[gu] = make_uint4(t, count, wm, cut);
+    if (a.op == OP_VERIFY && u == 0 && row == b * (a.L + 1)) a.res[row].arrived = 0u;
+  }
 }
 
 // ===========================================================================

@@ -15,7 +15,6 @@ template <int DT, int OP>
 hipError_t merge_smem_limit(int bytes);
 template <int DT>
 void launch_materialize(const KArgs& k, dim3 grid, dim3 block, hipStream_t st);
-void launch_assemble(const KArgs& k, dim3 grid, dim3 block, hipStream_t st);
 void launch_zero(uint32_t* p, size_t n, dim3 grid, dim3 block, hipStream_t st);
 
 #define SS_EXTERN_MERGE(DT, OP)                                                            \

@@ -1095,12 +1095,9 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
         }
       } else {
         if (tid == 0) {
-          RowResult rr;
-          rr.accept = has_draft && !none && dtok == argmax;
-          rr.emit = argmax;
-          rr.flags = flags;
-          rr.pad = 0;
-          a.res[row] = rr;
+          S.bc[9] = (has_draft && !none && dtok == argmax) ? 1u : 0u;
+          S.bc[10] = (uint32_t)argmax;
+          S.bc[11] = (uint32_t)flags;
         }
       }
       return;
@@ -1278,14 +1275,11 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
         }
       }
     } else {
-      // verification: this row's decision; the assembly combines a request's rows
+      // verification: this row's decision; assemble_request combines a request's rows
       auto publish = [&](int accept, int token) {
-        RowResult rr;
-        rr.accept = accept;
-        rr.emit = token;
-        rr.flags = flags;
-        rr.pad = 0;
-        a.res[row] = rr;
+        S.bc[9] = (uint32_t)accept;
+        S.bc[10] = (uint32_t)token;
+        S.bc[11] = (uint32_t)flags;
       };
       if (!has_draft) {
         draw((double)Zs, [&](uint64_t cm) { publish(0, (int)comp_idx(cm)); });
@@ -1391,6 +1385,50 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
   }
 }
 
+// Verification: publishes the row's decision (bc[9..11]: accept, token, flags)
+// and, in the workgroup that is the last of its request, writes the request's
+// outputs: the accepted drafts, then the first row's correction (or the bonus
+// token), then -1.  The streaming launch cleared the request's arrival count
+// (the first row's `arrived`).  A decision is one 64-bit word, written and read by
+// agent-scope atomics, which go past the XCD's L2 by themselves: the arrival
+// follows once the word's store has completed, so no fence has to write back and
+// invalidate the L2 (that took 1.5 us).  A launch of its own for this cost 4.1 us.
+__device__ __forceinline__ void assemble_request(const KArgs& a, int row, const MSmem& S) {
+  if (wave() != 0) return;
+  const int ln = lane(), L = a.L;
+  const int b = row / (L + 1);
+  RowResult* res = a.res + (size_t)b * (L + 1);
+  int last = 0;
+  if (ln == 0) {
+    const uint64_t word = ((uint64_t)S.bc[10] << 32) | (S.bc[11] << 1) | S.bc[9];
+    __hip_atomic_store(&a.res[row].word, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the store has completed
+    last = __hip_atomic_fetch_add(&res->arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)L;
+  }
+  if (__builtin_amdgcn_readfirstlane(last) == 0) return;
+  asm volatile("" ::: "memory");  // the words are read after the last arrival
+  static_assert(SS_MAX_L < 64, "one lane per position");
+  int accept = 0, emit = -1, fl = 0, draft = -1;
+  if (ln <= L) {
+    const uint64_t word = __hip_atomic_load(&res[ln].word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    accept = (int)(word & 1u);
+    fl = (int)((uint32_t)word >> 1);
+    emit = (int)(uint32_t)(word >> 32);
+    if (ln < L) draft = a.draft_tokens[(size_t)b * L + ln];
+  }
+  // the first position that does not accept (the bonus position never does)
+  const int stop = (int)__builtin_ctzll(__ballot(ln == L || (ln < L && accept == 0)));
+  int all = 0;
+#pragma unroll
+  for (int f = 0; f < 4; ++f) all |= __ballot(ln <= stop && ((fl >> f) & 1)) != 0ull ? 1 << f : 0;
+  static_assert((SS_FLAG_EMPTY | SS_FLAG_FALLBACK | SS_FLAG_OUT_TRUNC | SS_FLAG_KCAP) == 15, "four flag bits");
+  if (ln <= L) a.out_tokens[(size_t)b * (L + 1) + ln] = ln < stop ? draft : (ln == stop ? emit : -1);
+  if (ln == 0) {
+    a.out_nacc[b] = stop;
+    if (a.flags) a.flags[b] = all;
+  }
+}
+
 // Merge kernel: one workgroup per row (the launch boundary orders the
 // streaming kernel's records and candidates before it).
 template <int DT, int OP, int BS>
@@ -1405,6 +1443,10 @@ __global__ __launch_bounds__(BS) void ss_merge_kernel(KArgs a) {
   const int nunits = a.rows * a.U;
   if ((a.rows & 7) == 0 && (nunits & 31) == 0) row = (row & 7) * (a.rows >> 3) + (row >> 3);
   merge_row<DT, OP, BS>(a, row, S, stage);
+  if constexpr (OP == OP_VERIFY) {
+    lds_barrier();
+    assemble_request(late_args(), row, S);
+  }
 }
 
 }  // namespace ss
