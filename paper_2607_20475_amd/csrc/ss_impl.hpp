@@ -171,11 +171,11 @@ template <int DT>
 struct DTT;
 template <>
 struct DTT<SS_F32> {
-  static constexpr int VW = 4, NLD = 8, ES = 4, GPL = 16, GE = 2;
+  static constexpr int VW = 4, NLD = 8, ES = 4, GE = 2;
 };
 template <>
 struct DTT<SS_BF16> {
-  static constexpr int VW = 8, NLD = 4, ES = 2, GPL = 8, GE = 4;
+  static constexpr int VW = 8, NLD = 4, ES = 2, GE = 4;
 };
 
 __host__ __device__ inline int groups_per_unit(int dt) { return dt == SS_BF16 ? 512 : 1024; }
@@ -357,19 +357,24 @@ __host__ __device__ inline int quota(int k, int U) {
   return q < k ? q : k;
 }
 
-// threshold groups per lane for quota q (groups of 32/G elements); 0 when the
-// quota is too large for a group threshold and the unit emits all it has
-__host__ __device__ inline int thr_groups(int q, int gpl) {
-  for (int G = 1; G <= gpl; G <<= 1)
+// Threshold groups per lane for quota q (32 / G elements each).  Groups of
+// several elements need four times as many groups as the quota, so that two of the
+// largest elements seldom share one; single elements (G = 32) give the exact
+// threshold of any quota, at 32 comparisons per search step.  0 when the quota is
+// the whole unit, which then emits all it has.  (Quotas beyond 128 groups in bf16
+// used to emit everything, which overflowed the merge: k = 4096 at V = 102438,
+// B = 138 took 939 us.)
+__host__ __device__ inline int thr_groups(int q) {
+  for (int G = 1; G <= 16; G <<= 1)
     if (64 * G >= 4 * q) return G;
-  return 0;
+  return q < kUE ? 32 : 0;
 }
 
 // capacity (groups, 16 bytes each) of one unit's candidate region
 __host__ __device__ inline int unit_cap(int k_cap, int U, int dt) {
   const int gpu = groups_per_unit(dt);
   const int q = quota(k_cap, U);
-  if (thr_groups(q, dt == SS_BF16 ? 8 : 16) == 0) return gpu;
+  if (thr_groups(q) == 0) return gpu;
   // room for twice the quota, and, when less than a whole unit, for k_cap
   // elements of one unit: a row tied at its maximum then finds its top-k
   // among the lowest-index tie groups of its first unit (the tie cut keeps
@@ -451,6 +456,30 @@ __device__ __forceinline__ uint32_t thr_bf16(const uint32_t (&kd)[16], uint32_t 
     gm[g] = hmax16(m);
   }
   return thr_search<G>(gm, q, 0);
+}
+// the same over pairs (H = 1) or single elements (H = 2), the group maxima
+// formed at each step instead of held; vmax is the unit's largest key
+template <int H>
+__device__ __forceinline__ uint32_t thr_bf16_wide(const uint32_t (&kd)[16], uint32_t q, uint32_t vmax) {
+  uint32_t prefix = 0u;
+#pragma unroll 1
+  for (int b = 31 - __clz(vmax | 1u); b >= 0; --b) {
+    const uint32_t cand = prefix | (1u << b);
+    uint32_t cnt = 0u;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      if constexpr (H == 1) {
+        cnt += (uint32_t)__popcll(__ballot(hmax16(kd[j]) >= cand));
+      } else {
+        cnt += (uint32_t)__popcll(__ballot((kd[j] & 0xFFFFu) >= cand)) + (uint32_t)__popcll(__ballot((kd[j] >> 16) >= cand));
+      }
+    }
+    if (cnt >= q) {
+      prefix = cand;
+      if (cnt == q) break;
+    }
+  }
+  return prefix;
 }
 template <int G>
 __device__ __forceinline__ uint32_t thr_f32(const uint32_t (&kk)[32], uint32_t q) {
@@ -600,7 +629,7 @@ __device__ __forceinline__ uint32_t emit_elems(const uint2 (&gk)[NG], uint32_t g
 // ~0u when every group at or above the threshold was written).
 template <int DT, bool LP>
 __device__ __forceinline__ void scan_unit(const KArgs& a, int gu, WStage& W) {
-  constexpr int VW = DTT<DT>::VW, NLD = DTT<DT>::NLD, ES = DTT<DT>::ES, GPL = DTT<DT>::GPL;
+  constexpr int VW = DTT<DT>::VW, NLD = DTT<DT>::NLD, ES = DTT<DT>::ES;
   const int ln = lane();
   const int row = gu / a.U;
   const int u = gu - row * a.U;
@@ -734,12 +763,14 @@ __device__ __forceinline__ void scan_unit(const KArgs& a, int gu, WStage& W) {
       t16 = 0x0081u;  // nothing valid
     } else {
       const uint32_t q = (uint32_t)quota(k_eff, a.U);
-      const int G = thr_groups((int)q, GPL);
+      const int G = thr_groups((int)q);
       if (q <= 1) t16 = wm16;
       else if (G == 1) t16 = thr_bf16<1>(kd, q);
       else if (G == 2) t16 = thr_bf16<2>(kd, q);
       else if (G == 4) t16 = thr_bf16<4>(kd, q);
       else if (G == 8) t16 = thr_bf16<8>(kd, q);
+      else if (G == 16) t16 = thr_bf16_wide<1>(kd, q, wm16);
+      else if (G == 32) t16 = thr_bf16_wide<2>(kd, q, wm16);
       else t16 = 0x0081u;
       t16 = max(t16, 0x0081u);
     }
@@ -819,13 +850,14 @@ __device__ __forceinline__ void scan_unit(const KArgs& a, int gu, WStage& W) {
       t = kKeyFloor;
     } else {
       const uint32_t q = (uint32_t)quota(k_eff, a.U);
-      const int G = thr_groups((int)q, GPL);
+      const int G = thr_groups((int)q);
       if (q <= 1) t = wm;
       else if (G == 1) t = thr_f32<1>(kk, q);
       else if (G == 2) t = thr_f32<2>(kk, q);
       else if (G == 4) t = thr_f32<4>(kk, q);
       else if (G == 8) t = thr_f32<8>(kk, q);
       else if (G == 16) t = thr_f32<16>(kk, q);
+      else if (G == 32) t = thr_f32<32>(kk, q);
       else t = kKeyFloor;
       t = max(t, kKeyFloor);
     }
