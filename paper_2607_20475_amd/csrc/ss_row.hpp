@@ -510,6 +510,75 @@ __device__ __forceinline__ int slow_select(const KArgs& a, const Ctx& c, MSmem& 
   }
 }
 
+// The slow path of rows that want one element (a greedy row whose largest raw
+// logits are all patched: a penalised top token).  The best unpatched candidate
+// or final value bounds every unit whose threshold is no higher; the few others
+// are re-read whole, one per wavefront, all their loads in flight together.  The
+// general slow path took three passes, each element by element: 5 us more for a
+// call with one such row.
+template <int DT, int BS>
+__device__ __forceinline__ int greedy_refill(const KArgs& a, const Ctx& c, MSmem& S, uint64_t* pool, bool patch) {
+  constexpr int VW = DTT<DT>::VW, NLD = DTT<DT>::NLD, EPW = DT == SS_BF16 ? 1 : 2;
+  const int tid = threadIdx.x, ln = lane();
+  const int tpu = a.tpu;
+  const int u = (tid * a.tpu_inv) >> 20, sub = tid - u * tpu;
+  const bool act = u < a.U;
+  const size_t g = (size_t)c.row * a.U + (act ? u : 0);
+  const uint4 r4 = a.rec[g];
+  const uint32_t* src = reinterpret_cast<const uint32_t*>(a.cand + g * a.cap);
+  if (tid == 0) S.bc[8] = 0u;
+  uint64_t best = 0ull;
+  for (uint32_t i = (uint32_t)sub; act && i < r4.y; i += (uint32_t)tpu) {
+    const uint32_t w = src[i * EPW];
+    uint64_t cm;
+    if constexpr (DT == SS_BF16) cm = comp_of(w & 0xFFFF0000u, (uint32_t)(u * kUE) + 0xFFFFu - (w & 0xFFFFu));
+    else cm = ((uint64_t)src[i * EPW + 1] << 32) | w;
+    if (cm > best && !(patch && lds_patched(S, (int)comp_idx(cm), c.pexact))) best = cm;
+  }
+  if (patch) {
+    for (int sl = tid; sl < kH; sl += BS)
+      if (S.hk[sl] >= 0 && S.hf[sl] >= kKeyFloor) best = max(best, comp_of(S.hf[sl], (uint32_t)S.hk[sl]));
+  }
+  best = uniform(wg_max<BS>(best, S.x64[0]));
+  if (act && sub == 0 && r4.x != kNoEmit && comp_of(r4.x, r4.w) > best) S.bins[atomicAdd(&S.bc[8], 1u)] = (uint32_t)u;
+  lds_barrier();
+  const int nre = (int)uniform(S.bc[8]);
+#pragma unroll 1
+  for (int j = __builtin_amdgcn_readfirstlane(wave()); j < nre; j += BS / 64) {
+    const int lo = (int)uniform(S.bins[j]) * kUE;
+    uint4 r[NLD];
+    uint32_t mw[NLD];
+#pragma unroll
+    for (int i = 0; i < NLD; ++i) {
+      const int l0 = lo + (i * 64 + ln) * VW;
+      r[i] = make_uint4(kNone, kNone, kNone, kNone);  // negative NaN: invalid
+      mw[i] = kNone;
+      if (l0 + VW <= a.V) r[i] = load16(c.xrow + (size_t)l0 * DTT<DT>::ES);
+      if (c.mask && l0 < a.V) mw[i] = c.mask[l0 >> 5] >> (l0 & 31);
+    }
+#pragma unroll
+    for (int i = 0; i < NLD; ++i) {
+      const int l0 = lo + (i * 64 + ln) * VW;
+      const uint32_t w4[4] = {r[i].x, r[i].y, r[i].z, r[i].w};
+      const bool part = l0 < a.V && l0 + VW > a.V;  // the row's last chunk
+#pragma unroll
+      for (int e = 0; e < VW; ++e) {
+        uint32_t bits;
+        if constexpr (DT == SS_F32) bits = w4[e];
+        else bits = (e & 1) ? w4[e >> 1] & 0xFFFF0000u : w4[e >> 1] << 16;
+        if (part && l0 + e < a.V) bits = load_elem_bits<DT>(c.xrow, l0 + e);
+        const uint32_t k = ((mw[i] >> e) & 1u) ? fold_nan(key_raw(bits)) : 0u;
+        const uint64_t cm = comp_of(k, (uint32_t)(l0 + e));
+        if (k >= kKeyFloor && cm > best && !(patch && lds_patched(S, l0 + e, c.pexact))) best = cm;
+      }
+    }
+  }
+  best = wg_max<BS>(best, S.x64[1]);
+  if (tid == 0) pool[0] = best;
+  lds_barrier();
+  return best != 0ull ? 1 : 0;
+}
+
 // This thread's share of the full-row normaliser sum_j exp((y_j - M) / tau)
 // over the row's valid processed logits, for rows whose lists exceed the LDS
 // table: every element's processed value.
@@ -788,7 +857,7 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
       for (int x = 0; x < NE; ++x)
         if (x / EPQ < a.nq) hit |= ((pw[x] >> (pbit((int)comp_idx(elem(x)), pexact) & 31u)) & 1u) << x;
       hit &= sel;
-      if (pexact) {
+      if (__builtin_expect(pexact, 1)) {
         sel &= ~hit;
       } else {  // hashed bitmap: confirmed in the table
         while (hit != 0u) {
@@ -840,10 +909,10 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
   // first pass: the maximum (want == 1) or the bins' counts; second pass:
   // every element to its bin's next place (all places asked for before any is used)
   uint32_t bp[NE + 4 * KT];
-  bool single = want == 1;
+  const bool single = want == 1;
   for (int pass = 0; pass < 2 && nbatch > 0 && !slow; ++pass) {
     for (int batch = 0; batch < nbatch; ++batch) {
-      if (batch > 0 || (pass > 0 && nbatch > 1)) load_batch(batch);
+      if (__builtin_expect(batch > 0 || (pass > 0 && nbatch > 1), 0)) load_batch(batch);
       if (pass == 0 || nbatch > 1) {
         sel = select(batch);
         if (!single) {
@@ -921,7 +990,8 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
       if (total < (uint32_t)want) {
         // at the lowest threshold there is the list is the whole row (few
         // tokens allowed by a grammar); otherwise elements may be missing
-        if (tc == comp_of(kKeyFloor, kNone)) want = (int)total;
+        constexpr uint32_t lowest = DT == SS_BF16 ? 0x00810000u : kKeyFloor;  // smallest valid key
+        if (tc <= comp_of(lowest, kNone)) want = (int)total;
         else slow = true;
       }
 #pragma unroll
@@ -961,16 +1031,19 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
   int pmode = pst == 1 ? 1 : 0;
   PatchG pg = {};
   Ctx c = {};
-  if (!empty && want > 0 && slow) {
+  if (__builtin_expect(!empty && want > 0 && slow, 0)) {
     const KArgs& a = late_args();
     flags |= SS_FLAG_FALLBACK;
     c = make_ctx<DT>(a, row);
     if (pst == 2) pmode = global_table<DT, BS>(a, c, S, row, pg);
-    nB = (uint32_t)slow_select<DT, BS>(a, c, S, stage, pmode, pg, (uint32_t)want);
+    if (want == 1 && pmode <= 1 && cmax != kOvf)
+      nB = (uint32_t)greedy_refill<DT, BS>(a, c, S, stage, pmode == 1);
+    else
+      nB = (uint32_t)slow_select<DT, BS>(a, c, S, stage, pmode, pg, (uint32_t)want);
     nT = min(want, (int)nB);
     crowded = true;
   }
-  if (crowded) {
+  if (__builtin_expect(crowded, 0)) {
     T = stage;
     if (nB > 1u) {
       const int N = next_pow2((int)nB);
@@ -990,7 +1063,7 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
   auto row_norm = [&](double M, float tauf) -> double {
     const double tau2 = (double)tauf;
     double z = 0.0;
-    if (pmode <= 1) {
+    if (__builtin_expect(pmode <= 1, 1)) {
       const float c2 = lp_scale(tauf);
       double* uf = reinterpret_cast<double*>(S.bins);
       float* um = reinterpret_cast<float*>(S.bins + 2 * kMaxU);
