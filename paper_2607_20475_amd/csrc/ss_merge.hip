@@ -21,7 +21,8 @@ void launch_merge(const KArgs& k, int rows, int smem, hipStream_t st) {
   a.tpu_inv = ((1 << 20) + a.tpu - 1) / a.tpu;
   const int q = quota(a.k_cap, a.U), want = q + q / 8 + 4;
   const int nq = (want + a.tpu * EPQ - 1) / (a.tpu * EPQ);
-  a.nq = nq < NQM ? nq : NQM;
+  a.nq = nq < 4 ? nq : (nq == 4 ? 4 : NQM);
+  if (a.nq > NQM) a.nq = NQM;
   hipLaunchKernelGGL((ss_merge_kernel<DT, OP, BS>), dim3((unsigned)rows), dim3(BS), smem, st, a);
 }
 template <int DT, int OP>

@@ -658,10 +658,11 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
   uint4 cq[NQM];
   auto load_batch = [&](int batch) {
 #pragma unroll
-    for (int j = 0; j < NQM; ++j)
-      if (j < a.nq) cq[j] = region[min((batch * a.nq + j) * tpu + sub, a.cap - 1)];
+    for (int j = 0; j < NQM; ++j) cq[j] = region[min((batch * NQM + j) * tpu + sub, a.cap - 1)];
   };
-  load_batch(0);
+#pragma unroll
+  for (int j = 0; j < NQM; ++j)
+    if (j < a.nq) cq[j] = region[min(j * tpu + sub, a.cap - 1)];
   const bool tables = OP != OP_TOPK && a.patch_wgs > 0;
   constexpr int KT = (kH / 4 + BS - 1) / BS;  // 16-byte words per thread and table half
   uint4 tid4[KT], tfin4[KT];
@@ -807,10 +808,22 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
   const bool empty = hi < kKeyFloor;
   bool slow = cmax == kOvf || pst == 2;
 
-  // 3. the elements that take part
-  const int covered = a.nq * tpu * EPQ;  // candidates per unit in one batch
-  const int nbatch = (!empty && want > 0 && !slow) ? max(1, (int)((cmax + (uint32_t)covered - 1u) / (uint32_t)covered)) : 0;
+  // 3. the elements that take part.  The code below is written for a fixed
+  // number of candidate loads (with_nq), so that a row runs straight through it;
+  // units with more candidates than those loads cover (`many`: k in the thousands,
+  // heavy ties) are walked in batches of NQM loads instead.
+  const bool go = !empty && want > 0 && !slow;
+  const bool single = want == 1;
+  const bool many = cmax > (uint32_t)(a.nq * tpu * EPQ);
+  const int nbatch = many ? (int)((cmax + (uint32_t)(NQM * tpu * EPQ) - 1u) / (uint32_t)(NQM * tpu * EPQ)) : 1;
   constexpr int NE = NQM * EPQ;
+  auto with_nq = [&](auto&& f) {
+    if (a.nq == 1) f(std::integral_constant<int, 1>{});
+    else if (a.nq == 2) f(std::integral_constant<int, 2>{});
+    else if (NQM == 3 || a.nq == 3) f(std::integral_constant<int, 3>{});
+    else if (a.nq == 4) f(std::integral_constant<int, 4>{});
+    else f(std::integral_constant<int, NQM>{});
+  };
   // composite of candidate x = EPQ j + e
   const uint32_t ubase = ~(uint32_t)(u * kUE) - 0xFFFFu;
   auto elem = [&](int x) -> uint64_t {
@@ -827,35 +840,33 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
   uint32_t wthr = tck;
   if constexpr (DT == SS_BF16) {
     const uint32_t lo = (uint32_t)(u * kUE);
-    if (tcut < lo) wthr = tck + 0x10000u;
-    else if (tcut - lo < (uint32_t)kUE) wthr = tck | (0xFFFFu - (tcut - lo));
+    const uint32_t in = tcut - lo < (uint32_t)kUE ? tck | (0xFFFFu - (tcut - lo)) : tck;
+    wthr = tcut < lo ? tck + 0x10000u : in;
   }
   // the candidates of a batch that are at or above tc and no raw copy of a
   // patched id (every LDS read is issued before any is used)
-  auto select = [&](int batch) -> uint32_t {
+  auto select = [&](auto nq, int batch) -> uint32_t {
+    constexpr int NQ = decltype(nq)::value, N = NQ * EPQ;
     uint32_t sel = 0u;
 #pragma unroll
-    for (int j = 0; j < NQM; ++j) {
-      if (j < a.nq) {
-        const int rem = (int)cnt - ((batch * a.nq + j) * tpu + sub) * EPQ;
+    for (int j = 0; j < NQ; ++j) {
+      const int rem = (int)cnt - ((batch * NQ + j) * tpu + sub) * EPQ;
 #pragma unroll
-        for (int e = 0; e < EPQ; ++e) {
-          bool at;
-          if constexpr (DT == SS_BF16) at = (e == 0 ? cq[j].x : (e == 1 ? cq[j].y : (e == 2 ? cq[j].z : cq[j].w))) >= wthr;
-          else at = elem(j * EPQ + e) >= tc;
-          sel |= (at && e < rem) ? 1u << (j * EPQ + e) : 0u;
-        }
+      for (int e = 0; e < EPQ; ++e) {
+        bool at;
+        if constexpr (DT == SS_BF16) at = (e == 0 ? cq[j].x : (e == 1 ? cq[j].y : (e == 2 ? cq[j].z : cq[j].w))) >= wthr;
+        else at = elem(j * EPQ + e) >= tc;
+        sel |= (at && e < rem) ? 1u << (j * EPQ + e) : 0u;
       }
     }
-    if (pst == 1 && __ballot(sel != 0u) != 0ull) {
-      uint32_t pw[NE];
+    if (pst == 1) {
+      uint32_t pw[N];
 #pragma unroll
-      for (int x = 0; x < NE; ++x)
-        if (x / EPQ < a.nq) pw[x] = S.pbits[(pbit((int)comp_idx(elem(x)), pexact) >> 5) & (kPB / 32 - 1)];
+      for (int x = 0; x < N; ++x) pw[x] = S.pbits[(pbit((int)comp_idx(elem(x)), pexact) >> 5) & (kPB / 32 - 1)];
       uint32_t hit = 0u;
 #pragma unroll
-      for (int x = 0; x < NE; ++x)
-        if (x / EPQ < a.nq) hit |= ((pw[x] >> (pbit((int)comp_idx(elem(x)), pexact) & 31u)) & 1u) << x;
+      for (int x = 0; x < N; ++x)
+        hit |= ((pw[x] >> (pbit((int)comp_idx(elem(x)), pexact) & 31u)) & 1u) << x;
       hit &= sel;
       if (__builtin_expect(pexact, 1)) {
         sel &= ~hit;
@@ -864,7 +875,7 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
           const uint32_t low = hit & (0u - hit);
           int id = 0;
 #pragma unroll
-          for (int x = 0; x < NE; ++x) id = low == (1u << x) ? (int)comp_idx(elem(x)) : id;
+          for (int x = 0; x < N; ++x) id = low == (1u << x) ? (int)comp_idx(elem(x)) : id;
           if (hfind(S, id) >= 0) sel &= ~low;
           hit ^= low;
         }
@@ -872,26 +883,6 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
     }
     return sel;
   };
-  uint32_t sel = 0u;
-  uint32_t fsel = 0u;  // patched finals at or above tc
-  uint64_t fc[4 * KT];
-  if (nbatch > 0 && pst == 1) {
-#pragma unroll
-    for (int m = 0; m < KT; ++m) {
-      const uint32_t ids[4] = {tid4[m].x, tid4[m].y, tid4[m].z, tid4[m].w};
-      const uint32_t fk[4] = {tfin4[m].x, tfin4[m].y, tfin4[m].z, tfin4[m].w};
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        fc[4 * m + q] = comp_of(fk[q], ids[q]);
-        if ((int)ids[q] >= 0 && fk[q] >= kKeyFloor && fc[4 * m + q] >= tc) fsel |= 1u << (4 * m + q);
-      }
-    }
-  }
-  uint64_t* sorted = stage + a.pcap;
-  const uint64_t* T = sorted;  // the row's list in canonical order
-  int nT = 0;
-  bool crowded = false;  // the list (or a superset) is in stage, unsorted
-  uint32_t nB = 0u;      // entries of stage
   // Bins in canonical order: 2^sh steps of an order value below the largest
   // possible key.  bf16 keys lie on a grid of 2^16, so the order value of a grid
   // element carries its index in the low half (a key that a hundred ids share
@@ -906,59 +897,73 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
     if constexpr (DT == SS_BF16) o |= (key & 0xFFFFu) ? 0xFFFFu : comp_idx(cm) >> ish;
     return o >> sh;
   };
-  // first pass: the maximum (want == 1) or the bins' counts; second pass:
-  // every element to its bin's next place (all places asked for before any is used)
-  uint32_t bp[NE + 4 * KT];
-  const bool single = want == 1;
-  for (int pass = 0; pass < 2 && nbatch > 0 && !slow; ++pass) {
-    for (int batch = 0; batch < nbatch; ++batch) {
-      if (__builtin_expect(batch > 0 || (pass > 0 && nbatch > 1), 0)) load_batch(batch);
-      if (pass == 0 || nbatch > 1) {
-        sel = select(batch);
-        if (!single) {
-#pragma unroll
-          for (int x = 0; x < NE; ++x)
-            if (x / EPQ < a.nq) bp[x] = bin_of(elem(x)) & (kNB - 1);
-        }
-      }
-      const uint32_t fs = batch == 0 ? fsel : 0u;
+  auto grid_bin = [&](int x) -> uint32_t {  // of a candidate: a raw value, on the grid
+    const uint64_t cm = elem(x);
+    uint32_t o = kmax - comp_key(cm);
+    if constexpr (DT == SS_BF16) o |= comp_idx(cm) >> ish;
+    return (o >> sh) & (kNB - 1);
+  };
+  uint64_t* sorted = stage + a.pcap;
+  const uint64_t* T = sorted;  // the row's list in canonical order
+  int nT = 0;
+  bool crowded = false;  // the list (or a superset) is in stage, unsorted
+  uint32_t nB = 0u;      // entries of stage
+  if (go) {
+    uint32_t sel = 0u, bp[NE];
+    // first pass: the maximum (single) or the bins' counts
+    auto count = [&](auto nq, int batch) {
+      constexpr int N = decltype(nq)::value * EPQ;
+      sel = select(nq, batch);
       if (single) {
         uint64_t mc = 0ull;
 #pragma unroll
-        for (int x = 0; x < NE; ++x)
-          if (x / EPQ < a.nq) mc = ((sel >> x) & 1u) ? max(mc, elem(x)) : mc;
-        if (fs != 0u) {
-#pragma unroll
-          for (int x = 0; x < 4 * KT; ++x) mc = ((fs >> x) & 1u) ? max(mc, fc[x]) : mc;
-        }
+        for (int x = 0; x < N; ++x) mc = ((sel >> x) & 1u) ? max(mc, elem(x)) : mc;
         if (mc != 0ull) atomicMax((unsigned long long*)&S.best, (unsigned long long)mc);
-      } else if (pass == 0) {
-#pragma unroll
-        for (int x = 0; x < NE; ++x)
-          if ((sel >> x) & 1u) atomicAdd(&S.bins[bp[x]], 1u);
-        if (fs != 0u) {
-#pragma unroll
-          for (int x = 0; x < 4 * KT; ++x) {
-            bp[NE + x] = bin_of(fc[x]) & (kNB - 1);
-            if ((fs >> x) & 1u) atomicAdd(&S.bins[bp[NE + x]], 1u);
-          }
-        }
       } else {
 #pragma unroll
-        for (int x = 0; x < NE; ++x)
-          if ((sel >> x) & 1u) bp[x] = atomicAdd(&S.bins[bp[x]], 1u);
-        if (fs != 0u) {
+        for (int x = 0; x < N; ++x) bp[x] = grid_bin(x);
 #pragma unroll
-          for (int x = 0; x < 4 * KT; ++x)
-            if ((fs >> x) & 1u) bp[NE + x] = atomicAdd(&S.bins[bp[NE + x]], 1u);
-        }
+        for (int x = 0; x < N; ++x)
+          if ((sel >> x) & 1u) atomicAdd(&S.bins[bp[x]], 1u);
+      }
+    };
+    // second pass: every element to its bin's next place (all asked for before any is used)
+    auto place = [&](auto nq) {
+      constexpr int N = decltype(nq)::value * EPQ;
 #pragma unroll
-        for (int x = 0; x < NE; ++x)
-          if (((sel >> x) & 1u) && bp[x] < nB) stage[bp[x]] = elem(x);
-        if (fs != 0u) {
+      for (int x = 0; x < N; ++x)
+        if ((sel >> x) & 1u) bp[x] = atomicAdd(&S.bins[bp[x]], 1u);
 #pragma unroll
-          for (int x = 0; x < 4 * KT; ++x)
-            if (((fs >> x) & 1u) && bp[NE + x] < nB) stage[bp[NE + x]] = fc[x];
+      for (int x = 0; x < N; ++x)
+        if (((sel >> x) & 1u) && bp[x] < nB) stage[bp[x]] = elem(x);
+    };
+    constexpr auto all = std::integral_constant<int, NQM>{};
+    if (__builtin_expect(!many, 1)) {
+      with_nq([&](auto nq) { count(nq, 0); });
+    } else {
+#pragma unroll 1
+      for (int batch = 0; batch < nbatch; ++batch) {
+        load_batch(batch);
+        count(all, batch);
+      }
+    }
+    // patched final values at or above tc
+    uint32_t fsel = 0u;
+    uint64_t fc[4 * KT];
+    const bool finals = pst == 1 && hfmax >= tck;
+    if (finals) {
+#pragma unroll
+      for (int m = 0; m < KT; ++m) {
+        const uint32_t ids[4] = {tid4[m].x, tid4[m].y, tid4[m].z, tid4[m].w};
+        const uint32_t fk[4] = {tfin4[m].x, tfin4[m].y, tfin4[m].z, tfin4[m].w};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {  // (empty slots have key 0, below every tc)
+          fc[4 * m + q] = comp_of(fk[q], ids[q]);
+          if (fc[4 * m + q] >= tc) {
+            fsel |= 1u << (4 * m + q);
+            if (single) atomicMax((unsigned long long*)&S.best, (unsigned long long)fc[4 * m + q]);
+            else atomicAdd(&S.bins[bin_of(fc[4 * m + q])], 1u);
+          }
         }
       }
     }
@@ -969,9 +974,7 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
       nT = slow ? 0 : 1;
       if (tid == 0) sorted[0] = mc;
       lds_barrier();
-      break;
-    }
-    if (pass == 0) {
+    } else {
       // counts to starts; the bins that hold the list end at nB
       constexpr int BPT = kNB / BS;  // bins per thread
       uint32_t h[BPT], s = 0u;
@@ -1006,23 +1009,46 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
       lds_barrier();
       nB = uniform(S.bc[0]);
       if (nB > (uint32_t)a.pcap) slow = true;  // ties beyond the staging area
-    } else {
-      crowded = uniform(S.bc[1]) != 0u;
-      nT = want;
-      if (!crowded) {
-        for (uint32_t p = (uint32_t)tid; p < nB; p += (uint32_t)BS) {
-          const uint64_t e = stage[p];
-          const uint32_t bn = bin_of(e);
-          const uint32_t bs = bn != 0u ? S.bins[bn - 1u] : 0u, be = S.bins[bn];
-          uint32_t r = bs;
-          for (uint32_t j = bs; j < be; j += 4u) {
-            const uint64_t s0 = stage[j], s1 = stage[j + 1u], s2 = stage[j + 2u], s3 = stage[j + 3u];
-            r += (s0 > e ? 1u : 0u) + ((j + 1u < be && s1 > e) ? 1u : 0u) + ((j + 2u < be && s2 > e) ? 1u : 0u) +
-                 ((j + 3u < be && s3 > e) ? 1u : 0u);
+      if (!slow) {
+        if (__builtin_expect(!many, 1)) {
+          with_nq([&](auto nq) { place(nq); });
+        } else {
+#pragma unroll 1
+          for (int batch = 0; batch < nbatch; ++batch) {
+            load_batch(batch);
+            sel = select(all, batch);
+#pragma unroll
+            for (int x = 0; x < NE; ++x) bp[x] = grid_bin(x);
+            place(all);
           }
-          if (r < (uint32_t)want) sorted[r] = e;
+        }
+        if (fsel != 0u) {
+#pragma unroll
+          for (int x = 0; x < 4 * KT; ++x) {
+            if ((fsel >> x) & 1u) {
+              const uint32_t p = atomicAdd(&S.bins[bin_of(fc[x])], 1u);
+              if (p < nB) stage[p] = fc[x];
+            }
+          }
         }
         lds_barrier();
+        crowded = uniform(S.bc[1]) != 0u;
+        nT = want;
+        if (!crowded) {
+          for (uint32_t p = (uint32_t)tid; p < nB; p += (uint32_t)BS) {
+            const uint64_t e = stage[p];
+            const uint32_t bn = bin_of(e);
+            const uint32_t bs = bn != 0u ? S.bins[bn - 1u] : 0u, be = S.bins[bn];
+            uint32_t r = bs;
+            for (uint32_t j = bs; j < be; j += 4u) {
+              const uint64_t s0 = stage[j], s1 = stage[j + 1u], s2 = stage[j + 2u], s3 = stage[j + 3u];
+              r += (s0 > e ? 1u : 0u) + ((j + 1u < be && s1 > e) ? 1u : 0u) + ((j + 2u < be && s2 > e) ? 1u : 0u) +
+                   ((j + 3u < be && s3 > e) ? 1u : 0u);
+            }
+            if (r < (uint32_t)want) sorted[r] = e;
+          }
+          lds_barrier();
+        }
       }
     }
   }
