@@ -240,7 +240,7 @@ __device__ __forceinline__ uint32_t wave_excl_small(uint32_t c, uint32_t& total)
   return off;
 }
 
-__host__ __device__ constexpr int next_pow2(int v) {
+__host__ __device__ __forceinline__ constexpr int next_pow2(int v) {
   int p = 1;
   while (p < v) p <<= 1;
   return p;

@@ -655,14 +655,21 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
   const size_t gu = (size_t)row * U + u;
   const uint4* region = a.cand + gu * (size_t)a.cap;
   const uint4 r4 = a.rec[gu];
-  uint4 cq[NQM];
+  uint32_t cw[4 * NQM];
+  auto load_one = [&](int j, int at) {
+    const uint4 q = region[min(at, a.cap - 1)];
+    cw[4 * j] = q.x;
+    cw[4 * j + 1] = q.y;
+    cw[4 * j + 2] = q.z;
+    cw[4 * j + 3] = q.w;
+  };
   auto load_batch = [&](int batch) {
 #pragma unroll
-    for (int j = 0; j < NQM; ++j) cq[j] = region[min((batch * NQM + j) * tpu + sub, a.cap - 1)];
+    for (int j = 0; j < NQM; ++j) load_one(j, (batch * NQM + j) * tpu + sub);
   };
 #pragma unroll
   for (int j = 0; j < NQM; ++j)
-    if (j < a.nq) cq[j] = region[min(j * tpu + sub, a.cap - 1)];
+    if (j < a.nq) load_one(j, j * tpu + sub);
   const bool tables = OP != OP_TOPK && a.patch_wgs > 0;
   constexpr int KT = (kH / 4 + BS - 1) / BS;  // 16-byte words per thread and table half
   uint4 tid4[KT], tfin4[KT];
@@ -827,14 +834,8 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
   // composite of candidate x = EPQ j + e
   const uint32_t ubase = ~(uint32_t)(u * kUE) - 0xFFFFu;
   auto elem = [&](int x) -> uint64_t {
-    const uint4 q = cq[x / EPQ];
-    const int e = x % EPQ;
-    if constexpr (DT == SS_BF16) {
-      const uint32_t w = e == 0 ? q.x : (e == 1 ? q.y : (e == 2 ? q.z : q.w));
-      return ((uint64_t)(w & 0xFFFF0000u) << 32) | (ubase + (w & 0xFFFFu));
-    } else {
-      return e == 0 ? ((uint64_t)q.y << 32) | q.x : ((uint64_t)q.w << 32) | q.z;
-    }
+    if constexpr (DT == SS_BF16) return ((uint64_t)(cw[x] & 0xFFFF0000u) << 32) | (ubase + (cw[x] & 0xFFFFu));
+    else return ((uint64_t)cw[2 * x + 1] << 32) | cw[2 * x];
   };
   // bf16: tc as a stored word of this thread's unit
   uint32_t wthr = tck;
@@ -854,7 +855,7 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
 #pragma unroll
       for (int e = 0; e < EPQ; ++e) {
         bool at;
-        if constexpr (DT == SS_BF16) at = (e == 0 ? cq[j].x : (e == 1 ? cq[j].y : (e == 2 ? cq[j].z : cq[j].w))) >= wthr;
+        if constexpr (DT == SS_BF16) at = cw[j * EPQ + e] >= wthr;
         else at = elem(j * EPQ + e) >= tc;
         sel |= (at && e < rem) ? 1u << (j * EPQ + e) : 0u;
       }
@@ -1205,7 +1206,8 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
     // ---- truncation and selection (Alg. 11 order) on T[0, nT): entry r =
     // 64 (E wave + j) + lane is held by one thread, E entries per thread
     const double M = (double)float_of_key(comp_key(Mcomp));
-    const int E = (nT + BS - 1) / BS;
+    auto epilogue = [&](auto ec) {
+    constexpr int E = decltype(ec)::value;
     const int r0 = 64 * E * wv + ln;
     auto yval = [&](uint64_t cm) { return (double)float_of_key(comp_key(cm)); };
     auto weight = [&](uint64_t cm) { return weight_fast(yval(cm), M, itau); };
@@ -1216,12 +1218,12 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
       return cm != Mcomp && !(l >= lt);
     };
     // exclusive prefix sums of wt over the list; returns the total
-    uint64_t el[EM], wt[EM], ex[EM];
+    uint64_t el[E], wt[E], ex[E];
     auto scan_list = [&](uint64_t* scratch) -> uint64_t {
       uint64_t run = 0ull;
 #pragma unroll
-      for (int j = 0; j < EM; ++j) {
-        if (j < E) {
+      for (int j = 0; j < E; ++j) {
+        {
           const uint64_t inc = wave_incl_scan(wt[j]);
           ex[j] = run + inc - wt[j];
           run += readlane_T(inc, 63);
@@ -1232,13 +1234,13 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
       uint64_t before, total;
       wave_prefix<NW>(scratch, wv, before, total);
 #pragma unroll
-      for (int j = 0; j < EM; ++j)
-        if (j < E) ex[j] += before;
+      for (int j = 0; j < E; ++j)
+        ex[j] += before;
       return total;
     };
 #pragma unroll
-    for (int j = 0; j < EM; ++j) {
-      if (j < E) {
+    for (int j = 0; j < E; ++j) {
+      {
         const int r = r0 + 64 * j;
         el[j] = r < nT ? T[r] : 0ull;
         wt[j] = r < nT ? (uint64_t)__double2ll_rn(weight(el[j]) * kFix) : 0ull;
@@ -1252,8 +1254,8 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
     if (OP == OP_SAMPLE_X && full_row) zrow = kFix * row_norm(M, (float)tau);
     const double Xp = (double)topp_v * (double)Zk, Xr = (double)topp_v * zrow;
 #pragma unroll
-    for (int j = 0; j < EM; ++j) {
-      if (j < E) {
+    for (int j = 0; j < E; ++j) {
+      {
         const int r = r0 + 64 * j;
         if (r < nT) {
           const double in = (double)(ex[j] + wt[j]), be = (double)ex[j];
@@ -1310,8 +1312,8 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
     auto draw = [&](double total, auto&& f) {
       const double X = u0 * total;
 #pragma unroll
-      for (int j = 0; j < EM; ++j) {
-        if (j < E) {
+      for (int j = 0; j < E; ++j) {
+        {
           const int r = r0 + 64 * j;
           if (r < (int)n_s && ((double)(ex[j] + wt[j]) > X || r == (int)n_s - 1) && (r == 0 || (double)ex[j] <= X))
             f(el[j]);
@@ -1344,8 +1346,8 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
         double bs = -__builtin_inf();
         uint64_t bk = 0ull;  // (~id << 32) | key of this thread's best
 #pragma unroll
-        for (int j = 0; j < EM; ++j) {
-          if (j < E) {
+        for (int j = 0; j < E; ++j) {
+          {
             const int r = r0 + 64 * j;
             if (r < (int)n_s) {
               const uint64_t cm = el[j];
@@ -1386,8 +1388,8 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
       }
       // P(d): zero (bc64[3]) unless the draft token is kept
 #pragma unroll
-      for (int j = 0; j < EM; ++j) {
-        if (j < E) {
+      for (int j = 0; j < E; ++j) {
+        {
           const int r = r0 + 64 * j;
           if (r < (int)n_s && (int)comp_idx(el[j]) == dtok) S.bc64[3] = __builtin_bit_cast(uint64_t, weight(el[j]) / Zsd);
         }
@@ -1452,7 +1454,7 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
       };
       // residual max(0, P - q) over the kept set, canonical order; the kept
       // weights again when it is empty
-      uint64_t rs[EM];
+      uint64_t rs[E];
 #pragma unroll 1
       for (int j = 0; j < E; ++j) {
         const int r = r0 + 64 * j;
@@ -1463,23 +1465,28 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
           v64 = v > 0.0 ? (uint64_t)__double2ll_rn(v * kFix) : 0ull;
         }
 #pragma unroll
-        for (int jj = 0; jj < EM; ++jj)
+        for (int jj = 0; jj < E; ++jj)
           if (jj == j) rs[jj] = v64;
       }
       uint64_t any = 0ull;
 #pragma unroll
-      for (int j = 0; j < EM; ++j)
-        if (j < E) any |= rs[j];
+      for (int j = 0; j < E; ++j)
+        any |= rs[j];
       any = wg_max<BS>(any, S.x64[2]);
       double total = (double)Zs;
       if (any != 0ull) {
 #pragma unroll
-        for (int j = 0; j < EM; ++j)
-          if (j < E) wt[j] = rs[j];
+        for (int j = 0; j < E; ++j)
+          wt[j] = rs[j];
         total = (double)scan_list(S.x64[0]);
       }
       draw(total, [&](uint64_t cm) { publish(0, (int)comp_idx(cm)); });
     }
+    };
+    // straight-line code for the usual list lengths
+    if (nT <= BS) epilogue(std::integral_constant<int, 1>{});
+    else if (nT <= 2 * BS) epilogue(std::integral_constant<int, 2>{});
+    else epilogue(std::integral_constant<int, EM>{});
   }
   }
 }
@@ -1530,8 +1537,10 @@ __device__ __forceinline__ void assemble_request(const KArgs& a, int row, const 
 
 // Merge kernel: one workgroup per row (the launch boundary orders the
 // streaming kernel's records and candidates before it).
+// (At most 128 registers, so that two workgroups share a CU when there are more
+// rows than CUs; the extended sampling merge needs a few more.)
 template <int DT, int OP, int BS>
-__global__ __launch_bounds__(BS) void ss_merge_kernel(KArgs a) {
+__global__ __launch_bounds__(BS, OP == OP_SAMPLE_X ? 2 : 4) void ss_merge_kernel(KArgs a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   MSmem& S = *reinterpret_cast<MSmem*>(smem_raw);
   uint64_t* stage = reinterpret_cast<uint64_t*>(smem_raw + kSmemFixed);
