@@ -10,6 +10,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import struct as _struct
 
 import numpy as np
 import torch
@@ -44,6 +45,12 @@ class _Params(C.Structure):
     ]
 
 
+# _Params as bytes: B, V, fourteen pointers, bitmask_ld, seed, position (one pack
+# call instead of nineteen ctypes fields)
+_PARAMS = _struct.Struct("=2i14Qq2Q")
+assert _PARAMS.size == C.sizeof(_Params)
+
+
 def lib():
     global _lib
     if _lib is None:
@@ -58,36 +65,36 @@ def lib():
         L.ss_topk.restype = i32
         L.ss_topk.argtypes = [vp, C.c_int, C.c_int, C.c_int, i64, vp, C.c_int, vp, vp, vp, vp, sz, vp]
         L.ss_sample.restype = i32
-        L.ss_sample.argtypes = [vp, C.c_int, i64, C.POINTER(_Params), C.c_int, vp, vp, vp, vp, C.c_int, vp,
+        L.ss_sample.argtypes = [vp, C.c_int, i64, vp, C.c_int, vp, vp, vp, vp, C.c_int, vp,
                                 vp, sz, vp]
         if hasattr(L, "ss_sample_full"):
             L.ss_sample_full.restype = i32
-            L.ss_sample_full.argtypes = [vp, C.c_int, i64, C.POINTER(_Params), C.c_int, vp, vp, vp, vp, C.c_int,
+            L.ss_sample_full.argtypes = [vp, C.c_int, i64, vp, C.c_int, vp, vp, vp, vp, C.c_int,
                                          vp, vp, sz, vp]
         if hasattr(L, "ss_sample_gumbel"):
             L.ss_sample_gumbel.restype = i32
-            L.ss_sample_gumbel.argtypes = [vp, C.c_int, i64, C.POINTER(_Params), C.c_int, vp, i64, vp, vp, vp, vp,
+            L.ss_sample_gumbel.argtypes = [vp, C.c_int, i64, vp, C.c_int, vp, i64, vp, vp, vp, vp,
                                            C.c_int, vp, vp, sz, vp]
         if hasattr(L, "ss_sample_noalloc"):
             L.ss_sample_noalloc.restype = i32
-            L.ss_sample_noalloc.argtypes = [vp, C.c_int, i64, C.POINTER(_Params), C.c_int, vp, vp, vp, vp, C.c_int,
+            L.ss_sample_noalloc.argtypes = [vp, C.c_int, i64, vp, C.c_int, vp, vp, vp, vp, C.c_int,
                                             vp, vp]
         L.ss_verify.restype = i32
-        L.ss_verify.argtypes = [vp, C.c_int, i64, vp, i64, vp, C.c_int, C.POINTER(_Params), C.c_int, vp, vp,
+        L.ss_verify.argtypes = [vp, C.c_int, i64, vp, i64, vp, C.c_int, vp, C.c_int, vp, vp,
                                 vp, vp, sz, vp]
         if hasattr(L, "ss_verify_tree"):
             L.ss_verify_tree.restype = i32
             L.ss_verify_tree.argtypes = [vp, C.c_int, i64, C.c_int, vp, vp, vp, C.c_int, vp, C.c_int,
-                                         C.POINTER(_Params), C.c_int, vp, vp, vp, vp, sz, vp]
+                                         vp, C.c_int, vp, vp, vp, vp, sz, vp]
         if hasattr(L, "ss_verify_sparse"):
             L.ss_verify_sparse.restype = i32
-            L.ss_verify_sparse.argtypes = [vp, C.c_int, i64, vp, vp, C.c_int, vp, C.c_int, C.POINTER(_Params),
+            L.ss_verify_sparse.argtypes = [vp, C.c_int, i64, vp, vp, C.c_int, vp, C.c_int, vp,
                                            C.c_int, vp, vp, vp, vp, sz, vp]
         if hasattr(L, "ss_logprobs"):
             L.ss_logprobs.restype = i32
-            L.ss_logprobs.argtypes = [vp, C.c_int, i64, C.POINTER(_Params), C.c_int, vp, vp, vp, vp, sz, vp]
+            L.ss_logprobs.argtypes = [vp, C.c_int, i64, vp, C.c_int, vp, vp, vp, vp, sz, vp]
         L.ss_process_logits.restype = i32
-        L.ss_process_logits.argtypes = [vp, C.c_int, i64, C.POINTER(_Params), C.c_int, vp, vp, vp, vp, sz, vp]
+        L.ss_process_logits.argtypes = [vp, C.c_int, i64, vp, C.c_int, vp, vp, vp, vp, sz, vp]
         L.ss_status_string.restype = C.c_char_p
         L.ss_status_string.argtypes = [i32]
         _lib = L
@@ -100,11 +107,12 @@ def _check(st):
 
 
 def _ptr(t):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # torch.cuda.current_stream().cuda_stream without the Stream object (3 us)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _dtype_code(t):
@@ -173,6 +181,18 @@ class Params:
             bitmask=_ptr(bm), bitmask_ld=0 if bm is None else int(bm.shape[-1]),
             seed=_ptr(self.seed), position=_ptr(self.position))
 
+    def packed(self):
+        """The bytes of ``struct()``, for one call."""
+        def ptr(t):
+            return 0 if t is None else t.data_ptr()
+
+        bm = self.bitmask
+        return _PARAMS.pack(
+            self.B, self.V, ptr(self.mode), ptr(self.temperature), ptr(self.top_k), ptr(self.top_p),
+            ptr(self.min_p), ptr(self.rep), ptr(self.freq), ptr(self.pres), ptr(self.hist_offsets),
+            ptr(self.hist_ids), ptr(self.bias_offsets), ptr(self.bias_ids), ptr(self.bias_vals), ptr(bm),
+            0 if bm is None else bm.shape[-1], ptr(self.seed), ptr(self.position))
+
 
 def _ws(ws, op, B, V, L, k_max, dtype, device):
     if ws is None:
@@ -204,8 +224,8 @@ def logprobs(logits, params, n_lp, out_idx=None, out_lp=None, flags=None, ws=Non
         out_idx = torch.empty(B, n_lp, dtype=torch.int32, device=logits.device)
     if out_lp is None:
         out_lp = torch.empty(B, n_lp, dtype=torch.float32, device=logits.device)
-    p = params.struct()
-    _check(lib().ss_logprobs(_ptr(logits), dt, logits.stride(0), C.byref(p), n_lp, _ptr(out_idx), _ptr(out_lp),
+    p = params.packed()
+    _check(lib().ss_logprobs(_ptr(logits), dt, logits.stride(0), p, n_lp, _ptr(out_idx), _ptr(out_lp),
                              _ptr(flags), _ptr(ws), ws.numel(), _stream()))
     return out_idx, out_lp
 
@@ -228,8 +248,8 @@ def sample(logits, params, k_max, k_out=0, out_token=None, out_logprob=None, out
             out_idx = torch.empty(B, k_out, dtype=torch.int32, device=dev)
         if out_prob is None:
             out_prob = torch.empty(B, k_out, dtype=torch.float32, device=dev)
-    p = params.struct()
-    _check(lib().ss_sample(_ptr(logits), dt, logits.stride(0), C.byref(p), k_max, _ptr(out_token),
+    p = params.packed()
+    _check(lib().ss_sample(_ptr(logits), dt, logits.stride(0), p, k_max, _ptr(out_token),
                            _ptr(out_logprob), _ptr(out_idx), _ptr(out_prob), k_out, _ptr(flags), _ptr(ws),
                            ws.numel(), _stream()))
     if k_out > 0:
@@ -256,8 +276,8 @@ def sample_full(logits, params, k_max, k_out=0, out_token=None, out_logprob=None
             out_idx = torch.empty(B, k_out, dtype=torch.int32, device=dev)
         if out_prob is None:
             out_prob = torch.empty(B, k_out, dtype=torch.float32, device=dev)
-    p = params.struct()
-    _check(lib().ss_sample_full(_ptr(logits), dt, logits.stride(0), C.byref(p), k_max, _ptr(out_token),
+    p = params.packed()
+    _check(lib().ss_sample_full(_ptr(logits), dt, logits.stride(0), p, k_max, _ptr(out_token),
                                 _ptr(out_logprob), _ptr(out_idx), _ptr(out_prob), k_out, _ptr(flags), _ptr(ws),
                                 ws.numel(), _stream()))
     if k_out > 0:
@@ -287,8 +307,8 @@ def sample_gumbel(logits, params, k_max, noise, k_out=0, out_token=None, out_log
             out_idx = torch.empty(B, k_out, dtype=torch.int32, device=dev)
         if out_prob is None:
             out_prob = torch.empty(B, k_out, dtype=torch.float32, device=dev)
-    p = params.struct()
-    _check(lib().ss_sample_gumbel(_ptr(logits), dt, logits.stride(0), C.byref(p), k_max, _ptr(noise), noise.stride(0),
+    p = params.packed()
+    _check(lib().ss_sample_gumbel(_ptr(logits), dt, logits.stride(0), p, k_max, _ptr(noise), noise.stride(0),
                                   _ptr(out_token), _ptr(out_logprob), _ptr(out_idx), _ptr(out_prob), k_out,
                                   _ptr(flags), _ptr(ws), ws.numel(), _stream()))
     if k_out > 0:
@@ -300,8 +320,8 @@ def sample_noalloc(logits, params, k_max, out_token, out_logprob, flags, k_out=0
     """ss_sample_noalloc: sampling into caller-provided outputs with the
     library's own per-GPU workspace (nothing is allocated by this call)."""
     B, V = logits.shape
-    p = params.struct()
-    _check(lib().ss_sample_noalloc(_ptr(logits), _dtype_code(logits), logits.stride(0), C.byref(p), k_max,
+    p = params.packed()
+    _check(lib().ss_sample_noalloc(_ptr(logits), _dtype_code(logits), logits.stride(0), p, k_max,
                                    _ptr(out_token), _ptr(out_logprob), _ptr(out_idx), _ptr(out_prob), k_out,
                                    _ptr(flags), _stream()))
     return out_token, out_logprob, flags
@@ -323,9 +343,9 @@ def verify(target_logits, draft_probs, draft_tokens, params, k_max, out_tokens=N
         flags = torch.empty(B, dtype=torch.int32, device=dev)
     if target_logits.stride(0) != L1 * target_logits.stride(1) or draft_probs.stride(0) != L * draft_probs.stride(1):
         raise SSError("target rows and draft rows must be evenly strided")
-    p = params.struct()
+    p = params.packed()
     _check(lib().ss_verify(_ptr(target_logits), dt, target_logits.stride(1), _ptr(draft_probs),
-                           draft_probs.stride(1), _ptr(draft_tokens), L, C.byref(p), k_max, _ptr(out_tokens),
+                           draft_probs.stride(1), _ptr(draft_tokens), L, p, k_max, _ptr(out_tokens),
                            _ptr(out_nacc), _ptr(flags), _ptr(ws), ws.numel(), _stream()))
     return out_tokens, out_nacc, flags
 
@@ -351,9 +371,9 @@ def verify_sparse(target_logits, draft_idx, draft_q, draft_tokens, params, k_max
     for t, dtype in ((draft_idx, torch.int32), (draft_q, torch.float32)):
         if t.shape != (B, L, kq) or t.dtype != dtype or not t.is_contiguous():
             raise SSError("draft lists must be contiguous [B, L, kq] int32 ids and float32 probabilities")
-    p = params.struct()
+    p = params.packed()
     _check(lib().ss_verify_sparse(_ptr(target_logits), dt, target_logits.stride(1), _ptr(draft_idx), _ptr(draft_q),
-                                  kq, _ptr(draft_tokens), L, C.byref(p), k_max, _ptr(out_tokens), _ptr(out_nacc),
+                                  kq, _ptr(draft_tokens), L, p, k_max, _ptr(out_tokens), _ptr(out_nacc),
                                   _ptr(flags), _ptr(ws), ws.numel(), _stream()))
     return out_tokens, out_nacc, flags
 
@@ -382,9 +402,9 @@ def verify_tree(target_logits, row_map, draft_idx, draft_q, draft_tokens, params
     for t, dtype in ((draft_idx, torch.int32), (draft_q, torch.float32)):
         if t.shape != (B, L, kq) or t.dtype != dtype or not t.is_contiguous():
             raise SSError("draft lists must be contiguous [B, L, kq] int32 ids and float32 probabilities")
-    p = params.struct()
+    p = params.packed()
     _check(lib().ss_verify_tree(_ptr(target_logits), dt, target_logits.stride(1), Lt, _ptr(row_map), _ptr(draft_idx),
-                                _ptr(draft_q), kq, _ptr(draft_tokens), L, C.byref(p), k_max, _ptr(out_tokens),
+                                _ptr(draft_q), kq, _ptr(draft_tokens), L, p, k_max, _ptr(out_tokens),
                                 _ptr(out_nacc), _ptr(flags), _ptr(ws), ws.numel(), _stream()))
     return out_tokens, out_nacc, flags
 
@@ -401,8 +421,8 @@ def process_logits(logits, params, k_max, out_logits=None, out_probs=None, flags
         out_probs = torch.empty(B, V, dtype=torch.float32, device=dev)
     if flags is None:
         flags = torch.empty(B, dtype=torch.int32, device=dev)
-    p = params.struct()
-    _check(lib().ss_process_logits(_ptr(logits), dt, logits.stride(0), C.byref(p), k_max, _ptr(out_logits),
+    p = params.packed()
+    _check(lib().ss_process_logits(_ptr(logits), dt, logits.stride(0), p, k_max, _ptr(out_logits),
                                    _ptr(out_probs), _ptr(flags), _ptr(ws), ws.numel(), _stream()))
     return out_logits, out_probs, flags
 
