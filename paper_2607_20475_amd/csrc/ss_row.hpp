@@ -655,13 +655,19 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
   const size_t gu = (size_t)row * U + u;
   const uint4* region = a.cand + gu * (size_t)a.cap;
   const uint4 r4 = a.rec[gu];
-  uint32_t cw[4 * NQM];
+  // the candidates as stored: bf16 words, fp32 composites
+  std::conditional_t<DT == SS_BF16, uint32_t, uint64_t> cw[NQM * EPQ];
   auto load_one = [&](int j, int at) {
     const uint4 q = region[min(at, a.cap - 1)];
-    cw[4 * j] = q.x;
-    cw[4 * j + 1] = q.y;
-    cw[4 * j + 2] = q.z;
-    cw[4 * j + 3] = q.w;
+    if constexpr (DT == SS_BF16) {
+      cw[4 * j] = q.x;
+      cw[4 * j + 1] = q.y;
+      cw[4 * j + 2] = q.z;
+      cw[4 * j + 3] = q.w;
+    } else {
+      cw[2 * j] = ((uint64_t)q.y << 32) | q.x;
+      cw[2 * j + 1] = ((uint64_t)q.w << 32) | q.z;
+    }
   };
   auto load_batch = [&](int batch) {
 #pragma unroll
@@ -835,7 +841,7 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
   const uint32_t ubase = ~(uint32_t)(u * kUE) - 0xFFFFu;
   auto elem = [&](int x) -> uint64_t {
     if constexpr (DT == SS_BF16) return ((uint64_t)(cw[x] & 0xFFFF0000u) << 32) | (ubase + (cw[x] & 0xFFFFu));
-    else return ((uint64_t)cw[2 * x + 1] << 32) | cw[2 * x];
+    else return cw[x];
   };
   // bf16: tc as a stored word of this thread's unit
   uint32_t wthr = tck;
