@@ -286,6 +286,68 @@ def test_greedy_patched_maxima(ssb, dtype):
     assert np.array_equal(tok, ref["token"]), f"greedy-patched-{dtype}"
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_greedy_refill_ragged_vocab(ssb, dtype):
+    """Greedy rows whose maximum is penalised, at a vocabulary above the exact
+    bitmap (2^17) whose last 16-byte chunk is partial: the unit to re-read is the
+    last one, the first one or several, with and without a grammar mask."""
+    rng = np.random.default_rng(77)
+    B, V = 12, 140001
+    xf = rng.normal(0.0, 1.0, (B, V))
+    hist, mask = [], np.full((B, (V + 31) // 32), 0xFFFFFFFF, np.uint32)
+    mode = np.full(B, W.MODE_GREEDY | W.MODE_REP, np.uint32)
+    for r in range(B):
+        top = [[V - 1], [V - 2, V - 1], [0, 1, V - 3], list(rng.choice(V, 30, replace=False))][r % 4]
+        xf[r, top] += 9.0
+        near = [V - 4, 2, V - 1 if r % 4 == 2 else V - 5, 3][r % 4]  # the answer sits beside a penalised one
+        xf[r, near] = 5.5 + 0.125 * r
+        hist.append(np.concatenate([top, rng.integers(0, V, 40)]).astype(np.int32))
+        if r >= 8:
+            mask[r, ::2] = 0
+            mode[r] |= W.MODE_GRAMMAR
+    x = xf.astype(np.float32)
+    if dtype == "bf16":
+        x = W.bf16_bits_from_f32(x)
+    hoff = np.concatenate([[0], np.cumsum([len(h) for h in hist])]).astype(np.int32)
+    inp = W.custom_rows(x, dtype=W.BF16 if dtype == "bf16" else W.F32, k_max=64, mode=mode,
+                        rep=np.full(B, 8.0, np.float32), hist_offsets=hoff, hist_ids=np.concatenate(hist), bitmask=mask)
+    tok, lp, fl = run_sample(ssb, inp)
+    ref = check_sample(inp, tok, lp, fl, f"greedy-refill-{dtype}")
+    assert np.array_equal(tok, ref["token"])
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("V,offset", [(4099, 1), (40007, 3), (2048, 1), (7, 0)])
+def test_rows_at_any_address(ssb, dtype, V, offset):
+    """Rows of odd length that start at odd element addresses, through the
+    streaming loads and the materialising pass's loads and stores."""
+    rng = np.random.default_rng(V)
+    B = 5
+    xf = rng.normal(0.0, 2.0, (B, V)).astype(np.float32)
+    x = W.bf16_bits_from_f32(xf) if dtype == "bf16" else xf
+    hist = [rng.integers(0, V, 20).astype(np.int32) for _ in range(B)]
+    mode = np.full(B, W.MODE_TEMP | W.MODE_TOPK | W.MODE_TOPP | W.MODE_REP, np.uint32)
+    mode[0] = W.MODE_GREEDY
+    inp = W.custom_rows(x, dtype=W.BF16 if dtype == "bf16" else W.F32, k_max=50, mode=mode,
+                        temperature=np.full(B, 0.8), top_k=np.full(B, min(30, V)), top_p=np.full(B, 0.9),
+                        rep=np.full(B, 1.2), hist_offsets=np.arange(B + 1) * 20, hist_ids=np.concatenate(hist))
+    src = ssb.logits_tensor(inp)
+    buf = torch.empty(B * V + 8, dtype=src.dtype, device="cuda")
+    at = buf[offset:offset + B * V].view(B, V)
+    at.copy_(src)
+    prm = ssb.Params.from_arrays(inp)
+    r = ssb.sample(at, prm, inp["k_max"])
+    out = torch.empty(2, B * V + 8, device="cuda")
+    y, P = (o[offset:offset + B * V].view(B, V) for o in out)
+    ssb.process_logits(at, prm, inp["k_max"], out_logits=y, out_probs=P)
+    torch.cuda.synchronize()
+    check_sample(inp, _np(r[0]), _np(r[1]), _np(r[2]), f"address-{V}-{dtype}")
+    ref = oracle.process_logits(inp)
+    assert np.array_equal(_np(y).view(np.uint32), ref["y"].view(np.uint32))
+    sure = ref["ns_range"][:, 0] == ref["ns_range"][:, 1]
+    assert np.all(np.abs(_np(P)[sure] - ref["P"][sure]) <= 1e-5 * ref["P"][sure] + 1e-38)
+
+
 def test_sample_large_vocab_patched(ssb):
     """V = 2^18 bf16 with penalties and bias: the patched-id bitmap is hashed
     above 2^17 ids, so pooled raw copies are checked against the hash table."""
@@ -879,6 +941,36 @@ def test_verify_edge_cases(ssb):
     say("[verify-edge] B=12 L=3 V=5000")
     out, nacc, fl = run_verify(ssb, inp)
     check_verify(inp, out, nacc, fl, "verify-edge")
+
+
+@pytest.mark.parametrize("L", [1, 16])
+def test_verify_request_assembly(ssb, L):
+    """A request's outputs are written by its last merged row, for the shortest
+    and the longest draft: acceptances to the end, rejections at every
+    position, greedy and stochastic requests, drafts that end early."""
+    rng = np.random.default_rng(60 + L)
+    B, V = 21, 2500
+    t = rng.normal(0, 1.0, (B, L + 1, V)).astype(np.float32)
+    best = t.argmax(2).astype(np.int32)
+    d = best[:, :L].copy()
+    q = np.full((B, L, V), 1e-9, np.float32)
+    for b in range(B):
+        stop = b % (L + 2)  # this position rejects (none from L on)
+        for l in range(L):
+            if l == stop:
+                d[b, l] = int(t[b, l].argmin())
+            q[b, l, d[b, l]] = 1.0 if l == stop else 1e-9  # a likely draft of a tiny P, or a sure acceptance
+    if L > 2:
+        d[4, 2] = -1
+    mode = np.where(np.arange(B) % 3 == 0, W.MODE_GREEDY, W.MODE_TEMP | W.MODE_TOPK | W.MODE_TOPP)
+    inp = W.custom_rows(t[:, 0], W.F32, k_max=64, mode=mode, temperature=np.full(B, 0.7), top_k=np.full(B, 40),
+                        top_p=np.full(B, 0.9), position=np.arange(B) * 5)
+    inp.update(x=t, B=B, L=L, draft_probs=q, draft_tokens=d)
+    say(f"[verify-assembly] B={B} L={L} V={V}")
+    for _ in range(2):  # the arrival counts start over with each call
+        out, nacc, fl = run_verify(ssb, inp)
+        check_verify(inp, out, nacc, fl, f"verify-assembly-{L}")
+    assert nacc.min() == 0 and nacc.max() == L
 
 
 def test_verify_grammar(ssb):
