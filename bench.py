@@ -169,7 +169,7 @@ def load_profile(name):
 # rocprofv3 summaries -> profiles/kernels.json
 # ---------------------------------------------------------------------------
 def _kernel_key(n):
-    for k in ("ss_stream_kernel", "ss_merge_kernel", "ss_assemble_kernel", "ss_materialize_kernel",
+    for k in ("ss_stream_kernel", "ss_merge_kernel", "ss_materialize_kernel",
               "bench_read_kernel", "bench_write_kernel"):
         if k in n:
             return n[:n.index("(")] if "(" in n else n

@@ -772,7 +772,7 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
   }
 
   // 2. largest threshold, row maximum, longest candidate list; the patch table
-  const uint32_t cnt = (act && r4.y != kOvf) ? r4.y : 0u;
+  uint32_t cnt = (act && r4.y != kOvf) ? r4.y : 0u;
   if (act && r4.y == kOvf) atomicOr(&S.rmask[u >> 5], 1u << (u & 31));
   uint32_t hfmax = 0u;
   if (pst == 1) {
@@ -948,8 +948,12 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
     if (__builtin_expect(!many, 1)) {
       with_nq([&](auto nq) { count(nq, 0); });
     } else {
+      // a unit whose first possible element lies below tc has nothing to give
+      // (rows tied at their threshold: every unit but the first ones)
+      if (comp_of(r4.z, (uint32_t)(u * kUE)) < tc) cnt = 0u;
 #pragma unroll 1
       for (int batch = 0; batch < nbatch; ++batch) {
+        if (__ballot(cnt > (uint32_t)(batch * NQM * tpu * EPQ)) == 0ull) break;
         load_batch(batch);
         count(all, batch);
       }
@@ -1022,6 +1026,7 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
         } else {
 #pragma unroll 1
           for (int batch = 0; batch < nbatch; ++batch) {
+            if (__ballot(cnt > (uint32_t)(batch * NQM * tpu * EPQ)) == 0ull) break;
             load_batch(batch);
             sel = select(all, batch);
 #pragma unroll
