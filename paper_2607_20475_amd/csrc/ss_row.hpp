@@ -657,8 +657,11 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
   const uint4 r4 = a.rec[gu];
   // the candidates as stored: bf16 words, fp32 composites
   std::conditional_t<DT == SS_BF16, uint32_t, uint64_t> cw[NQM * EPQ];
+  // whose candidates this thread looks at: its share of its unit's
+  const uint4* sreg = region;
+  int stpu = tpu, ssub = sub;
   auto load_one = [&](int j, int at) {
-    const uint4 q = region[min(at, a.cap - 1)];
+    const uint4 q = sreg[min(at, a.cap - 1)];
     if constexpr (DT == SS_BF16) {
       cw[4 * j] = q.x;
       cw[4 * j + 1] = q.y;
@@ -671,7 +674,7 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
   };
   auto load_batch = [&](int batch) {
 #pragma unroll
-    for (int j = 0; j < NQM; ++j) load_one(j, (batch * NQM + j) * tpu + sub);
+    for (int j = 0; j < NQM; ++j) load_one(j, (batch * NQM + j) * stpu + ssub);
   };
 #pragma unroll
   for (int j = 0; j < NQM; ++j)
@@ -838,18 +841,19 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
     else f(std::integral_constant<int, NQM>{});
   };
   // composite of candidate x = EPQ j + e
-  const uint32_t ubase = ~(uint32_t)(u * kUE) - 0xFFFFu;
+  uint32_t ubase = ~(uint32_t)(u * kUE) - 0xFFFFu;
   auto elem = [&](int x) -> uint64_t {
     if constexpr (DT == SS_BF16) return ((uint64_t)(cw[x] & 0xFFFF0000u) << 32) | (ubase + (cw[x] & 0xFFFFu));
     else return cw[x];
   };
   // bf16: tc as a stored word of this thread's unit
-  uint32_t wthr = tck;
-  if constexpr (DT == SS_BF16) {
-    const uint32_t lo = (uint32_t)(u * kUE);
+  auto word_threshold = [&](int v) -> uint32_t {
+    const uint32_t lo = (uint32_t)(v * kUE);
     const uint32_t in = tcut - lo < (uint32_t)kUE ? tck | (0xFFFFu - (tcut - lo)) : tck;
-    wthr = tcut < lo ? tck + 0x10000u : in;
-  }
+    return tcut < lo ? tck + 0x10000u : in;
+  };
+  uint32_t wthr = word_threshold(u);
+  uint32_t scnt = cnt;
   // the candidates of a batch that are at or above tc and no raw copy of a
   // patched id (every LDS read is issued before any is used)
   auto select = [&](auto nq, int batch) -> uint32_t {
@@ -857,7 +861,7 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
     uint32_t sel = 0u;
 #pragma unroll
     for (int j = 0; j < NQ; ++j) {
-      const int rem = (int)cnt - ((batch * NQ + j) * tpu + sub) * EPQ;
+      const int rem = (int)scnt - ((batch * NQ + j) * stpu + ssub) * EPQ;
 #pragma unroll
       for (int e = 0; e < EPQ; ++e) {
         bool at;
@@ -945,18 +949,43 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
         if (((sel >> x) & 1u) && bp[x] < nB) stage[bp[x]] = elem(x);
     };
     constexpr auto all = std::integral_constant<int, NQM>{};
+    // f(batch) for every batch of candidates when there are many: each thread
+    // walks its share of its unit, or, when lists are far longer than that (rows
+    // tied at their threshold), each wavefront whole units.  A unit whose first
+    // possible element lies below tc has nothing to give (of a tied row, every
+    // unit but the first ones).
+    auto walk = [&](auto&& f) {
+      if (nbatch <= 4) {
+        if (comp_of(r4.z, (uint32_t)(u * kUE)) < tc) scnt = 0u;
+#pragma unroll 1
+        for (int batch = 0; batch < nbatch; ++batch) {
+          if (__ballot(scnt > (uint32_t)(batch * NQM * tpu * EPQ)) == 0ull) break;
+          load_batch(batch);
+          f(batch);
+        }
+        return;
+      }
+      stpu = 64;
+      ssub = ln;
+#pragma unroll 1
+      for (int v = wv; v < U; v += NW) {
+        const uint4 q4 = a.rec[(size_t)row * U + v];
+        if (q4.x == kNoEmit || comp_of(q4.z, (uint32_t)(v * kUE)) < tc) continue;
+        scnt = q4.y;
+        sreg = a.cand + ((size_t)row * U + v) * (size_t)a.cap;
+        ubase = ~(uint32_t)(v * kUE) - 0xFFFFu;
+        wthr = word_threshold(v);
+#pragma unroll 1
+        for (int batch = 0; batch * NQM * 64 * EPQ < (int)scnt; ++batch) {
+          load_batch(batch);
+          f(batch);
+        }
+      }
+    };
     if (__builtin_expect(!many, 1)) {
       with_nq([&](auto nq) { count(nq, 0); });
     } else {
-      // a unit whose first possible element lies below tc has nothing to give
-      // (rows tied at their threshold: every unit but the first ones)
-      if (comp_of(r4.z, (uint32_t)(u * kUE)) < tc) cnt = 0u;
-#pragma unroll 1
-      for (int batch = 0; batch < nbatch; ++batch) {
-        if (__ballot(cnt > (uint32_t)(batch * NQM * tpu * EPQ)) == 0ull) break;
-        load_batch(batch);
-        count(all, batch);
-      }
+      walk([&](int batch) { count(all, batch); });
     }
     // patched final values at or above tc
     uint32_t fsel = 0u;
@@ -1024,15 +1053,12 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
         if (__builtin_expect(!many, 1)) {
           with_nq([&](auto nq) { place(nq); });
         } else {
-#pragma unroll 1
-          for (int batch = 0; batch < nbatch; ++batch) {
-            if (__ballot(cnt > (uint32_t)(batch * NQM * tpu * EPQ)) == 0ull) break;
-            load_batch(batch);
+          walk([&](int batch) {
             sel = select(all, batch);
 #pragma unroll
             for (int x = 0; x < NE; ++x) bp[x] = grid_bin(x);
             place(all);
-          }
+          });
         }
         if (fsel != 0u) {
 #pragma unroll
