@@ -1,9 +1,8 @@
 // ss_impl.hpp -- device implementation shared by the kernel translation units.
 //
-// Two launches per call (plus a verification assembly or a materialising
-// pass for ss_verify / ss_process_logits); the grids depend only on the
-// shapes, nothing synchronises with the host, so every call can be captured
-// in a HIP graph.
+// Two launches per call (plus the materialising pass of ss_process_logits); the
+// grids depend only on the shapes, nothing synchronises with the host, so every
+// call can be captured in a HIP graph.
 //
 // Streaming kernel.  Every wavefront owns one "unit": 2048 consecutive logits
 // of one row (16-byte loads, 32 elements per lane, read exactly once).  It
