@@ -795,7 +795,10 @@ __device__ __forceinline__ void scan_unit(const KArgs& a, int gu, WStage& W) {
       for (int g = 0; g < 8; ++g) gk[g] = make_uint2(kd[2 * g], kd[2 * g + 1]);
       count = emit_elems<DT>(gk, gmask, off, total, t16, (uint32_t)lo, region, W);
     }
-    t = t16 >= 0x10000u ? kNoEmit : (t16 << 16);
+    // a unit that emitted all it has states the lowest valid key: patched finals are
+    // float32 and may lie below every finite bf16 value (a bias of -FLT_MAX)
+    const bool whole = t16 == 0x0081u && cut == 0xFFFFFFFFu;
+    t = t16 >= 0x10000u ? kNoEmit : (whole ? kKeyFloor : t16 << 16);
     wm = wm16 << 16;
   } else {
     uint32_t kk[32];

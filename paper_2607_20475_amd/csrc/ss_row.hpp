@@ -1036,8 +1036,7 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
       if (total < (uint32_t)want) {
         // at the lowest threshold there is the list is the whole row (few
         // tokens allowed by a grammar); otherwise elements may be missing
-        constexpr uint32_t lowest = DT == SS_BF16 ? 0x00810000u : kKeyFloor;  // smallest valid key
-        if (tc <= comp_of(lowest, kNone)) want = (int)total;
+        if (tc <= comp_of(kKeyFloor, kNone)) want = (int)total;
         else slow = true;
       }
 #pragma unroll

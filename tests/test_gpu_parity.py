@@ -1164,6 +1164,106 @@ def test_verify_tree_edge_cases(ssb, dtype):
 
 
 # --------------------------------------------------------------------------
+# Lowest finite values
+# --------------------------------------------------------------------------
+FLT_MAX = float(np.finfo(np.float32).max)
+BF16_MIN = -3.3895313892515355e38  # torch.finfo(torch.bfloat16).min
+
+
+def _banned_rows(dtype, seed=5):
+    """Rows whose lists reach the lowest finite values: a bias of -FLT_MAX (the usual
+    ban) leaves finals of -FLT_MAX, below every finite bf16 value but valid.
+    Rows 0 and 6: every allowed id is banned.  1: two of five are.  2: two of
+    twenty, beside raw elements at bf16's lowest value and finals between
+    that and -FLT_MAX.  3: the whole row at bf16's lowest value but for ten ids (more
+    ties than a unit stores), some finals below.  4: one allowed id, banned.
+    5: greedy, every allowed id banned."""
+    rng = np.random.default_rng(seed)
+    B, V = 7, 4500
+    x = rng.normal(0.0, 2.0, (B, V)).astype(np.float32)
+    mask = np.zeros((B, (V + 31) // 32), np.uint32)
+    allow = [[5, 2100, 4499], [7, 900, 901, 3000, 4400], list(range(10, 4500, 230)), None, [4100], [3, 2049], [64, 65]]
+    ban = [[5, 2100, 4499], [900, 4400], [240, 4150], [], [4100], [3, 2049], [64, 65]]
+    bias = [{i: -FLT_MAX for i in b} for b in ban]
+    x[2, [470, 700, 930]] = BF16_MIN
+    x[2, [1160, 1390]] = BF16_MIN
+    bias[2].update({1160: -1e36, 1390: -1e36})
+    keep = x[3, ::450].copy()
+    x[3] = BF16_MIN
+    x[3, ::450] = keep
+    bias[3] = {1: -1e36, 2: -1e36, 450: -FLT_MAX}
+    for r in range(B):
+        for i in (range(V) if allow[r] is None else allow[r]):
+            mask[r, i >> 5] |= np.uint32(1 << (i & 31))
+    mode = np.full(B, W.MODE_TEMP | W.MODE_TOPK | W.MODE_BIAS | W.MODE_GRAMMAR, np.uint32)
+    mode[5] = W.MODE_GREEDY | W.MODE_BIAS | W.MODE_GRAMMAR
+    inp = W.custom_rows(x if dtype == W.F32 else W.bf16_bits_from_f32(x), dtype, k_max=64, mode=mode,
+                        temperature=np.ones(B), top_k=np.full(B, 50), bitmask=mask,
+                        bias_offsets=np.concatenate([[0], np.cumsum([len(b) for b in bias])]),
+                        bias_ids=np.concatenate([list(b.keys()) for b in bias]),
+                        bias_vals=np.concatenate([list(b.values()) for b in bias]))
+    return inp
+
+
+def _short_banned_rows(dtype):
+    """A vocabulary shorter than the list, no grammar, some ids banned."""
+    rng = np.random.default_rng(6)
+    B, V = 3, 40
+    x = rng.normal(0.0, 2.0, (B, V)).astype(np.float32)
+    mode = np.full(B, W.MODE_TEMP | W.MODE_TOPK | W.MODE_BIAS, np.uint32)
+    return W.custom_rows(x if dtype == W.F32 else W.bf16_bits_from_f32(x), dtype, k_max=64, mode=mode,
+                         temperature=np.ones(B), top_k=np.full(B, 60), bias_offsets=[0, 3, 6, 7],
+                         bias_ids=[0, 17, 39, 1, 2, 3, 20], bias_vals=np.full(7, -FLT_MAX))
+
+
+@pytest.mark.parametrize("dtype", [W.F32, W.BF16])
+@pytest.mark.parametrize("rows", [_banned_rows, _short_banned_rows])
+def test_finals_below_the_lowest_bf16_value(ssb, rows, dtype):
+    inp = rows(dtype)
+    label = f"{rows.__name__[1:]}-{dtype}"
+    k_out = 64
+    tok, lp, fl, idx, prob = run_sample(ssb, inp, k_out=k_out)
+    check_sample(inp, tok, lp, fl, label)
+    # the kept list: the k leading valid tokens (no top-p or min-p here)
+    ref = oracle.process_logits(inp)
+    for b in range(inp["B"]):
+        y = ref["y"][b]
+        n = 1 if inp["mode"][b] & W.MODE_GREEDY else min(int(inp["top_k"][b]), int((y > -np.inf).sum()))
+        order = np.lexsort((np.arange(inp["V"]), -y.astype(np.float64)))[:n]
+        assert np.array_equal(idx[b, :n], order) and np.all(idx[b, n:] == -1), (label, b)
+        np.testing.assert_allclose(prob[b, :n], ref["P"][b][order], rtol=1e-5, atol=1e-30)
+    y, P, _ = ssb.process_logits(ssb.logits_tensor(inp), ssb.Params.from_arrays(inp), inp["k_max"])
+    torch.cuda.synchronize()
+    assert np.array_equal(_np(y).view(np.uint32), ref["y"].view(np.uint32))
+    np.testing.assert_allclose(_np(P), ref["P"], rtol=1e-5, atol=1e-38)
+    # log-probabilities of the rows that have an unbanned token
+    inp["mode"] = (inp["mode"] & ~np.uint32(W.MODE_GREEDY)) | np.uint32(W.MODE_LOGPROBS)
+    if inp["V"] > 64:
+        inp["mode"][[0, 4, 5, 6]] &= ~np.uint32(W.MODE_LOGPROBS)
+    check_logprobs(ssb, inp, 50, f"{label}-logprobs")
+
+
+@pytest.mark.parametrize("dtype", [W.F32, W.BF16])
+def test_verify_with_every_allowed_id_banned(ssb, dtype):
+    """Target rows whose allowed ids all carry a -FLT_MAX bias: drafts among and
+    beside them, corrections and the bonus token."""
+    rows = _banned_rows(dtype)
+    L, V, r = 1, rows["V"], np.array([0, 6, 1, 0, 2, 3])  # three requests of two rows
+    B = len(r) // (L + 1)
+    inp = W.custom_rows(rows["x"][r[:B]], dtype, k_max=64, mode=np.full(B, rows["mode"][0]),
+                        temperature=np.full(B, 0.8), top_k=np.full(B, 50), bias_offsets=np.arange(B + 1) * 7,
+                        bias_ids=np.tile([5, 2100, 4499, 64, 65, 900, 4400], B), bias_vals=np.full(7 * B, -FLT_MAX))
+    inp["bitmask"] = rows["bitmask"][r]
+    q = np.full((B, L, V), 1e-6, np.float32)
+    inp.update(x=rows["x"][r].reshape(B, L + 1, V), B=B, L=L, draft_probs=q,
+               draft_tokens=np.array([[2100], [11], [5]], np.int32))
+    say(f"[verify-banned-{dtype}]")
+    out, nacc, fl = run_verify(ssb, inp)
+    check_verify(inp, out, nacc, fl, f"verify-banned-{dtype}")
+    assert nacc[0] == 1 and out[0, 1] in (64, 65)
+
+
+# --------------------------------------------------------------------------
 # Graph capture and determinism
 # --------------------------------------------------------------------------
 def test_graph_replay_matches_eager(ssb):
