@@ -600,6 +600,43 @@ __device__ __forceinline__ double row_norm_all(const KArgs& a, const Ctx& c, con
   return z;
 }
 
+// This thread's share of the normaliser terms, relative to M, of the n units listed in
+// `units`, ids in the LDS patch table left out.  The workgroup reads a unit at a time,
+// a few consecutive logits per thread, the next unit's loads ahead of this one's terms.
+template <int DT, int BS>
+__device__ __forceinline__ double units_norm(const KArgs& a, const MSmem& S, int row, uint32_t mode,
+                                             const uint32_t* units, int n, float M, float c) {
+  constexpr int VE = kUE / BS, ES = DTT<DT>::ES;
+  static_assert(32 % VE == 0, "a thread's logits share a word of the mask");
+  const unsigned char* xrow = reinterpret_cast<const unsigned char*>(a.x) + (size_t)row * (size_t)a.ld * ES;
+  const uint32_t* mask = (mode & SS_GRAMMAR) ? a.bitmask + (size_t)row * (size_t)a.mask_ld : nullptr;
+  const bool pexact = a.V <= kPB;
+  uint32_t x[VE], mw = 0u, nx[VE], nmw = 0u;  // raw bits and allow bits, of this unit and the next
+  auto load = [&](int j, uint32_t (&r)[VE], uint32_t& m) {
+    const int i0 = (int)uniform(units[j]) * kUE + (int)threadIdx.x * VE;
+    m = i0 < a.V ? (mask ? mask[i0 >> 5] >> (i0 & 31) : kNone) : 0u;
+#pragma unroll
+    for (int e = 0; e < VE; ++e) r[e] = load_elem_bits<DT>(xrow, min(i0 + e, a.V - 1));
+#pragma unroll
+    for (int e = 0; e < VE; ++e) m &= i0 + e < a.V ? ~0u : ~(1u << e);
+  };
+  double z = 0.0;
+  load(0, x, mw);
+#pragma unroll 1
+  for (int j = 0; j < n; ++j) {
+    if (j + 1 < n) load(j + 1, nx, nmw);
+    const int i0 = (int)uniform(units[j]) * kUE + (int)threadIdx.x * VE;
+#pragma unroll
+    for (int e = 0; e < VE; ++e) {
+      const bool in = ((mw >> e) & 1u) && !lds_patched(S, i0 + e, pexact);
+      z += in ? (double)lp_term(__uint_as_float(x[e]), M, c) : 0.0;  // -inf and NaN give zero
+      x[e] = nx[e];
+    }
+    mw = nmw;
+  }
+  return z;
+}
+
 // Sums of the NW wave totals in scratch: of those before this wave, and of all
 // (one read and a few DPP steps per lane instead of a loop over the waves).
 template <int NW, typename T>
@@ -745,6 +782,7 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
     S.bc[2] = kNone;  // top-p: last rank kept
     S.bc[3] = kNone;  // min-p: first rank dropped
     S.bc[7] = kNone;  // top-p against the whole row: last rank kept
+    S.bc[10] = 0u;    // normaliser: units to sum again
     S.bc64[3] = 0ull;
     S.best = 0ull;
   }
@@ -1126,20 +1164,35 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
   // The row's normaliser relative to M: the units' sums (taken relative to each
   // unit's raw maximum) rescaled, each patched id's raw term replaced by its
   // final value's.  The units' factors go through the bins' memory.
+  // A unit whose raw maximum lies above M by more than ln kLead owes it to patched
+  // ids: their terms would be taken from a sum that holds little else (a lead of 36
+  // leaves nothing of the rest, one of 710 overflows), so it is summed again from
+  // the logits, relative to M and without them.  Below that, what the subtraction
+  // leaves is off by at most kLead 2^-46 of Z, and the terms' exponents by ln kLead
+  // float32 roundings more than those of other units.  One such unit in every row costs
+  // 1 us: log-probabilities at B=32 V=2^17 17.6 -> 18.3 us, full-row sampling 22.6 -> 23.6.
   auto row_norm = [&](double M, float tauf) -> double {
     const double tau2 = (double)tauf;
     double z = 0.0;
     if (__builtin_expect(pmode <= 1, 1)) {
+      constexpr double kLead = 16.0;
       const float c2 = lp_scale(tauf);
       double* uf = reinterpret_cast<double*>(S.bins);
       float* um = reinterpret_cast<float*>(S.bins + 2 * kMaxU);
-      static_assert(3 * kMaxU <= kNB, "unit factors and maxima over the bins");
+      uint32_t* again = S.bins + 3 * kMaxU;  // units to sum again
+      static_assert(4 * kMaxU <= kNB, "unit factors, maxima and the list of units over the bins");
       if (act && sub == 0) {
         const float mu = float_of_key(r4.z);
-        const double f = r4.z >= kKeyFloor ? exp(((double)mu - M) / tau2) : 0.0;
+        const bool some = r4.z >= kKeyFloor;
+        double f = some ? exp(((double)mu - M) / tau2) : 0.0;
+        if (pmode == 1 && f > kLead) {
+          again[atomicAdd(&S.bc[10], 1u)] = (uint32_t)u;
+          f = 0.0;
+        } else if (some) {
+          z = f * us;
+        }
         uf[u] = f;
         um[u] = mu;
-        if (r4.z >= kKeyFloor) z = f * us;
       }
       lds_barrier();
       if (pmode == 1) {
@@ -1156,6 +1209,8 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
             if (fk[q] >= kKeyFloor) z += exp(((double)float_of_key(fk[q]) - M) / tau2);
           }
         }
+        const int n = (int)uniform(S.bc[10]);
+        if (__builtin_expect(n > 0, 0)) z += units_norm<DT, BS>(late_args(), S, row, mode, again, n, (float)M, c2);
       }
     } else {
       z = row_norm_all<DT, BS>(a, c, S, pmode, pg, M, tau2);

@@ -1264,6 +1264,54 @@ def test_verify_with_every_allowed_id_banned(ssb, dtype):
 
 
 # --------------------------------------------------------------------------
+# Normaliser of rows whose largest raw logits are penalised
+# --------------------------------------------------------------------------
+def _dominated_rows(dtype, V, seed=17):
+    """Rows whose units are led by ids that the request's lists pull far down: by
+    a bias, by frequency counts and by repetition; one such id, several of one unit
+    and one in every unit; with a grammar mask over the rest; every allowed id
+    banned; and a lead that the penalty does not undo."""
+    rng = np.random.default_rng(seed + V)
+    B = 12
+    x = rng.normal(0.0, 1.0, (B, V)).astype(np.float32)
+    nU = (V + 2047) // 2048
+    every = np.minimum(np.arange(nU) * 2048 + 1500, V - 1)
+    # (ids, lead, temperature, bias, occurrences)
+    spec = [([7], 30, 1.0, -100, 0), ([V - 1], 36, 1.0, -100, 0), ([V // 2], 12, 0.3, -100, 0), ([5], 60, 0.05, -100, 0),
+            ([1, 2, 3], 25, 0.5, -60, 0), (every, 40, 0.8, -80, 0), ([9], 50, 1.0, 0, 300), ([4, V - 2], 20, 0.3, 0, 90),
+            ([11], 40, 0.7, -100, 0), ([13], 3, 0.9, -FLT_MAX, 0), ([17], 30, 1.0, -5, 0), ([19], 45, 0.4, -FLT_MAX, 2)]
+    mask = np.full((B, (V + 31) // 32), 0xFFFFFFFF, np.uint32)
+    mask[8, ::2] = 0
+    mask[8, 0] |= np.uint32(1 << 11)
+    mask[9] = 0
+    mask[9, 0] = np.uint32(1 << 13)  # the only allowed id is banned
+    mask[11, 1:] = 0xF0F0F0F0
+    hist, bids, bvals = [], [], []
+    for b, (ids, lead, _, bias, n) in enumerate(spec):
+        ids = np.unique(np.asarray(ids))
+        x[b, ids] = lead + rng.uniform(0.0, 0.5, ids.size)
+        hist.append(np.concatenate([np.repeat(ids, n), rng.integers(0, V, 40)]).astype(np.int32))
+        bids.append(ids if bias else ids[:0])
+        bvals.append(np.full(bids[-1].size, bias, np.float32))
+    cat = lambda t: np.concatenate([[0], np.cumsum([len(r) for r in t])])  # noqa: E731
+    mode = np.full(B, W.MODE_TEMP | W.MODE_TOPP | W.MODE_FREQ | W.MODE_BIAS | W.MODE_GRAMMAR, np.uint32)
+    return W.custom_rows(x if dtype == W.F32 else W.bf16_bits_from_f32(x), dtype, k_max=256, mode=mode,
+                         temperature=np.array([s[2] for s in spec]), top_p=np.full(B, 0.6), freq=np.full(B, 0.25),
+                         bitmask=mask, hist_offsets=cat(hist), hist_ids=np.concatenate(hist), bias_offsets=cat(bids),
+                         bias_ids=np.concatenate(bids), bias_vals=np.concatenate(bvals), position=np.arange(B))
+
+
+@pytest.mark.parametrize("dtype", [W.F32, W.BF16])
+@pytest.mark.parametrize("V", [1999, 9001, 140001])
+def test_normaliser_without_the_raw_maximum(ssb, V, dtype):
+    inp = _dominated_rows(dtype, V)
+    label = f"dominated-{V}-{dtype}"
+    check_sample_full(ssb, inp, f"{label}-full")
+    inp["mode"] = inp["mode"] | np.uint32(W.MODE_LOGPROBS)
+    check_logprobs(ssb, inp, 30, f"{label}-logprobs")
+
+
+# --------------------------------------------------------------------------
 # Graph capture and determinism
 # --------------------------------------------------------------------------
 def test_graph_replay_matches_eager(ssb):
