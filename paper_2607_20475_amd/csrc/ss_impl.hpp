@@ -552,7 +552,10 @@ __device__ __forceinline__ float lp_tau(const KArgs& a, uint32_t mode, int b) {
 // roundings as expf of (v - mu) (1 / tau) at a fifth of its instructions.  The
 // merge recomputes a term bit for bit for the raw copies of patched ids.
 // Terms below 2^-126 of the unit's largest count as zero; so do NaNs.
-__device__ __forceinline__ float lp_scale(float tau) { return (float)(1.4426950408889634 / (double)tau); }
+// (The constant stays finite at subnormal temperatures: the maximum's term is 1.)
+__device__ __forceinline__ float lp_scale(float tau) {
+  return fminf((float)(1.4426950408889634 / (double)tau), 3.402823466e38f);
+}
 __device__ __forceinline__ float lp_term(float v, float mu, float c) {
   return fmaxf(__builtin_amdgcn_exp2f((v - mu) * c), 0.0f);
 }

@@ -1311,6 +1311,19 @@ def test_normaliser_without_the_raw_maximum(ssb, V, dtype):
     check_logprobs(ssb, inp, 30, f"{label}-logprobs")
 
 
+@pytest.mark.parametrize("dtype", [W.F32, W.BF16])
+def test_logprobs_at_subnormal_temperatures(ssb, dtype):
+    """1 / tau beyond float32's range: the maximum keeps its whole weight."""
+    rng = np.random.default_rng(8)
+    tau = np.array([4.0e-39, 3.0e-39, 1.0e-41, 1.5e-45, 1.2e-38], np.float32)
+    B, V = tau.size, 5000
+    x = rng.normal(0.0, 2.0, (B, V)).astype(np.float32)
+    x[4, [3, 4000]] = 30.0  # two equal maxima, in two units
+    inp = W.custom_rows(x if dtype == W.F32 else W.bf16_bits_from_f32(x), dtype,
+                        mode=np.full(B, W.MODE_TEMP | W.MODE_LOGPROBS), temperature=tau)
+    check_logprobs(ssb, inp, 1, f"logprobs-subnormal-tau-{dtype}")
+
+
 # --------------------------------------------------------------------------
 # Graph capture and determinism
 # --------------------------------------------------------------------------
