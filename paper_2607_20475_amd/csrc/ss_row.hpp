@@ -14,7 +14,7 @@
 //      histogram over kNB equal key ranges between tc and the row maximum, a
 //      scan, a scatter into bin order, and each element's rank inside its bin by
 //      comparing it with the bin's few others.  Bins past the k-th element are
-//      left out.  Crowded bins (ties) are sorted by a bitonic network instead.
+//      left out.  Crowded bins (ties) are split again by their own extent.
 //      (Radix selection, two radix searches for the cuts and a bitonic sort for
 //      lists took 26.8 us at B=64 V=2^17 bf16 with a 64-entry list, 87 us for
 //      top-k at B=256 V=2^18 fp32 k<=4096; this takes 7.4 and 16.9 us.)
@@ -66,14 +66,17 @@ struct MSmem {
   alignas(16) uint32_t bins[kNB];        // counts, then starts, then ends; the slow path's digit counts
 };
 constexpr int kSmemFixed = (int)((sizeof(MSmem) + 15) & ~(size_t)15);
-// The sorted list's staging area: room for the k_cap leading elements and the
-// rest of the bin that holds the last of them; after it the sorted list.  The
-// two together hold the next power of two of the staging area (bitonic sort).
-__host__ __device__ constexpr int stage_cap(int k_cap) { return (k_cap + 512 + 255) & ~255; }
-__host__ __device__ constexpr int sorted_cap(int k_cap) {
-  const int s = stage_cap(k_cap), p = next_pow2(s) - s;
-  return (p > k_cap ? p : k_cap) + 8;  // rank loops read up to three entries past a bin
+// The staging area of the list's sort: room for the k_cap leading elements and the
+// rest of the bin that holds the last of them.  Bins of tied fp32 values are as
+// long as their ties, so up to k_cap = 1088 it holds 2 k_cap + 128 (at least 1024)
+// elements; beyond, 512 more than the list, and two workgroups still share a
+// CU up to k_cap = 2048.  After it the sorted list (rank loops read up to three
+// entries past a bin).
+__host__ __device__ constexpr int stage_cap(int k_cap) {
+  const int t = 2 * k_cap + 128 < 2304 ? 2 * k_cap + 128 : 2304, u = k_cap + 512 > 1024 ? k_cap + 512 : 1024;
+  return ((t > u ? t : u) + 255) & ~255;
 }
+__host__ __device__ constexpr int sorted_cap(int k_cap) { return k_cap + 8; }
 constexpr int merge_smem(int k_cap) { return kSmemFixed + 8 * (stage_cap(k_cap) + sorted_cap(k_cap)); }
 static_assert(merge_smem(SS_MAX_K) <= 160 * 1024, "merge LDS beyond a CU's 160 KiB");
 // The verification epilogue keeps a sparse draft list (one 64-bit entry per
@@ -658,6 +661,125 @@ __device__ __forceinline__ void wave_prefix(const T* scratch, int wv, T& before,
   total = x;
 }
 
+// Rank of e among the staged entries [bs, be) of its bin, from the list's start.
+__device__ __forceinline__ uint32_t rank_in_bin(const uint64_t* stage, uint64_t e, uint32_t bs, uint32_t be) {
+  uint32_t r = bs;
+  for (uint32_t j = bs; j < be; j += 4u) {
+    const uint64_t s0 = stage[j], s1 = stage[j + 1u], s2 = stage[j + 2u], s3 = stage[j + 3u];
+    r += (s0 > e ? 1u : 0u) + ((j + 1u < be && s1 > e) ? 1u : 0u) + ((j + 2u < be && s2 > e) ? 1u : 0u) +
+         ((j + 3u < be && s3 > e) ? 1u : 0u);
+  }
+  return r;
+}
+
+// Lists with crowded bins (ties, or a few outliers that stretch the key range) and those
+// of the slow path.  Ranges of `stage` still to be sorted, start << 16 | end, are kept in
+// the wavefronts' record words, their number in bc[5].
+static_assert(stage_cap(SS_MAX_K) / kCrowd <= 4 * kMaxWaves && stage_cap(SS_MAX_K) < 65536,
+              "ranges are disjoint and longer than kCrowd");
+__device__ __forceinline__ uint32_t* ranges(MSmem& S) { return reinterpret_cast<uint32_t*>(S.wred); }
+
+// Entries [s0, s1) of `stage`, in the bins of `bin` (S.bins holds their ends): those of
+// small bins to their place in `sorted`, crowded bins to the ranges.
+template <int BS, typename Bin>
+__device__ __forceinline__ void place_or_defer(MSmem& S, const uint64_t* stage, uint64_t* sorted, uint32_t s0,
+                                               uint32_t s1, uint32_t want, int tid, Bin&& bin) {
+#pragma unroll 1
+  for (uint32_t p = s0 + (uint32_t)tid; p < s1; p += (uint32_t)BS) {
+    const uint64_t e = stage[p];
+    const uint32_t bn = bin(e);
+    const uint32_t bs = bn != 0u ? S.bins[bn - 1u] : s0, be = S.bins[bn];
+    if (be - bs > (uint32_t)kCrowd) {
+      if (p == bs && bs < want) ranges(S)[atomicAdd(&S.bc[5], 1u)] = (bs << 16) | be;
+    } else {
+      const uint32_t r = rank_in_bin(stage, e, bs, be);
+      if (r < want) sorted[r] = e;
+    }
+  }
+}
+
+// Sorts the ranges: one is split into kNB equal ranges of its composites (keys, and
+// among tied keys indices) by its own extent, small ones ranked by comparison and
+// crowded ones split again.  Each split takes eleven bits off a range, and composites
+// differ, so this ends.  (A bitonic network, 66 steps of a barrier and two LDS round
+// trips at 2048 entries: top-k of 50 at B=32 V=2^17 fp32 with 1310 maxima tied took
+// 35.2 us, now 22.4.)
+template <int BS>
+__device__ __forceinline__ void sort_ranges(MSmem& S, uint64_t* stage, uint64_t* sorted, uint32_t want) {
+  constexpr int NW = BS / 64, EL = (stage_cap(SS_MAX_K) + BS - 1) / BS, BPT = kNB / BS;
+  // (values of its own: masks and addresses shared with the usual path would be kept
+  // in registers, and others spilled, across the whole kernel: 14.3 instead of 14.0 us
+  // for B=64 V=2^17 bf16 with a 64-entry list)
+  int tid = threadIdx.x;
+  asm("" : "+v"(tid));
+  const int ln = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+#pragma unroll 1
+  for (;;) {
+    const uint32_t left = uniform(S.bc[5]);
+    if (left == 0u) return;
+    uint32_t s1 = ranges(S)[left - 1u], s0 = s1 >> 16;
+    s1 &= 0xFFFFu;
+    auto keep_in_vgpr = [](uint32_t& x) { asm("" : "+v"(x)); };
+    keep_in_vgpr(s0);
+    keep_in_vgpr(s1);
+    uint64_t el[EL], hi = 0ull, lo = ~0ull;
+#pragma unroll
+    for (int j = 0; j < EL; ++j) {
+      const uint32_t p = s0 + (uint32_t)(tid + j * BS);
+      el[j] = p < s1 ? stage[p] : 0ull;
+      if (p < s1) {
+        hi = max(hi, el[j]);
+        lo = min(lo, el[j]);
+      }
+    }
+    for (int i = tid; i < kNB / 4; i += BS) reinterpret_cast<uint4*>(S.bins)[i] = make_uint4(0u, 0u, 0u, 0u);
+    hi = wave_reduce(hi, [](uint64_t x, uint64_t y) { return x > y ? x : y; });
+    lo = wave_reduce(lo, [](uint64_t x, uint64_t y) { return x < y ? x : y; });
+    if (ln == 0) {
+      S.x64[0][wv] = hi;
+      S.x64[1][wv] = lo;
+    }
+    lds_barrier();
+    if (tid == 0) S.bc[5] = left - 1u;
+#pragma unroll 1
+    for (int w = 0; w < NW; ++w) {
+      hi = max(hi, S.x64[0][w]);
+      lo = min(lo, S.x64[1][w]);
+    }
+    const int sh = max(0, 64 - __clzll((long long)((hi - lo) | 1ull)) - kNBLog);
+    keep_in_vgpr(s1);
+    auto bin = [&](uint64_t e) { return (uint32_t)((hi - e) >> sh); };
+#pragma unroll
+    for (int j = 0; j < EL; ++j)
+      if (s0 + (uint32_t)(tid + j * BS) < s1) atomicAdd(&S.bins[bin(el[j])], 1u);
+    keep_in_vgpr(s1);
+    lds_barrier();
+    uint32_t h[BPT], sum = 0u, run, total;
+#pragma unroll
+    for (int q = 0; q < BPT; ++q) {
+      h[q] = S.bins[tid * BPT + q];
+      sum += h[q];
+    }
+    const uint32_t inc = wave_incl_scan(sum);
+    if (ln == 63) S.x32[0][wv] = inc;
+    lds_barrier();
+    wave_prefix<NW>(S.x32[0], wv, run, total);
+    run += s0 + inc - sum;
+#pragma unroll
+    for (int q = 0; q < BPT; ++q) {
+      S.bins[tid * BPT + q] = run;
+      run += h[q];
+    }
+    lds_barrier();
+#pragma unroll
+    for (int j = 0; j < EL; ++j)
+      if (s0 + (uint32_t)(tid + j * BS) < s1) stage[atomicAdd(&S.bins[bin(el[j])], 1u)] = el[j];
+    lds_barrier();
+    place_or_defer<BS>(S, stage, sorted, s0, s1, want, tid, bin);
+    lds_barrier();
+  }
+}
+
 // Maximum over the NW lanes of every half row (row): lane l holds wave l mod
 // NW's value; uniform.
 template <int NW>
@@ -781,6 +903,7 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
     S.bc[1] = 0u;     // set when one of them is crowded
     S.bc[2] = kNone;  // top-p: last rank kept
     S.bc[3] = kNone;  // min-p: first rank dropped
+    S.bc[5] = 0u;     // crowded ranges of the list
     S.bc[7] = kNone;  // top-p against the whole row: last rank kept
     S.bc[10] = 0u;    // normaliser: units to sum again
     S.bc64[3] = 0ull;
@@ -958,7 +1081,7 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
   uint64_t* sorted = stage + a.pcap;
   const uint64_t* T = sorted;  // the row's list in canonical order
   int nT = 0;
-  bool crowded = false;  // the list (or a superset) is in stage, unsorted
+  bool crowded = false;  // ranges of stage hold (a superset of) the list, unsorted
   uint32_t nB = 0u;      // entries of stage
   if (go) {
     uint32_t sel = 0u, bp[NE];
@@ -1112,21 +1235,18 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
         lds_barrier();
         crowded = uniform(S.bc[1]) != 0u;
         nT = want;
-        if (!crowded) {
+        if (__builtin_expect(!crowded, 1)) {
           for (uint32_t p = (uint32_t)tid; p < nB; p += (uint32_t)BS) {
             const uint64_t e = stage[p];
             const uint32_t bn = bin_of(e);
             const uint32_t bs = bn != 0u ? S.bins[bn - 1u] : 0u, be = S.bins[bn];
-            uint32_t r = bs;
-            for (uint32_t j = bs; j < be; j += 4u) {
-              const uint64_t s0 = stage[j], s1 = stage[j + 1u], s2 = stage[j + 2u], s3 = stage[j + 3u];
-              r += (s0 > e ? 1u : 0u) + ((j + 1u < be && s1 > e) ? 1u : 0u) + ((j + 2u < be && s2 > e) ? 1u : 0u) +
-                   ((j + 3u < be && s3 > e) ? 1u : 0u);
-            }
+            const uint32_t r = rank_in_bin(stage, e, bs, be);
             if (r < (uint32_t)want) sorted[r] = e;
           }
-          lds_barrier();
+        } else {
+          place_or_defer<BS>(S, stage, sorted, 0u, nB, (uint32_t)want, tid, bin_of);
         }
+        lds_barrier();
       }
     }
   }
@@ -1145,17 +1265,15 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
     else
       nB = (uint32_t)slow_select<DT, BS>(a, c, S, stage, pmode, pg, (uint32_t)want);
     nT = min(want, (int)nB);
-    crowded = true;
-  }
-  if (__builtin_expect(crowded, 0)) {
-    T = stage;
-    if (nB > 1u) {
-      const int N = next_pow2((int)nB);
-      for (int i = tid + (int)nB; i < N; i += BS) stage[i] = 0ull;
-      lds_barrier();
-      lds_sort_desc<BS>(stage, N);
+    crowded = nB > 1u;
+    if (!crowded) T = stage;
+    if (tid == 0) {
+      ranges(S)[0] = nB;
+      S.bc[5] = 1u;
     }
+    lds_barrier();
   }
+  if (__builtin_expect(crowded, 0)) sort_ranges<BS>(S, stage, sorted, (uint32_t)nT);
   const bool none = empty || nT == 0;
   if (none) flags = empty ? SS_FLAG_EMPTY : flags | SS_FLAG_EMPTY;
   const uint64_t Mcomp = none ? 0ull : uniform(T[0]);

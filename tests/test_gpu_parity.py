@@ -100,6 +100,7 @@ def check_topk(ssb, inp, label):
     assert bad.size == 0, (label, bad[:5])
     assert np.array_equal(gv.view(np.uint32), rv.view(np.uint32)), label
     say(f"[{label}] ok, fallback rows={int((_np(fl) & FALLBACK > 0).sum())}")
+    return _np(fl)
 
 
 def test_topk_config2_full(ssb):
@@ -1322,6 +1323,50 @@ def test_logprobs_at_subnormal_temperatures(ssb, dtype):
     inp = W.custom_rows(x if dtype == W.F32 else W.bf16_bits_from_f32(x), dtype,
                         mode=np.full(B, W.MODE_TEMP | W.MODE_LOGPROBS), temperature=tau)
     check_logprobs(ssb, inp, 1, f"logprobs-subnormal-tau-{dtype}")
+
+
+# --------------------------------------------------------------------------
+# Lists with crowded bins, and the exact slow path
+# --------------------------------------------------------------------------
+def _crowded_rows(kind, rng, B, V):
+    x = rng.normal(0.0, 2.0, (B, V)).astype(np.float32)
+    step = lambda n: np.arange(n) * (V // n)  # noqa: E731
+    if kind == "tied-spread":    # n equal maxima over the row
+        x[:, step(900 if V < 100000 else 1900)] = 30.0
+    elif kind == "tied-block":   # the same, side by side
+        x[:, V // 3:V // 3 + 350] = 30.0
+    elif kind == "neighbours":   # two adjacent fp32 values tied hundreds of times, far below an outlier
+        x[:, step(1400)] = np.where(np.arange(1400) % 3 == 0, np.nextafter(np.float32(20.0), np.float32(30.0)),
+                                    np.float32(20.0))
+        x[:, 11] = 3e38
+    elif kind == "steps":        # every list entry tied with a few hundred others
+        x = (np.round(x * 2) / 2).astype(np.float32)
+    return x
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("kind,V,km", [
+    ("tied-spread", 32000, 64), ("tied-spread", 131073, 1024), ("tied-spread", 5000, 300), ("tied-block", 40000, 300),
+    ("neighbours", 131073, 1024), ("neighbours", 131073, 4096), ("steps", 9001, 4096), ("steps", 33001, 1200),
+])
+def test_crowded_lists(ssb, dtype, kind, V, km):
+    """Lists whose bins hold hundreds of tied or nearly tied elements, sorted by
+    splitting the crowded ranges; spread ties up to the staging area's size need
+    no slow path."""
+    rng = np.random.default_rng(V + km)
+    B = 5
+    x = _crowded_rows(kind, rng, B, V)
+    x = W.bf16_bits_from_f32(x) if dtype == "bf16" else x
+    dt = W.BF16 if dtype == "bf16" else W.F32
+    k = np.array([km, 50, 1, km // 2, km - 1], np.int32)
+    inp = W.custom_rows(x, dt, k_max=km, top_k=k)
+    flags = check_topk(ssb, inp, f"crowded-{kind}-{V}-{dtype}")
+    if kind == "tied-spread":
+        assert not (flags & FALLBACK).any()
+    inp = W.custom_rows(x, dt, k_max=km, mode=np.full(B, W.MODE_TEMP | W.MODE_TOPK | W.MODE_TOPP), top_k=k,
+                        top_p=np.array([0.9, 0.5, 1.0, 0.8, 0.99]), temperature=np.full(B, 1.5), position=np.arange(B))
+    tok, lp, fl = run_sample(ssb, inp)
+    check_sample(inp, tok, lp, fl, f"crowded-sample-{kind}-{V}-{dtype}")
 
 
 # --------------------------------------------------------------------------
