@@ -1369,6 +1369,45 @@ def test_crowded_lists(ssb, dtype, kind, V, km):
     check_sample(inp, tok, lp, fl, f"crowded-sample-{kind}-{V}-{dtype}")
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("kind,V,km", [
+    ("sorted", 5000, 1024), ("sorted", 140001, 1024), ("one-unit", 131072, 1024), ("one-unit", 6001, 1024),
+    ("tied", 131072, 4096), ("tied", 3001, 1000), ("wide-ties", 70000, 2000),
+])
+def test_slow_path_selection(ssb, dtype, kind, V, km):
+    """Rows whose largest values sit in few units: the bound from the emitted
+    elements (found at once, after some digits, to the last one, by index), units
+    re-read, and a second selection where more than the pool holds lie above
+    it; raw rows and rows with penalties and biases (finals off bf16's grid)."""
+    rng = np.random.default_rng(V + km + 1)
+    B = 6
+    x = rng.normal(0.0, 2.0, (B, V)).astype(np.float32)
+    if kind == "sorted":
+        x = -np.sort(-x, axis=1)
+    elif kind == "one-unit":
+        x[:, V // 2:V // 2 + 700] += 20.0
+    elif kind == "tied":
+        x[:] = 1.0
+    else:
+        x[:, 2048:6000] = 25.0  # two units of ties, below a few larger values
+        x[:, 2100:2400] = 26.0
+    x = W.bf16_bits_from_f32(x) if dtype == "bf16" else x
+    dt = W.BF16 if dtype == "bf16" else W.F32
+    k = np.minimum(np.array([km, 50, km // 3, km - 1, 2, 300]), km).astype(np.int32)
+    flags = check_topk(ssb, W.custom_rows(x, dt, k_max=km, top_k=k), f"slow-{kind}-{V}-{dtype}")
+    if kind in ("sorted", "one-unit"):  # (of tied rows the first unit's region may hold enough)
+        assert (flags & FALLBACK).any()
+    hist = [np.concatenate([rng.integers(0, V, 200), np.arange(40) * 7]).astype(np.int32) for _ in range(B)]
+    bids = [rng.choice(V, 16, replace=False).astype(np.int32) for _ in range(B)]
+    inp = W.custom_rows(x, dt, k_max=km, top_k=k, top_p=np.array([0.99, 1.0, 0.7, 0.9, 1.0, 0.8]),
+                        mode=np.full(B, W.MODE_TEMP | W.MODE_TOPK | W.MODE_TOPP | W.MODE_REP | W.MODE_BIAS),
+                        temperature=np.full(B, 3.0), rep=np.full(B, 1.3), hist_offsets=np.arange(B + 1) * 240,
+                        hist_ids=np.concatenate(hist), bias_offsets=np.arange(B + 1) * 16,
+                        bias_ids=np.concatenate(bids), bias_vals=rng.uniform(-3, 3, 16 * B), position=np.arange(B))
+    tok, lp, fl = run_sample(ssb, inp)
+    check_sample(inp, tok, lp, fl, f"slow-sample-{kind}-{V}-{dtype}")
+
+
 # --------------------------------------------------------------------------
 # Graph capture and determinism
 # --------------------------------------------------------------------------
