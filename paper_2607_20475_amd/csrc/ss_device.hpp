@@ -10,7 +10,6 @@
 namespace ss {
 
 constexpr int kBlock = 512;
-constexpr int kWaves = kBlock / 64;
 // the streaming launch (one unit per wavefront, plus the patch-table
 // workgroups) keeps 256-thread workgroups
 constexpr int kSBlock = 256;
@@ -79,14 +78,10 @@ __device__ inline double uniform01(uint64_t seed, uint32_t request, int64_t posi
   return ((double)w + 0.5) * (1.0 / 4294967296.0);
 }
 
-// weight of a kept token: exp((y - M)/tau), exactly 1 at the maximum
-__device__ inline double weight_of(double y, double M, double tau) {
-  return (y == M) ? 1.0 : exp((y - M) / tau);
-}
-// The same weight with the exponent (y - M) / tau formed in double and the
-// exponential taken in float (about one ulp): relative error near 1e-7, far
-// inside the 1e-5 relative agreement the probabilities are held to, at a
-// fraction of the cost of a double exponential.
+// Weight of a kept token, exp((y - M) / tau), exactly 1 at the maximum: the exponent
+// formed in double, the exponential taken in float (about one ulp).  Relative error
+// near 1e-7, far inside the 1e-5 relative agreement the probabilities are held to, at
+// a fraction of the cost of a double exponential.
 __device__ inline double weight_fast(double y, double M, double inv_tau) {
   return (y == M) ? 1.0 : (double)expf((float)((y - M) * inv_tau));
 }
@@ -159,10 +154,6 @@ template <typename T, typename Op>
 __device__ __forceinline__ T wave_reduce(T v, Op op) {
   v = row_reduce(v, op);
   return op(op(readlane_T(v, 0), readlane_T(v, 16)), op(readlane_T(v, 32), readlane_T(v, 48)));
-}
-template <typename T>
-__device__ __forceinline__ T wave_max(T v) {
-  return wave_reduce(v, [](T x, T y) { return x > y ? x : y; });
 }
 template <typename T>
 __device__ __forceinline__ T wave_min(T v) {

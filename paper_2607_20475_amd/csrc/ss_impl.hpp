@@ -230,7 +230,7 @@ __device__ __forceinline__ uint32_t load_elem_bits(const unsigned char* xrow, in
 // Per-row context
 // ---------------------------------------------------------------------------
 struct Ctx {
-  int row, req, ell;
+  int row;
   uint32_t mode;
   const unsigned char* xrow;
   const int32_t* hist;
@@ -242,15 +242,7 @@ struct Ctx {
   int nbias;
   const uint32_t* mask;
   float rep, freq, pres;
-  float tau, top_p, min_p;  // sampling parameters (tau 1 when the TEMP bit is off)
-  uint64_t seed;
-  int64_t pos;              // Philox position of this row
-  int dtok;                 // verification: draft token of this row (-1: none)
-  bool greedy;
-  bool kcap;
   bool pexact;              // the patched-id bitmap is exact (V <= kPB)
-  bool full_row;            // truncation over the whole row (sampling with a.full, no top-k cut)
-  int k_eff;
 };
 
 // Allow bits of a target row that a tree path maps outside the tree: none
@@ -271,23 +263,16 @@ template <int DT>
 __device__ __forceinline__ Ctx make_ctx(const KArgs& a, int row) {
   Ctx c;
   c.row = row;
+  int b = row, ell = 0;
   if (a.op == OP_VERIFY) {
-    c.req = row / (a.L + 1);
-    c.ell = row % (a.L + 1);
-  } else {
-    c.req = row;
-    c.ell = 0;
+    b = row / (a.L + 1);
+    ell = row % (a.L + 1);
   }
-  const int b = c.req;
   const uint32_t m = (a.op == OP_TOPK ? SS_TOPK : a.mode[b]) & a.feat;
   c.mode = m;
   // read together, used if their bits are set
   const int h0 = a.hist_off[b], h1 = a.hist_off[b + 1], e0 = a.bias_off[b], e1 = a.bias_off[b + 1];
-  const float rep = a.rep[b], freq = a.freq[b], pres = a.pres[b], temp = a.temperature[b];
-  const float top_p = a.top_p[b], min_p = a.min_p[b];
-  const int topk = a.top_k[b];
-  const uint64_t seed = a.seed[b];
-  const int64_t position = a.position[b];
+  const float rep = a.rep[b], freq = a.freq[b], pres = a.pres[b];
   const int64_t srow = a.op == OP_VERIFY ? source_row(a, row) : row;
   c.xrow = reinterpret_cast<const unsigned char*>(a.x) + (size_t)(srow < 0 ? 0 : srow) * (size_t)a.ld * DTT<DT>::ES;
   c.hist = nullptr;
@@ -299,7 +284,7 @@ __device__ __forceinline__ Ctx make_ctx(const KArgs& a, int row) {
     c.nhist = h1 - h0;
     if (a.op == OP_VERIFY && a.draft_tokens) {
       c.extra = a.draft_tokens + (size_t)b * a.L;
-      c.nextra = c.ell;
+      c.nextra = ell;
     }
   }
   c.bias_ids = nullptr;
@@ -315,31 +300,7 @@ __device__ __forceinline__ Ctx make_ctx(const KArgs& a, int row) {
   c.rep = (m & SS_REP) ? rep : 1.0f;
   c.freq = (m & SS_FREQ) ? freq : 0.0f;
   c.pres = (m & SS_PRES) ? pres : 0.0f;
-  c.tau = (m & SS_TEMP) ? temp : 1.0f;
-  c.top_p = (m & SS_TOPP) ? top_p : 1.0f;
-  c.min_p = (m & SS_MINP) ? min_p : 0.0f;
-  c.seed = (a.have & kHaveSeed) ? seed : 0ull;
-  c.pos = ((a.have & kHavePos) ? position : 0) + c.ell;
-  c.dtok = -1;
-  if (a.op == OP_VERIFY && c.ell < a.L) c.dtok = a.draft_tokens[(size_t)b * a.L + c.ell];
-  c.kcap = false;
-  c.full_row = false;
   c.pexact = a.V <= kPB;
-  if (a.op == OP_TOPK) {
-    c.greedy = false;
-    int k = (a.have & kHaveTopK) ? topk : a.k_cap;
-    c.k_eff = k < 0 ? 0 : (k > a.k_cap ? a.k_cap : k);
-  } else if (a.op == OP_LOGPROBS) {  // the leading k_cap tokens of rows with the bit
-    c.greedy = false;
-    c.k_eff = (m & SS_LOGPROBS) ? a.k_cap : 0;
-  } else {
-    c.greedy = (m & SS_GREEDY) || ((m & SS_TEMP) && c.tau <= 0.0f);
-    const int64_t kreq = ((m & SS_TOPK) && topk >= 1) ? (int64_t)topk : (int64_t)INT_MAX;
-    c.k_eff = kreq < a.k_cap ? (int)kreq : a.k_cap;
-    c.kcap = !c.greedy && kreq > a.k_cap;
-    c.full_row = a.full && !c.greedy && !((m & SS_TOPK) && topk >= 1);
-    if (c.greedy) c.k_eff = 1;
-  }
   return c;
 }
 
