@@ -110,9 +110,15 @@ def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
+# torch.cuda.current_stream().cuda_stream without the Stream object (3 us); a private
+# name of torch, so calls go without it where a release has none
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream():
-    # torch.cuda.current_stream().cuda_stream without the Stream object (3 us)
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _dtype_code(t):
@@ -182,7 +188,7 @@ class Params:
             seed=_ptr(self.seed), position=_ptr(self.position))
 
     def packed(self):
-        """The bytes of ``struct()``, for one call."""
+        """The bytes of ``struct()``, for one call (the two agree: tests/test_capi.py)."""
         def ptr(t):
             return 0 if t is None else t.data_ptr()
 

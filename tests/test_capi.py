@@ -156,6 +156,38 @@ def test_invalid_arguments_are_rejected_before_launch(lib):
     assert lib.ss_workspace_init(C.c_void_p(0x10001), 64, None) == -1  # misaligned
 
 
+def test_packed_parameters_are_the_struct():
+    """The bytes a call passes are those of the ctypes structure, field by field, with
+    every array and with each one missing."""
+    import numpy as np
+
+    ssb = pytest.importorskip("paper_2607_20475_amd.binding")
+    rng = np.random.default_rng(3)
+    full = {f: rng.integers(1, 9, (3, 5) if f == "bitmask" else 6) for f in ssb.Params.FIELDS}
+    for drop in (None, *full):
+        p = ssb.Params.from_arrays({**{f: a for f, a in full.items() if f != drop}, "B": 3, "V": 160}, device="cpu")
+        st = p.struct()
+        assert p.packed() == bytes(st), drop
+        assert (st.B, st.V, st.bitmask_ld) == (3, 160, 0 if drop == "bitmask" else 5)
+        missing = [n for n, t in ssb._Params._fields_ if t is C.c_void_p and getattr(st, n) is None]
+        assert len(missing) == (drop is not None), (drop, missing)
+
+
+def test_stream_without_torchs_private_name(monkeypatch):
+    """Where torch has no raw-stream query, the stream object's handle is passed."""
+    import types
+
+    import torch
+
+    ssb = pytest.importorskip("paper_2607_20475_amd.binding")
+    monkeypatch.setattr(ssb, "_raw_stream", None)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=0x5150))
+    assert ssb._stream() == 0x5150
+    monkeypatch.setattr(ssb, "_raw_stream", lambda dev: 0x1000 + dev)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    assert ssb._stream() == 0x1003
+
+
 def test_product_path_does_not_touch_the_oracle():
     pkg = os.path.join(ROOT, "paper_2607_20475_amd")
     for dirpath, _, files in os.walk(pkg):
