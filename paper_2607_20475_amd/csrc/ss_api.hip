@@ -166,7 +166,7 @@ static ss_status launch(KArgs& k, int dtype, const Layout& lay, void* ws, hipStr
   k.ptab = reinterpret_cast<uint32_t*>(w + lay.off_ptab);
   k.usum = (k.op == OP_LOGPROBS || k.full) ? reinterpret_cast<double*>(w + lay.off_usum) : nullptr;
   // patch-table workgroups (a multiple of 8, so the stream's XCD remap holds)
-  k.patch_wgs = (k.feat & (SS_REP | SS_FREQ | SS_PRES | SS_BIAS)) ? (lay.rows + 7) & ~7 : 0;
+  k.patch_wgs = (k.feat & kListBits) ? (lay.rows + 7) & ~7 : 0;
   // parameter arrays that were not given: any readable memory of their length
   // (the workspace holds 16 bytes per unit and row), ignored by feat and have
   k.have = (k.top_k ? kHaveTopK : 0) | (k.seed ? kHaveSeed : 0) | (k.position ? kHavePos : 0);

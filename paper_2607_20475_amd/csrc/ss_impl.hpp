@@ -135,6 +135,7 @@ struct KArgs {
   double* usum;        // log-probabilities: per unit, sum of exp((x - unit max) / tau) over its valid logits
 };
 
+constexpr uint32_t kListBits = SS_REP | SS_FREQ | SS_PRES | SS_BIAS;  // requests with history or bias lists
 enum { kHaveTopK = 1, kHaveSeed = 2, kHavePos = 4 };
 
 // Brings the kernel arguments into the scalar cache in one round trip: each
@@ -304,36 +305,51 @@ __device__ __forceinline__ Ctx make_ctx(const KArgs& a, int row) {
   return c;
 }
 
-// Candidate quota of one unit when a row's top-k is spread over U units: the
-// unit keeps at least its q largest elements, q well above the expected share
-// k/U (five standard deviations plus six), so that the largest unit threshold
-// lies below the row's k-th value except with negligible probability.
-__host__ __device__ inline int quota(int k, int U) {
-  if (U <= 1 || k <= 1) return k;
-  const int kt = (k + U - 1) / U;
+// Candidate quota of one unit when a full unit's share of the row's top-k is kt: the
+// unit keeps at least its q largest elements, q well above that share (five
+// standard deviations plus six), so that the largest unit threshold lies below
+// the row's k-th value except with negligible probability.
+__host__ __device__ inline int quota(int k, int kt) {
   int s = 0;
   while (s * s < kt) ++s;
   const int q = kt + 5 * s + 6;
   return q < k ? q : k;
 }
+// The quota of a unit of a row of V elements in U units.  The share of few units goes
+// by elements: a short last one leaves the others more (k = 4096 at V = 5000 took the
+// slow path in every row, 115 us at B = 64).  Beyond 12 units that is at most a
+// standard deviation of the margin's five, and quotas stay what their loads hold.
+__host__ __device__ inline int unit_quota(int k, int U, int V) {
+  if (U <= 1 || k <= 1) return k;
+  const uint32_t num = (uint32_t)(U <= 12 ? k * kUE : k), den = (uint32_t)(U <= 12 ? V : U);
+  return quota(k, (int)((num + den - 1u) / den));
+}
+// A row of one unit emits its top k, and twice as many when penalties can push some of
+// those down (rows of V = 1000 with 528 listed ids: 43 us with the slow path).
+__host__ __device__ inline int emit_k(int k, int V, uint32_t mode) {
+  const uint32_t m = mode & (V <= kUE ? kListBits : 0u);
+  static_assert(kListBits == 30u, "the sum below reaches 32 with any of the bits");
+  return k << ((m + 30u) >> 5);  // (scalar; a condition goes through a vector register)
+}
 
 // Threshold groups per lane for quota q (32 / G elements each).  Groups of
 // several elements need four times as many groups as the quota, so that two of the
 // largest elements seldom share one; single elements (G = 32) give the exact
-// threshold of any quota, at 32 comparisons per search step.  0 when the quota is
-// the whole unit, which then emits all it has.  (Quotas beyond 128 groups in bf16
-// used to emit everything, which overflowed the merge: k = 4096 at V = 102438,
-// B = 138 took 939 us.)
+// threshold of any quota, at 32 comparisons per search step.  0, and the unit emits all
+// it has, when the quota is half of it: that adds less than the search takes and leaves
+// the row nothing to miss.  (Quotas beyond 128 groups in bf16 used to emit
+// everything, which overflowed the merge: k <= 4096 at V = 102438, B = 138 took 783 us,
+// 45 us with the thresholds.)
 __host__ __device__ inline int thr_groups(int q) {
   for (int G = 1; G <= 16; G <<= 1)
     if (64 * G >= 4 * q) return G;
-  return q < kUE ? 32 : 0;
+  return q < kUE / 2 ? 32 : 0;
 }
 
 // capacity (groups, 16 bytes each) of one unit's candidate region
 __host__ __device__ inline int unit_cap(int k_cap, int U, int dt) {
   const int gpu = groups_per_unit(dt);
-  const int q = quota(k_cap, U);
+  const int q = unit_quota(k_cap, U, U * kUE);
   if (thr_groups(q) == 0) return gpu;
   // room for twice the quota, and, when less than a whole unit, for k_cap
   // elements of one unit: a row tied at its maximum then finds its top-k
@@ -657,10 +673,11 @@ __device__ __forceinline__ void scan_unit(const KArgs& a, int gu, WStage& W) {
     const int k = (a.have & kHaveTopK) ? topk : a.k_cap;
     k_eff = k < 0 ? 0 : min(k, a.k_cap);
   } else if (a.op == OP_LOGPROBS) {
-    k_eff = (mode & SS_LOGPROBS) ? a.k_cap : 0;
+    k_eff = (mode & SS_LOGPROBS) ? emit_k(a.k_cap, a.V, mode) : 0;
   } else {
     const bool greedy = (mode & SS_GREEDY) || ((mode & SS_TEMP) && temp <= 0.0f);
-    k_eff = greedy ? 1 : (((mode & SS_TOPK) && topk >= 1) ? min(topk, a.k_cap) : a.k_cap);
+    const int k = ((mode & SS_TOPK) && topk >= 1) ? min(topk, a.k_cap) : a.k_cap;
+    k_eff = greedy ? 1 : emit_k(k, a.V, mode);
   }
 
   // 3. keys, unit maximum, threshold, emission
@@ -725,7 +742,7 @@ __device__ __forceinline__ void scan_unit(const KArgs& a, int gu, WStage& W) {
     } else if (wm16 < 0x0081u) {
       t16 = 0x0081u;  // nothing valid
     } else {
-      const uint32_t q = (uint32_t)quota(k_eff, a.U);
+      const uint32_t q = (uint32_t)unit_quota(k_eff, a.U, a.V);
       const int G = thr_groups((int)q);
       if (q <= 1) t16 = wm16;
       else if (G == 1) t16 = thr_bf16<1>(kd, q);
@@ -815,7 +832,7 @@ __device__ __forceinline__ void scan_unit(const KArgs& a, int gu, WStage& W) {
     } else if (wm < kKeyFloor) {
       t = kKeyFloor;
     } else {
-      const uint32_t q = (uint32_t)quota(k_eff, a.U);
+      const uint32_t q = (uint32_t)unit_quota(k_eff, a.U, a.V);
       const int G = thr_groups((int)q);
       if (q <= 1) t = wm;
       else if (G == 1) t = thr_f32<1>(kk, q);

@@ -19,7 +19,7 @@ void launch_merge(const KArgs& k, int rows, int smem, hipStream_t st) {
   constexpr int BS = merge_threads<OP>(), EPQ = DT == SS_BF16 ? 4 : 2, NQM = DT == SS_BF16 ? 3 : 6;
   a.tpu = BS / a.U > 1 ? BS / a.U : 1;
   a.tpu_inv = ((1 << 20) + a.tpu - 1) / a.tpu;
-  const int q = quota(a.k_cap, a.U), want = q + q / 8 + 4;
+  const int q = unit_quota(emit_k(a.k_cap, a.V, a.feat), a.U, a.V), want = q + q / 8 + 4;
   const int nq = (want + a.tpu * EPQ - 1) / (a.tpu * EPQ);
   a.nq = nq < 4 ? nq : (nq == 4 ? 4 : NQM);
   if (a.nq > NQM) a.nq = NQM;

@@ -1408,6 +1408,29 @@ def test_slow_path_selection(ssb, dtype, kind, V, km):
     check_sample(inp, tok, lp, fl, f"slow-sample-{kind}-{V}-{dtype}")
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("V,km", [(1000, 1000), (1000, 200), (2047, 2047), (2049, 1500), (2500, 800), (5000, 4096), (7000, 2000)])
+def test_rows_of_few_units(ssb, dtype, V, km):
+    """Lists that take much of a row of one unit, or of a few of which the last is
+    short: the units' quotas hold them, also where penalties lower half of the ids."""
+    rng = np.random.default_rng(V + km)
+    B = 8
+    x = rng.normal(0.0, 2.0, (B, V)).astype(np.float32)
+    x = W.bf16_bits_from_f32(x) if dtype == "bf16" else x
+    dt = W.BF16 if dtype == "bf16" else W.F32
+    k = np.array([km, km - 1, 3 * km // 4, km // 2, km // 3, 50, 2, 1], np.int32)
+    flags = check_topk(ssb, W.custom_rows(x, dt, k_max=km, top_k=k), f"few-units-{V}-{km}-{dtype}")
+    assert not (flags & FALLBACK).any()
+    inp = W.custom_rows(x, dt, k_max=km, top_k=k, top_p=np.full(B, 0.95), temperature=np.full(B, 2.0),
+                        mode=np.full(B, W.MODE_TEMP | W.MODE_TOPK | W.MODE_TOPP | W.MODE_REP),
+                        rep=np.full(B, 1.3), hist_offsets=np.arange(B + 1) * 528, hist_ids=rng.integers(0, V, 528 * B),
+                        position=np.arange(B))
+    tok, lp, fl = run_sample(ssb, inp)
+    check_sample(inp, tok, lp, fl, f"few-units-sample-{V}-{km}-{dtype}")
+    if V <= 2048:
+        assert not (fl[:5] & FALLBACK).any()
+
+
 # --------------------------------------------------------------------------
 # Graph capture and determinism
 # --------------------------------------------------------------------------
