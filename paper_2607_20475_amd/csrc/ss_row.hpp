@@ -66,17 +66,21 @@ struct MSmem {
   alignas(16) uint32_t bins[kNB];        // counts, then starts, then ends; the slow path's digit counts
 };
 constexpr int kSmemFixed = (int)((sizeof(MSmem) + 15) & ~(size_t)15);
-// The staging area of the list's sort: room for the k_cap leading elements and the
-// rest of the bin that holds the last of them.  Bins of tied fp32 values are as
-// long as their ties, so up to k_cap = 1088 it holds 2 k_cap + 128 (at least 1024)
-// elements; beyond, 512 more than the list, and two workgroups still share a
-// CU up to k_cap = 2048.  After it the sorted list (rank loops read up to three
-// entries past a bin).
-__host__ __device__ constexpr int stage_cap(int k_cap) {
-  const int t = 2 * k_cap + 128 < 2304 ? 2 * k_cap + 128 : 2304, u = k_cap + 512 > 1024 ? k_cap + 512 : 1024;
-  return ((t > u ? t : u) + 255) & ~255;
-}
+// The sorted list (rank loops read up to three entries past a bin), and the staging
+// area of its sort before it: room for the k_cap leading elements and the rest of the
+// bin that holds the last of them.  Bins of tied fp32 values are as long as their ties,
+// so it holds 2 k_cap + 128 (at least 1024) elements, but at most 2560 more than the
+// list (sort_ranges keeps a thread's share in registers) and up to k_cap = 2048 only
+// what lets two workgroups share a CU's 160 KB, at least 864 more than the list.
+// (512 more beyond 1088: sampling of 4096 at B=32 V=2^17 fp32 with values in steps of a
+// quarter took the slow path, 145 us.)
 __host__ __device__ constexpr int sorted_cap(int k_cap) { return k_cap + 8; }
+__host__ __device__ constexpr int stage_cap(int k_cap) {
+  const int most = (k_cap < 2432 ? 2 * k_cap + 128 : k_cap + 2560) + 255;
+  const int t = most > 1024 ? most & ~255 : 1024;
+  const int two = ((80 * 1024 - kSmemFixed) / 8 - sorted_cap(k_cap)) & ~31;
+  return k_cap <= 2048 && two < t ? two : t;
+}
 constexpr int merge_smem(int k_cap) { return kSmemFixed + 8 * (stage_cap(k_cap) + sorted_cap(k_cap)); }
 static_assert(merge_smem(SS_MAX_K) <= 160 * 1024, "merge LDS beyond a CU's 160 KiB");
 // The verification epilogue keeps a sparse draft list (one 64-bit entry per
@@ -744,9 +748,11 @@ __device__ __forceinline__ void sort_ranges(MSmem& S, uint64_t* stage, uint64_t*
     auto keep_in_vgpr = [](uint32_t& x) { asm("" : "+v"(x)); };
     keep_in_vgpr(s0);
     keep_in_vgpr(s1);
+    const int n = (int)uniform(s1 - s0);
     uint64_t el[EL], hi = 0ull, lo = ~0ull;
 #pragma unroll
     for (int j = 0; j < EL; ++j) {
+      if (j * BS >= n) break;
       const uint32_t p = s0 + (uint32_t)(tid + j * BS);
       el[j] = p < s1 ? stage[p] : 0ull;
       if (p < s1) {
@@ -772,8 +778,9 @@ __device__ __forceinline__ void sort_ranges(MSmem& S, uint64_t* stage, uint64_t*
     keep_in_vgpr(s1);
     auto bin = [&](uint64_t e) { return (uint32_t)((hi - e) >> sh); };
 #pragma unroll
-    for (int j = 0; j < EL; ++j)
-      if (s0 + (uint32_t)(tid + j * BS) < s1) atomicAdd(&S.bins[bin(el[j])], 1u);
+    for (int j = 0; j < EL; ++j) {
+      if (j * BS < n && s0 + (uint32_t)(tid + j * BS) < s1) atomicAdd(&S.bins[bin(el[j])], 1u);
+    }
     keep_in_vgpr(s1);
     lds_barrier();
     uint32_t h[BPT], sum = 0u, run, total;
@@ -794,8 +801,9 @@ __device__ __forceinline__ void sort_ranges(MSmem& S, uint64_t* stage, uint64_t*
     }
     lds_barrier();
 #pragma unroll
-    for (int j = 0; j < EL; ++j)
-      if (s0 + (uint32_t)(tid + j * BS) < s1) stage[atomicAdd(&S.bins[bin(el[j])], 1u)] = el[j];
+    for (int j = 0; j < EL; ++j) {
+      if (j * BS < n && s0 + (uint32_t)(tid + j * BS) < s1) stage[atomicAdd(&S.bins[bin(el[j])], 1u)] = el[j];
+    }
     lds_barrier();
     place_or_defer<BS>(S, stage, sorted, s0, s1, want, tid, bin);
     lds_barrier();
@@ -1774,7 +1782,7 @@ __device__ __forceinline__ void assemble_request(const KArgs& a, int row, const 
 // (At most 128 registers, so that two workgroups share a CU when there are more
 // rows than CUs; the extended sampling merge needs a few more.)
 template <int DT, int OP, int BS>
-__global__ __launch_bounds__(BS, OP == OP_SAMPLE_X ? 2 : 4) void ss_merge_kernel(KArgs a) {
+__global__ __launch_bounds__(BS, OP == OP_SAMPLE_X ? 3 : 4) void ss_merge_kernel(KArgs a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   MSmem& S = *reinterpret_cast<MSmem*>(smem_raw);
   uint64_t* stage = reinterpret_cast<uint64_t*>(smem_raw + kSmemFixed);

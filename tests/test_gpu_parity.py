@@ -1431,6 +1431,22 @@ def test_rows_of_few_units(ssb, dtype, V, km):
         assert not (fl[:5] & FALLBACK).any()
 
 
+@pytest.mark.parametrize("V,km,ties", [(131072, 4096, 2400), (131073, 1300, 1200), (60001, 2048, 850)])
+def test_long_lists_that_end_in_ties(ssb, V, km, ties):
+    """fp32 rows whose lists end among hundreds or thousands of equal values, spread over
+    the row: their bin fits the staging area."""
+    rng = np.random.default_rng(V)
+    B = 5
+    x = rng.normal(0.0, 2.0, (B, V)).astype(np.float32)
+    for b in range(B):
+        n = km - 3 * (b + 1)  # larger values than the ties
+        ids = rng.permutation(V)[:n + ties + b]
+        x[b, ids] = np.where(np.arange(ids.size) < n, rng.uniform(31.0, 40.0, ids.size), 30.0)
+    k = np.array([km, km - 1, km - 1, km - 1, km - 10], np.int32)
+    flags = check_topk(ssb, W.custom_rows(x, W.F32, k_max=km, top_k=k), f"long-ties-{V}-{km}")
+    assert not (flags & FALLBACK).any()
+
+
 # --------------------------------------------------------------------------
 # Graph capture and determinism
 # --------------------------------------------------------------------------
