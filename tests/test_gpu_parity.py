@@ -1447,6 +1447,29 @@ def test_long_lists_that_end_in_ties(ssb, V, km, ties):
     assert not (flags & FALLBACK).any()
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("V,km,nb,lift", [(131072, 4096, 20, 5.0), (70001, 1000, 20, 300.0), (131072, 512, 400, 3.0),
+                                          (3000, 600, 5, 1e30)])
+def test_finals_above_the_raw_maximum(ssb, dtype, V, km, nb, lift):
+    """Biases that lift a few ids, or more than a bin ranks by comparison, above the
+    raw maximum of closely spaced logits: whole lists in order."""
+    rng = np.random.default_rng(V + nb)
+    B = 6
+    x = rng.uniform(0.0, 1.0, (B, V)).astype(np.float32)
+    bids = np.concatenate([rng.choice(V, nb, replace=False) for _ in range(B)])
+    inp = W.custom_rows(W.bf16_bits_from_f32(x) if dtype == "bf16" else x, W.BF16 if dtype == "bf16" else W.F32,
+                        k_max=km, top_k=np.array([km, km - 1, 500, nb, nb + 1, 1]), temperature=np.full(B, 0.7 * lift),
+                        mode=np.full(B, W.MODE_TEMP | W.MODE_TOPK | W.MODE_BIAS), bias_offsets=np.arange(B + 1) * nb,
+                        bias_ids=bids, bias_vals=rng.uniform(0.1, 1.0, nb * B) * lift, position=np.arange(B))
+    tok, lp, fl, idx, _ = run_sample(ssb, inp, k_out=km)
+    check_sample(inp, tok, lp, fl, f"lifted-{V}-{km}-{nb}-{dtype}")
+    y = oracle.process_logits(inp)["y"].astype(np.float64)
+    for b in range(B):
+        n = int(inp["top_k"][b])
+        order = np.lexsort((np.arange(V), -y[b]))[:n]
+        assert np.array_equal(idx[b, :n], order) and np.all(idx[b, n:] == -1), b
+
+
 # --------------------------------------------------------------------------
 # Graph capture and determinism
 # --------------------------------------------------------------------------
