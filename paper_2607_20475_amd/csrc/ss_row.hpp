@@ -724,17 +724,20 @@ static_assert(stage_cap(SS_MAX_K) / kCrowd <= 4 * kMaxWaves && stage_cap(SS_MAX_
 __device__ __forceinline__ uint32_t* ranges(MSmem& S) { return reinterpret_cast<uint32_t*>(S.wred); }
 
 // Entries [s0, s1) of `stage`, in the bins of `bin` (S.bins holds their ends): those of
-// small bins to their place in `sorted`, crowded bins to the ranges.
+// small bins to their place in `sorted`, crowded bins to the ranges, or, when a bin is
+// one composite (`last`), as they stand.
 template <int BS, typename Bin>
 __device__ __forceinline__ void place_or_defer(MSmem& S, const uint64_t* stage, uint64_t* sorted, uint32_t s0,
-                                               uint32_t s1, uint32_t want, int tid, Bin&& bin) {
+                                               uint32_t s1, uint32_t want, int tid, bool last, Bin&& bin) {
 #pragma unroll 1
   for (uint32_t p = s0 + (uint32_t)tid; p < s1; p += (uint32_t)BS) {
     const uint64_t e = stage[p];
     const uint32_t bn = bin(e);
     const uint32_t bs = bn != 0u ? S.bins[bn - 1u] : s0, be = S.bins[bn];
     if (be - bs > (uint32_t)kCrowd) {
-      if (p == bs && bs < want) ranges(S)[atomicAdd(&S.bc[5], 1u)] = (bs << 16) | be;
+      if (last) {
+        if (p < want) sorted[p] = e;
+      } else if (p == bs && bs < want) ranges(S)[atomicAdd(&S.bc[5], 1u)] = (bs << 16) | be;
     } else {
       const uint32_t r = rank_in_bin(stage, e, bs, be);
       if (r < want) sorted[r] = e;
@@ -744,10 +747,10 @@ __device__ __forceinline__ void place_or_defer(MSmem& S, const uint64_t* stage, 
 
 // Sorts the ranges: one is split into kNB equal ranges of its composites (keys, and
 // among tied keys indices) by its own extent, small ones ranked by comparison and
-// crowded ones split again.  Each split takes eleven bits off a range, and composites
-// differ, so this ends.  (A bitonic network, 66 steps of a barrier and two LDS round
-// trips at 2048 entries: top-k of 50 at B=32 V=2^17 fp32 with 1310 maxima tied took
-// 35.2 us, now 22.4.)
+// crowded ones split again.  Each split takes eleven bits off a range, so this ends, also
+// where calls that overlap on one workspace leave composites that do not differ.
+// (A bitonic network, 66 steps of a barrier and two LDS round trips at 2048 entries:
+// top-k of 50 at B=32 V=2^17 fp32 with 1310 maxima tied took 35.2 us, now 22.4.)
 template <int BS>
 __device__ __forceinline__ void sort_ranges(MSmem& S, uint64_t* stage, uint64_t* sorted, uint32_t want) {
   constexpr int NW = BS / 64, EL = (stage_cap(SS_MAX_K) + BS - 1) / BS, BPT = kNB / BS;
@@ -823,7 +826,7 @@ __device__ __forceinline__ void sort_ranges(MSmem& S, uint64_t* stage, uint64_t*
       if (j * BS < n && s0 + (uint32_t)(tid + j * BS) < s1) stage[atomicAdd(&S.bins[bin(el[j])], 1u)] = el[j];
     }
     lds_barrier();
-    place_or_defer<BS>(S, stage, sorted, s0, s1, want, tid, bin);
+    place_or_defer<BS>(S, stage, sorted, s0, s1, want, tid, sh == 0, bin);
     lds_barrier();
   }
 }
@@ -1306,7 +1309,7 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
             if (r < (uint32_t)want) sorted[r] = e;
           }
         } else {
-          place_or_defer<BS>(S, stage, sorted, 0u, nB, (uint32_t)want, tid, bin_of);
+          place_or_defer<BS>(S, stage, sorted, 0u, nB, (uint32_t)want, tid, false, bin_of);
         }
         lds_barrier();
       }
