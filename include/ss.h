@@ -300,8 +300,10 @@ ss_status ss_process_logits(const void *logits, int dtype, int64_t ld, const ss_
  *             beyond the valid tokens and for requests without the bit.
  *   flags     int32[B] or NULL.
  *   ws        ss_workspace_bytes(SS_OP_LOGPROBS, B, V, 0, n_lp, dtype) bytes.
- * The normaliser's terms are float32 exponentials summed in double
- * (relative error below about 2e-7).
+ * The normaliser's terms are float32 exponentials, summed in double: a term e^-x
+ * of its 2048-token unit's largest has a relative error of up to about
+ * (1 + 1.5 x) 1.2e-7, so the sum's is a few 1e-7 (2.6e-8 measured on model-like
+ * rows) and stays below 3e-6 where most of the mass lies in the tail.
  */
 ss_status ss_logprobs(const void *logits, int dtype, int64_t ld, const ss_params *p, int n_lp,
                       int32_t *out_idx, float *out_lp, int32_t *flags, void *ws, size_t ws_bytes,

@@ -42,9 +42,10 @@ constexpr uint32_t kNone = 0xFFFFFFFFu;
 // Threads of a merge workgroup.  A wavefront issues a dependent instruction
 // every four cycles and a SIMD keeps two wavefronts at that rate, so 512 threads
 // run the fixed part of a row (reductions, scans) as fast as one wavefront
-// would; 1024 made every row of up to 1024 entries slower (B=64 V=2^17 bf16
-// sampling: 12.4 -> 13.9 us, its 64-entry lists 8.9 -> 11.5 us).  Top-k alone
-// lists up to 4096 entries and has little else to do: 1024.
+// would; 1024 made every row of up to 1024 entries slower (this merge in an earlier
+// form, now 10.8 and 7.4 us: B=64 V=2^17 bf16 sampling 12.4 -> 13.9 us, its 64-entry
+// lists 8.9 -> 11.5 us).  Top-k alone lists up to 4096 entries and has little else to do:
+// 1024.
 template <int OP>
 constexpr int merge_threads() {
   return OP == OP_TOPK ? 1024 : kBlock;
@@ -120,7 +121,7 @@ __device__ __forceinline__ T wg_max(T v, T* scratch) {
 }
 
 // Patched-id bitmap position: the id itself when V <= kPB (the bitmap is then
-// exact), else an 18-bit hash (a set bit then needs a table lookup).
+// exact), else a 17-bit hash (a set bit then needs a table lookup).
 __device__ __forceinline__ uint32_t pbit(int id, bool exact) {
   return exact ? (uint32_t)id : (((uint32_t)id * 0x9E3779B1u) >> (32 - kPBLog));
 }
@@ -273,7 +274,7 @@ __device__ __forceinline__ int global_table(const KArgs& a, const Ctx& c, MSmem&
 // Passes are what it costs, and in them adds of many threads to one digit's count:
 // hence a bound found to the digit that suffices, and runs added at once (top-k of
 // 1024 at B=32 V=5000 bf16, 700 of the largest in one unit: 92.7 -> 35.3 us; of 4096
-// in a tied row at V=2^17: 536 -> 250 us).
+// in a tied row at V=2^17: 536 -> 205 us).
 // ---------------------------------------------------------------------------
 template <int DT, int BS>
 __device__ __forceinline__ int slow_select(const KArgs& a, const Ctx& c, MSmem& S, uint64_t* pool, int pmode,
@@ -329,7 +330,7 @@ __device__ __forceinline__ int slow_select(const KArgs& a, const Ctx& c, MSmem& 
       const uint32_t cn = act ? a.rec[g].y : 0u;
       const uint32_t* src = reinterpret_cast<const uint32_t*>(a.cand + g * a.cap);
       // four loads in flight (one at a time: a tied row's top 4096 with penalties at
-      // B=32 V=2^17 bf16 took 942 us)
+      // B=32 V=2^17 bf16 took 940 us, now 775)
       constexpr int ND = 4;
 #pragma unroll 1
       for (uint32_t i = (uint32_t)sub; i < cn; i += (uint32_t)(ND * tpu)) {
@@ -850,6 +851,7 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
   constexpr int EPQ = DT == SS_BF16 ? 4 : 2;   // candidates per 16-byte load
   constexpr int NQM = DT == SS_BF16 ? 3 : 6;   // candidate loads a thread holds at most
   constexpr int EM = SS_MAX_K / BS;            // list entries per thread at most
+  static_assert(OP == OP_TOPK || BS <= kH / 4, "every thread loads words of the patch table");
   const int tid = threadIdx.x;
   const int ln = lane(), wv = __builtin_amdgcn_readfirstlane(wave());
   const int U = a.U;
@@ -1180,9 +1182,12 @@ __device__ __forceinline__ void merge_row(const KArgs& early, int row, MSmem& S,
     constexpr auto all = std::integral_constant<int, NQM>{};
     // f(batch) for every batch of candidates when there are many: each thread
     // walks its share of its unit, or, when lists are far longer than that (rows
-    // tied at their threshold), each wavefront whole units.  A unit whose first
-    // possible element lies below tc has nothing to give (of a tied row, every
-    // unit but the first ones).
+    // tied at their threshold: a few units hold everything), each wavefront whole
+    // units.  Shares keep all threads busy (B=32 V=2^17 bf16, 1024 of uniform values:
+    // 19.6 us, 43.3 by units); units bring all loads to the few useful ones (1024 of a
+    // tied row: 28.6 us, 48.0 by shares); four batches a thread lie between the two.
+    // A unit whose first possible element lies below tc has nothing to give (of a
+    // tied row, every unit but the first ones: 74.4 us if they are read).
     auto walk = [&](auto&& f) {
       if (nbatch <= 4) {
         if (comp_of(r4.z, (uint32_t)(u * kUE)) < tc) scnt = 0u;
